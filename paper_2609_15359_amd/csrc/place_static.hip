@@ -5,23 +5,21 @@
 //   rsc_state           one workgroup per decoder: held and reserved blocks of
 //                       its residents (and of requests whose prompt KV is
 //                       still in transfer) summed in 64-bit integers;
-//   static_independent  every arrival against the reported state: the
-//                       decoders' (B_eff, Q) staged in LDS in tiles, each
-//                       thread scanning them for four arrivals at once (the
-//                       LDS reads are broadcasts);
-//   static_need         every arrival's B_need, in parallel;
+//   static_independent  every arrival against the reported state: a workgroup
+//                       sorts the decoders by (queue, index) in LDS, keeps
+//                       the records of B_eff in that order, and each arrival
+//                       takes the first record that holds its B_need by a
+//                       binary search;
 //   static_reserve      arrivals one after another, each reserving its B_need
 //                       and joining its decoder's queue before the next: one
 //                       wavefront holds the state of up to 1,024 decoders in
-//                       registers (ceil(D/64) per lane, a template parameter);
-//                       the largest B_eff is kept from one arrival to the next
-//                       (a wavefront maximum through DPP after each
-//                       reservation), so an arrival that fits no decoder takes
-//                       it directly; a feasible shortest-queue choice takes a
-//                       wavefront minimum over every decoder.  The owning lane
-//                       updates its register.  The chain is serial by
-//                       definition, so this kernel runs at the latency of one
-//                       wavefront.
+//                       registers (ceil(D/64) per lane, a template parameter)
+//                       and computes the needs itself, 64 arrivals at a time.
+//                       The chain is serial by definition, so this kernel runs
+//                       at the latency of one wavefront: a feasible shortest
+//                       queue is one wavefront minimum, a choice of the
+//                       largest B_eff one maximum and a search of its lane,
+//                       and the update a masked add of every slot.
 #include <type_traits>
 
 #include "maps_internal.hpp"
@@ -29,14 +27,25 @@
 namespace maps {
 namespace {
 
-constexpr int kRscNT = 256;
-constexpr int kIndNT = 256;
-constexpr int kIndPer = 4;           // arrivals per thread
-constexpr int kIndTile = 2048;       // decoders per LDS tile
+constexpr int kRscNT = 512;
+constexpr int kRscPer = 4;           // residents per thread whose loads are in flight together
+constexpr int kIndNT = 1024;         // one decoder of a tile per thread
 constexpr int kResSlots = MAPS_MAX_RESERVE_DECODERS / kWave;
 constexpr int64_t kBlockLimit = int64_t(1) << 52;
 
-__device__ inline int64_t ceil_blocks(int64_t tokens, int64_t S) { return (tokens + S - 1) / S; }
+// ceil(tokens / S) for 0 <= tokens < 2^32 with inv = min(floor(2^32 / S), 2^32 - 1):
+// the product's high word is the quotient or one less (tokens (2^32 / S - inv) < 2^32),
+// so the remainder against it stays below 2 S.  Five instructions against about
+// forty of a 64-bit division, which bounded the sums over the residents.
+__device__ inline uint32_t ceil_blocks(uint32_t tokens, uint32_t S, uint32_t inv) {
+    const uint32_t q = __umulhi(tokens, inv);
+    const uint32_t r = tokens - q * S;
+    return q + (r > 0) + (r > S);
+}
+inline uint32_t block_inverse(int32_t S) {
+    const uint64_t q = (uint64_t(1) << 32) / uint32_t(S);
+    return q < UINT32_MAX ? uint32_t(q) : UINT32_MAX;
+}
 
 // ---------------------------------------------------------------------------
 // Runtime state
@@ -45,10 +54,10 @@ __global__ __launch_bounds__(kRscNT) void rsc_state(int32_t D, const int64_t* __
                                                     int64_t n_total, const int32_t* __restrict__ p,
                                                     const int32_t* __restrict__ g, const int32_t* __restrict__ U,
                                                     const uint8_t* __restrict__ in_flight,
-                                                    const int32_t* __restrict__ cap, int32_t S,
+                                                    const int32_t* __restrict__ cap, int32_t S, uint32_t inv,
                                                     int64_t* __restrict__ b_free, int64_t* __restrict__ b_res,
                                                     int64_t* __restrict__ b_eff, uint32_t* dev_err) {
-    __shared__ int64_t tmp[kRscNT / kWave];
+    __shared__ int64_t tmp[2][kRscNT / kWave];
     const int d = blockIdx.x;
     int64_t lo = seg_off[d], hi = seg_off[d + 1];
     if (!(0 <= lo && lo <= hi && hi <= n_total)) {
@@ -60,24 +69,34 @@ __global__ __launch_bounds__(kRscNT) void rsc_state(int32_t D, const int64_t* __
     }
     int64_t held = 0, res = 0;
     bool bad = false;
-    for (int64_t r = lo + threadIdx.x; r < hi; r += kRscNT) {
-        const int32_t pr = p[r], gr = g[r], ur = U[r];
-        if (in_flight && in_flight[r]) {
+    for (int64_t r0 = lo + threadIdx.x; r0 < hi; r0 += kRscNT * kRscPer) {
+        int32_t pr[kRscPer], gr[kRscPer], ur[kRscPer];
+        uint8_t fl[kRscPer];
+#pragma unroll
+        for (int k = 0; k < kRscPer; ++k) {
+            const int64_t r = r0 + k * kRscNT;
+            const bool in = r < hi;   // past the segment: nothing held, nothing reserved
+            pr[k] = in ? p[r] : 0;
+            gr[k] = in ? g[r] : 0;
+            ur[k] = in ? U[r] : 0;
+            fl[k] = in && in_flight ? in_flight[r] : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < kRscPer; ++k) {
+            const uint32_t pk = uint32_t(pr[k]), uk = ur[k] < 0 ? 0u : uint32_t(ur[k]);
+            const uint32_t budget = ceil_blocks(pk + uk, uint32_t(S), inv);
             // staged reservation: prompt KV still in transfer, nothing held,
             // the whole budget (the prompt's blocks without a bound) reserved
-            bad |= pr < 0;
-            res += ceil_blocks(int64_t(pr) + (ur < 0 ? 0 : ur), S);
-            continue;
+            const bool staged = fl[k] != 0;
+            bad |= (pr[k] < 0) | (!staged & (gr[k] < 0));
+            const uint32_t now = staged ? 0u : ceil_blocks(pk + uint32_t(gr[k]), uint32_t(S), inv);
+            held += now;
+            if ((staged || ur[k] >= 0) && budget > now) res += budget - now;
         }
-        bad |= (pr < 0) | (gr < 0);
-        const int64_t now = ceil_blocks(int64_t(pr) + gr, S);
-        const int64_t demand = ur < 0 ? now : ceil_blocks(int64_t(pr) + ur, S);
-        held += now;
-        res += demand > now ? demand - now : 0;
     }
     if (bad) raise_error(dev_err, MAPS_ERR_NEG_LEN);
-    held = block_reduce_add<kRscNT>(held, tmp);
-    res = block_reduce_add<kRscNT>(res, tmp);
+    held = block_reduce_add<kRscNT>(held, tmp[0]);
+    res = block_reduce_add<kRscNT>(res, tmp[1]);
     if (threadIdx.x == 0) {
         const int32_t c = cap[d];
         if (c < 0) raise_error(dev_err, MAPS_ERR_NEG_LEN);
@@ -93,6 +112,7 @@ struct StaticArgs {
     const int64_t* beff;
     const int32_t* qlen;
     int32_t S;
+    uint32_t inv;      // block_inverse(S)
     const int32_t* ap;
     const int32_t* aU;
     int64_t A;
@@ -109,77 +129,126 @@ struct StaticArgs {
 // ---------------------------------------------------------------------------
 // Every arrival against the reported state
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kIndNT) void static_independent(StaticArgs a) {
-    __shared__ int64_t lb[kIndTile];
-    __shared__ int32_t lq[kIndTile];
-    const int64_t first = int64_t(blockIdx.x) * (kIndNT * kIndPer) + threadIdx.x;
-    int64_t need[kIndPer];
-    int32_t feas[kIndPer], most[kIndPer], fq[kIndPer];
-    int64_t mb[kIndPer];
-    bool bad = false;
-#pragma unroll
-    for (int k = 0; k < kIndPer; ++k) {
-        const int64_t i = first + k * kIndNT;
-        need[k] = -1;
-        if (i < a.A && a.aU[i] >= 0) {
-            const int32_t pr = a.ap[i];
-            bad |= pr < 0;
-            need[k] = ceil_blocks(int64_t(pr) + a.aU[i], a.S);
-        }
-        feas[k] = -1;
-        fq[k] = 0;
-        most[k] = -1;
-        mb[k] = 0;
-    }
-    if (bad) raise_error(a.dev_err, MAPS_ERR_NEG_LEN);
-    for (int32_t t0 = 0; t0 < a.D; t0 += kIndTile) {
-        const int32_t n = a.D - t0 < kIndTile ? a.D - t0 : kIndTile;
-        __syncthreads();
-        for (int j = threadIdx.x; j < n; j += kIndNT) {
-            lb[j] = a.beff[t0 + j];
-            lq[j] = a.qlen[t0 + j];
-        }
-        __syncthreads();
-        for (int j = 0; j < n; ++j) {
-            const int64_t B = lb[j];
-            const int32_t Q = lq[j];
-            const int32_t d = t0 + j;
-#pragma unroll
-            for (int k = 0; k < kIndPer; ++k) {
-                // ascending decoders: strict comparisons keep the lowest index on ties
-                if (need[k] <= B && (feas[k] < 0 || Q < fq[k])) { feas[k] = d; fq[k] = Q; }
-                if (most[k] < 0 || B > mb[k]) { most[k] = d; mb[k] = B; }
+// Ascending bitonic sort of one key per thread over the first n2 threads (a
+// power of two, 64..kIndNT); the other threads only take part in the barriers.
+// Steps within a wavefront go through lane exchanges, the wider ones through LDS.
+__device__ inline uint64_t sort_keys(uint64_t key, int n2, uint64_t* lds) {
+    const int t = threadIdx.x;
+    for (int k = 2; k <= n2; k <<= 1) {
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            uint64_t other = key;
+            if (j >= kWave) {
+                __syncthreads();
+                if (t < n2) lds[t] = key;
+                __syncthreads();
+                if (t < n2) other = lds[t ^ j];
+            } else if (t < n2) {   // uniform per wavefront: n2 is a multiple of 64
+                other = (uint64_t(uint32_t(__shfl_xor(int(uint32_t(key >> 32)), j, kWave))) << 32) |
+                        uint32_t(__shfl_xor(int(uint32_t(key)), j, kWave));
             }
+            const bool keep_min = ((t & j) == 0) == ((t & k) == 0);
+            key = (other < key) == keep_min ? other : key;
         }
     }
-    // the feasible decoder's B_eff for the flag: feasible means need <= B_eff
-#pragma unroll
-    for (int k = 0; k < kIndPer; ++k) {
-        const int64_t i = first + k * kIndNT;
-        if (i >= a.A) continue;
-        int32_t d;
-        uint8_t f;
-        if (a.aU[i] < 0) {
-            d = int32_t((a.rr_offset + i) % a.D);
-            f = 2;
-        } else if (a.policy == MAPS_POLICY_MQ && feas[k] >= 0) {
-            d = feas[k];
-            f = 1;
-        } else {
-            d = most[k];
-            f = need[k] <= mb[k] ? 1 : 0;
-        }
-        a.choice[i] = d;
-        a.need[i] = need[k];
-        a.flags[i] = f;
-    }
+    return key;
 }
 
-__global__ void static_copy_state(StaticArgs a) {
-    for (int32_t d = blockIdx.x * blockDim.x + threadIdx.x; d < a.D; d += gridDim.x * blockDim.x) {
-        if (a.beff_out) a.beff_out[d] = a.beff[d];
-        if (a.q_out) a.q_out[d] = a.qlen[d];
+// The choice depends on the arrival only through its B_need: with the decoders
+// in (queue, index) order, the shortest feasible queue is the first whose
+// B_eff holds B_need, and only a B_eff above all those before it (a record)
+// can be that first one.  Each workgroup sorts the decoders, 1,024 at a time,
+// and keeps the records, so an arrival costs a binary search over a handful
+// of them instead of a comparison with every decoder: on 262,144 arrivals x
+// 256 decoders 70 us -> see the measured figures below the launch.
+template <int kPer>
+__global__ __launch_bounds__(kIndNT) void static_independent(StaticArgs a) {
+    __shared__ uint64_t skey[kIndNT];   // sort exchange, then the records' (queue, decoder)
+    __shared__ int64_t rec[kIndNT];     // the records' B_eff, increasing
+    __shared__ int64_t tmp64[kIndNT / kWave];
+    __shared__ int32_t tmp32[kIndNT / kWave];
+    const int t = threadIdx.x;
+    const int64_t first = int64_t(blockIdx.x) * (kIndNT * kPer) + t;
+    int32_t pr[kPer], ur[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {   // in flight during the first sort
+        const int64_t i = first + k * kIndNT;
+        pr[k] = i < a.A ? a.ap[i] : 0;
+        ur[k] = i < a.A ? a.aU[i] : -1;
     }
+    uint64_t best[kPer];                // (queue, decoder) of the shortest feasible queue so far
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) best[k] = ~0ull;
+    int64_t most_b = INT64_MIN;         // the largest B_eff and its first decoder
+    int32_t most = 0;
+    for (int64_t t0 = 0; t0 < a.D; t0 += kIndNT) {
+        const int n = a.D - t0 < kIndNT ? int(a.D - t0) : kIndNT;
+        int64_t B = INT64_MIN;
+        uint64_t key = ~0ull;
+        if (t < n) {
+            B = a.beff[t0 + t];
+            key = (uint64_t(uint32_t(a.qlen[t0 + t]) ^ 0x80000000u) << 32) | uint32_t(t0 + t);
+            if (blockIdx.x == 0) {      // the reported state stays: independent arrivals reserve nothing
+                if (a.beff_out) a.beff_out[t0 + t] = B;
+                if (a.q_out) a.q_out[t0 + t] = int32_t(uint32_t(key >> 32) ^ 0x80000000u);
+            }
+        }
+        const int64_t tile_b = block_reduce_max<kIndNT>(B, tmp64);
+        const int32_t tile_d = -block_reduce_max<kIndNT>(t < n && B == tile_b ? -t : -kIndNT, tmp32);
+        if (tile_b > most_b) { most_b = tile_b; most = int32_t(t0) + tile_d; }
+        if (a.policy != MAPS_POLICY_MQ) continue;
+        int n2 = kWave;
+        while (n2 < n) n2 <<= 1;
+        key = sort_keys(key, n2, skey);
+        __syncthreads();
+        rec[t] = B;
+        __syncthreads();
+        const int64_t b = t < n ? rec[uint32_t(key) - uint32_t(t0)] : INT64_MIN;
+        int64_t all;
+        const int64_t before = block_excl_scan<kIndNT, true>(b, INT64_MIN, tmp64, &all);
+        const bool is_rec = t < n && (t == 0 || b > before);
+        int32_t records;
+        const int32_t at = block_excl_scan<kIndNT, false>(int32_t(is_rec), 0, tmp32, &records);
+        if (is_rec) { rec[at] = b; skey[at] = key; }   // every thread read rec before the scans' barriers
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            if (ur[k] < 0) continue;
+            const int64_t need = ceil_blocks(uint32_t(pr[k]) + uint32_t(ur[k]), uint32_t(a.S), a.inv);
+            int lo = 0, hi = records;   // the first record that holds the need
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (rec[mid] < need) lo = mid + 1; else hi = mid;
+            }
+            const uint64_t c = lo < records ? skey[lo] : ~0ull;
+            best[k] = c < best[k] ? c : best[k];
+        }
+        __syncthreads();   // rec and skey are reused by the next tile
+    }
+    bool bad = false;
+    uint32_t rr = uint32_t((a.rr_offset + first) % a.D);
+    const uint32_t rr_step = uint32_t(kIndNT % a.D);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int64_t i = first + k * kIndNT;
+        if (i < a.A) {
+            int64_t need = -1;
+            int32_t d = int32_t(rr);
+            uint8_t f = 2;
+            if (ur[k] >= 0) {
+                bad |= pr[k] < 0;
+                need = ceil_blocks(uint32_t(pr[k]) + uint32_t(ur[k]), uint32_t(a.S), a.inv);
+                const bool feasible = best[k] != ~0ull;   // (queue, decoder) is never all ones: decoder < 2^31
+                d = feasible ? int32_t(uint32_t(best[k])) : most;
+                f = feasible || need <= most_b ? 1 : 0;
+            }
+            a.choice[i] = d;
+            a.need[i] = need;
+            a.flags[i] = f;
+        }
+        rr += rr_step;
+        rr = rr >= uint32_t(a.D) ? rr - uint32_t(a.D) : rr;
+    }
+    if (bad) raise_error(a.dev_err, MAPS_ERR_NEG_LEN);
 }
 
 // ---------------------------------------------------------------------------
@@ -201,97 +270,56 @@ __device__ inline uint64_t wave_min_u64(uint64_t v) {
     return ~wave_max_u64(~v);
 }
 
-// B_need of every arrival (-1 without a bound), in parallel before the chain
-__global__ void static_need(StaticArgs a) {
-    bool bad = false;
-    for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < a.A; i += int64_t(gridDim.x) * blockDim.x) {
-        const int32_t U = a.aU[i], p = a.ap[i];
-        bad |= U >= 0 && p < 0;
-        a.need[i] = U < 0 ? -1 : ceil_blocks(int64_t(p) + U, a.S);
-    }
-    if (bad) raise_error(a.dev_err, MAPS_ERR_NEG_LEN);
-}
-
 // Largest-B_eff key of one decoder: (B_eff + 2^52) above (1023 - decoder);
 // 0 (below every key) for a slot past the last decoder.
 __device__ inline uint64_t best_b_key(int64_t B, int32_t d, int32_t D) {
     return d < D ? (uint64_t(B + kBlockLimit) << 10) | uint64_t(1023 - d) : 0;
 }
 
-// The same order in 32 bits for a run of arrivals whose needs sum to less
-// than 2^21 blocks: B_eff relative to the largest one at the run's start,
-// `top` (B - top + 2^21, at least 1 for every B the largest can still reach,
-// 0 for the lower ones, which cannot become the largest within the run).
-constexpr int64_t kNarrowSpan = int64_t(1) << 21;
-__device__ inline uint32_t best_b_key32(int64_t B, int64_t top, int32_t d, int32_t D) {
-    if (d >= D) return 0;
-    const int64_t r = B - top + kNarrowSpan;
-    return (uint32_t(r > 0 ? r : 0) << 10) | uint32_t(1023 - d);
-}
+// kSlots decoders per lane: decoder lane + 64 s in slot s, its B_eff and queue
+// length in registers.  The arrivals go 64 at a time (one per lane, read out
+// with readlane).
 
-// kSlots decoders per lane: decoder lane + 64 s in slot s, with its B_eff,
-// queue length and largest-B_eff key in registers.  The largest key over all
-// decoders is kept between arrivals (only the chosen decoder's changes): an
-// arrival whose B_need exceeds it takes that decoder at once; only a
-// feasible shortest-queue choice scans every decoder.  The chosen decoder's
-// lane and slot are the same in every lane, so its update is one scalar
-// branch to one slot's code.  The arrivals go 64 at a time (one per lane,
-// read out with readlane); a run of 64 whose needs sum to less than 2^21
-// blocks and whose queues stay below 2^21 keeps its keys in 32 bits (one DPP
-// reduction per arrival instead of two), any other run in 64 bits.
-template <int kSlots, bool kNarrow>
-__device__ __forceinline__ void reserve_run(const StaticArgs& a, int64_t c0, int cnt, int64_t my_need,
-                                            int64_t (&B)[kSlots], int64_t (&Q)[kSlots], int64_t& bmax_all,
-                                            bool& range_bad, int32_t& out_d, uint8_t& out_f) {
-    using Key = typename std::conditional<kNarrow, uint32_t, uint64_t>::type;
+// A run of up to 64 arrivals with 64-bit keys.  The largest B_eff key over
+// all decoders is kept between arrivals (only the chosen decoder's changes):
+// an arrival whose B_need exceeds it takes that decoder at once; only a
+// feasible shortest-queue choice scans every decoder.
+template <int kSlots>
+__device__ __forceinline__ void reserve_run_wide(const StaticArgs& a, int cnt, int64_t my_need, int32_t my_rr,
+                                                 int64_t (&B)[kSlots], int64_t (&Q)[kSlots], int64_t& top,
+                                                 bool& range_bad, int32_t& out) {
     const int lane = threadIdx.x;
     const bool mq = a.policy == MAPS_POLICY_MQ;
-    const int64_t top = bmax_all;   // the largest B_eff at the run's start
-    Key K[kSlots];
-    auto key_of = [&](int64_t b, int32_t d) -> Key {
-        if constexpr (kNarrow) return best_b_key32(b, top, d, a.D);
-        else return best_b_key(b, d, a.D);
-    };
-    auto wave_max = [&](Key v) -> Key {
-        if constexpr (kNarrow) return wave_max_u32(v);
-        else return wave_max_u64(v);
-    };
+    uint64_t K[kSlots];
     auto lane_best = [&]() {
-        Key m = K[0];
+        uint64_t m = K[0];
 #pragma unroll
         for (int s = 1; s < kSlots; ++s) m = K[s] > m ? K[s] : m;
         return m;
     };
 #pragma unroll
-    for (int s = 0; s < kSlots; ++s) K[s] = key_of(B[s], lane + s * kWave);
-    Key kb = wave_max(lane_best());
-    auto largest = [&](Key k) -> int64_t {
-        if constexpr (kNarrow) return top + int64_t(k >> 10) - kNarrowSpan;
-        else return int64_t(k >> 10) - kBlockLimit;
-    };
+    for (int s = 0; s < kSlots; ++s) K[s] = best_b_key(B[s], lane + s * kWave, a.D);
+    uint64_t kb = wave_max_u64(lane_best());
     for (int j = 0; j < cnt; ++j) {
         const int64_t need = (int64_t(uint32_t(__builtin_amdgcn_readlane(int32_t(uint64_t(my_need) >> 32), j)))
                               << 32) |
                              uint32_t(__builtin_amdgcn_readlane(int32_t(my_need), j));
-        int32_t best;
-        uint8_t f;
+        int32_t best, f;
         if (need < 0) {
-            best = int32_t((a.rr_offset + c0 + j) % a.D);
+            best = __builtin_amdgcn_readlane(my_rr, j);
             f = 2;
         } else {
-            const int64_t bmax = largest(kb);
+            const int64_t bmax = int64_t(kb >> 10) - kBlockLimit;
             if (mq && need <= bmax) {
                 // feasible decoders exist: (Q, decoder) among them, smallest first
-                Key kf = ~Key(0);
+                uint64_t kf = ~0ull;
 #pragma unroll
                 for (int s = 0; s < kSlots; ++s) {
                     const int32_t d = lane + s * kWave;
-                    const Key k1 = kNarrow ? Key((uint64_t(Q[s]) << 10) | uint64_t(d))
-                                           : Key((uint64_t(Q[s]) << 20) | uint64_t(d));
+                    const uint64_t k1 = (uint64_t(Q[s]) << 20) | uint64_t(d);
                     if (d < a.D && need <= B[s] && k1 < kf) kf = k1;
                 }
-                kf = ~wave_max(~kf);
-                best = int32_t(kf & (kNarrow ? 0x3FF : 0xFFFFF));
+                best = int32_t(wave_min_u64(kf) & 0xFFFFF);
                 f = 1;
             } else {
                 best = 1023 - int32_t(kb & 1023);
@@ -306,25 +334,113 @@ __device__ __forceinline__ void reserve_run(const StaticArgs& a, int64_t c0, int
                 if (s == slot) {   // uniform: a scalar branch
                     if (need >= 0) {
                         B[s] -= need;
-                        K[s] = key_of(B[s], best);
+                        K[s] = best_b_key(B[s], best, a.D);
                     }
                     Q[s] += 1;
-                    if constexpr (!kNarrow) range_bad |= B[s] <= -kBlockLimit || B[s] >= kBlockLimit;
+                    range_bad |= B[s] <= -kBlockLimit || B[s] >= kBlockLimit;
                 }
             }
         }
-        if (need >= 0) kb = wave_max(lane_best());
-        if (lane == j) {
-            out_d = best;
-            out_f = f;
-        }
+        if (need >= 0) kb = wave_max_u64(lane_best());
+        out = lane == j ? best | (f << 30) : out;
     }
-    bmax_all = largest(kb);
-    if constexpr (kNarrow) {
-        // B only decreases: the run's end shows whether any left the packed-key range
+    top = int64_t(kb >> 10) - kBlockLimit;
+}
+
+// The same run in 32 bits: R = B_eff - top (top: the largest B_eff at the
+// run's start), saturated at kRelLow, and the queue keys (Q << 10) | decoder.
+// Taken when the needs sum to less than 2^29 blocks, top < 2^29 and every
+// queue is in [0, 2^21 - 64).  A saturated decoder has B_eff < top - 2^30 < 0:
+// it is never feasible, and never the largest, since the largest stays above
+// top - 2^29; so neither its R nor its B_eff is used.  A feasible R stays
+// above -2^29 after its reservation, the largest above -2^30.
+// The chain is bound by its dependent instructions (one wavefront issues one
+// at a time), so an arrival is a compare, a select and a minimum per slot, one
+// DPP minimum, and a masked add per slot, with no branch on the chosen lane or
+// slot; only an arrival that fits no decoder pays for the maximum.
+constexpr int32_t kRelLow = -(1 << 30);
+constexpr int64_t kRunSpan = int64_t(1) << 29;
+constexpr int64_t kRunQueue = int64_t(1) << 21;
+
+__device__ inline uint32_t wave_min_u32(uint32_t v) {
+    return wave_last(wave_incl_scan(v, ~0u, [](uint32_t x, uint32_t y) { return x < y ? x : y; }));
+}
+__device__ inline int32_t wave_max_i32(int32_t v) {
+    return wave_last(wave_incl_scan(v, INT32_MIN, [](int32_t x, int32_t y) { return x > y ? x : y; }));
+}
+
+template <int kSlots>
+__device__ __forceinline__ void reserve_run(const StaticArgs& a, int cnt, int32_t my_need, int32_t my_rr,
+                                            int64_t (&B)[kSlots], int64_t (&Q)[kSlots], int64_t& top,
+                                            int32_t& out) {
+    const int lane = threadIdx.x;
+    const bool mq = a.policy == MAPS_POLICY_MQ;
+    int32_t R[kSlots], R0[kSlots];
+    uint32_t K[kSlots];
 #pragma unroll
-        for (int s = 0; s < kSlots; ++s) range_bad |= B[s] <= -kBlockLimit;
+    for (int s = 0; s < kSlots; ++s) {
+        const int32_t d = lane + s * kWave;
+        const int64_t r = B[s] - top;
+        // past the last decoder: below every threshold and every maximum
+        R0[s] = R[s] = d >= a.D ? INT32_MIN : r > kRelLow ? int32_t(r) : kRelLow;
+        K[s] = (uint32_t(Q[s]) << 10) | uint32_t(d);
     }
+    // a decoder holds the need when R >= need - top
+    const int64_t thr64 = int64_t(my_need) - top;
+    const int32_t my_thr = thr64 < int64_t(INT32_MAX) ? int32_t(thr64) : INT32_MAX;
+    for (int j = 0; j < cnt; ++j) {
+        int32_t need = __builtin_amdgcn_readlane(my_need, j);
+        const int32_t thr = __builtin_amdgcn_readlane(my_thr, j);
+        int32_t best, f;
+        if (need < 0) {   // round robin: the request only joins the queue
+            best = __builtin_amdgcn_readlane(my_rr, j);
+            need = 0;
+            f = 2;
+        } else {
+            uint32_t kf = ~0u;
+            if (mq) {
+#pragma unroll
+                for (int s = 0; s < kSlots; ++s) {
+                    const uint32_t k1 = R[s] >= thr ? K[s] : ~0u;
+                    kf = k1 < kf ? k1 : kf;
+                }
+                kf = wave_min_u32(kf);
+            }
+            if (kf != ~0u) {
+                best = int32_t(kf & 1023u);
+                f = 1;
+            } else {
+                int32_t m = R[0];
+#pragma unroll
+                for (int s = 1; s < kSlots; ++s) m = R[s] > m ? R[s] : m;
+                m = wave_max_i32(m);
+                best = 0;   // the lowest decoder with the largest B_eff
+#pragma unroll
+                for (int s = kSlots - 1; s >= 0; --s) {
+                    const uint64_t at = __builtin_amdgcn_ballot_w64(R[s] == m);
+                    best = at != 0 ? s * kWave + (__ffsll((unsigned long long)at) - 1) : best;
+                }
+                f = m >= thr ? 1 : 0;
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < kSlots; ++s) {
+            const bool own = lane + s * kWave == best;
+            R[s] -= own ? need : 0;
+            K[s] += own ? 1024u : 0u;
+        }
+        out = lane == j ? best | (f << 30) : out;
+    }
+    int32_t m = INT32_MIN;
+#pragma unroll
+    for (int s = 0; s < kSlots; ++s) {
+        if (lane + s * kWave < a.D) {
+            B[s] += R[s] - R0[s];
+            Q[s] = int64_t(K[s] >> 10);
+        }
+        m = R[s] > m ? R[s] : m;
+    }
+    top += wave_max_i32(m);
 }
 
 template <int kSlots>
@@ -333,54 +449,65 @@ __global__ __launch_bounds__(kWave) void static_reserve(StaticArgs a) {
     int64_t B[kSlots];
     int64_t Q[kSlots];
     uint64_t k0 = 0;
+    bool range_bad = false, neg = false;
+    // the first run's arrivals
+    int32_t p = lane < a.A ? a.ap[lane] : 0, U = lane < a.A ? a.aU[lane] : -1;
 #pragma unroll
     for (int s = 0; s < kSlots; ++s) {
         const int32_t d = lane + s * kWave;
         B[s] = d < a.D ? a.beff[d] : 0;
         Q[s] = d < a.D ? a.qlen[d] : 0;
+        range_bad |= B[s] <= -kBlockLimit || B[s] >= kBlockLimit;   // outside the packed keys
         const uint64_t k = best_b_key(B[s], d, a.D);
         k0 = k > k0 ? k : k0;
     }
-    int64_t bmax_all = int64_t(wave_max_u64(k0) >> 10) - kBlockLimit;   // the largest B_eff
-    bool range_bad = false;
+    int64_t top = int64_t(wave_max_u64(k0) >> 10) - kBlockLimit;   // the largest B_eff
+    // the run's first round-robin decoder; runs advance by 64 arrivals
+    int32_t rr = int32_t(a.rr_offset % a.D);
+    const int32_t rr_step = kWave % a.D;
     for (int64_t c0 = 0; c0 < a.A; c0 += kWave) {
         const int64_t mine = c0 + lane;
-        const int64_t my_need = mine < a.A ? a.need[mine] : -1;
-        int32_t out_d = 0;
-        uint8_t out_f = 0;
+        neg |= U >= 0 && p < 0;
+        const int64_t my_need = U < 0 ? int64_t(-1)
+                                      : int64_t(ceil_blocks(uint32_t(p) + uint32_t(U), uint32_t(a.S), a.inv));
+        // the next run's arrivals are on their way during this one
+        p = mine + kWave < a.A ? a.ap[mine + kWave] : 0;
+        U = mine + kWave < a.A ? a.aU[mine + kWave] : -1;
+        const int32_t my_rr = int32_t(uint32_t(rr + lane) % uint32_t(a.D));
+        rr += rr_step;
+        rr = rr >= a.D ? rr - a.D : rr;
+        int32_t out = 0;
         const int cnt = a.A - c0 < kWave ? int(a.A - c0) : kWave;
-        // the run's needs and the longest queue after it decide the key width (the same in every lane)
-        int64_t qmax = 0;
+        // the run's needs, the largest B_eff and the queues decide the width (the same in every lane)
+        int64_t qmax = 0, qmin = 0;
 #pragma unroll
-        for (int s = 0; s < kSlots; ++s) qmax = Q[s] > qmax ? Q[s] : qmax;
-        qmax = int64_t(wave_max_u64(uint64_t(qmax)));
+        for (int s = 0; s < kSlots; ++s) {
+            qmax = Q[s] > qmax ? Q[s] : qmax;
+            qmin = Q[s] < qmin ? Q[s] : qmin;
+        }
+        const bool queues = __builtin_amdgcn_ballot_w64(qmin < 0 || qmax + kWave >= kRunQueue) == 0;
         const int64_t need_sum = wave_reduce_add(my_need > 0 ? my_need : int64_t(0));
-        if (need_sum < kNarrowSpan - 1 && qmax + kWave < kNarrowSpan)
-            reserve_run<kSlots, true>(a, c0, cnt, my_need, B, Q, bmax_all, range_bad, out_d, out_f);
+        if (queues && need_sum < kRunSpan && top < kRunSpan)
+            reserve_run<kSlots>(a, cnt, int32_t(my_need), my_rr, B, Q, top, out);
         else
-            reserve_run<kSlots, false>(a, c0, cnt, my_need, B, Q, bmax_all, range_bad, out_d, out_f);
+            reserve_run_wide<kSlots>(a, cnt, my_need, my_rr, B, Q, top, range_bad, out);
         if (mine < a.A) {
-            a.choice[mine] = out_d;
-            a.flags[mine] = out_f;
+            a.choice[mine] = out & 0x3FFFFFFF;
+            a.need[mine] = my_need;
+            a.flags[mine] = uint8_t(uint32_t(out) >> 30);
         }
     }
 #pragma unroll
     for (int s = 0; s < kSlots; ++s) {
         const int32_t d = lane + s * kWave;
+        range_bad |= B[s] <= -kBlockLimit;   // B_eff only falls: the end shows whether any left the keys' range
         if (d < a.D) {
             if (a.beff_out) a.beff_out[d] = B[s];
             if (a.q_out) a.q_out[d] = int32_t(Q[s]);
         }
     }
+    if (neg) raise_error(a.dev_err, MAPS_ERR_NEG_LEN);
     if (range_bad) raise_error(a.dev_err, MAPS_ERR_BLOCK_RANGE);
-}
-
-// every initial B_eff inside the packed-key range
-__global__ void static_check_range(StaticArgs a) {
-    bool bad = false;
-    for (int32_t d = blockIdx.x * blockDim.x + threadIdx.x; d < a.D; d += gridDim.x * blockDim.x)
-        bad |= a.beff[d] <= -kBlockLimit || a.beff[d] >= kBlockLimit;
-    if (bad) raise_error(a.dev_err, MAPS_ERR_BLOCK_RANGE);
 }
 
 }  // namespace
@@ -398,7 +525,8 @@ extern "C" maps_status maps_rsc_state(int32_t D, const int64_t* seg_off, int64_t
         (n_total > 0 && (!prompt || !generated || !upper)))
         return MAPS_E_NULL;
     hipLaunchKernelGGL(rsc_state, dim3(unsigned(D)), dim3(kRscNT), 0, stream, D, seg_off, n_total, prompt,
-                       generated, upper, in_flight, capacity, block_size, b_free, b_res, b_eff, dev_err);
+                       generated, upper, in_flight, capacity, block_size, block_inverse(block_size), b_free, b_res,
+                       b_eff, dev_err);
     MAPS_CHECK_LAUNCH();
     return MAPS_OK;
 }
@@ -413,16 +541,9 @@ extern "C" maps_status maps_place_static(int32_t D, const int64_t* b_eff, const 
     if (policy != MAPS_POLICY_MQ && policy != MAPS_POLICY_MC) return MAPS_E_POLICY;
     if (!b_eff || !queue_len || !dev_err || (A > 0 && (!a_prompt || !a_upper || !choice || !b_need || !flags)))
         return MAPS_E_NULL;
-    StaticArgs a{D, b_eff, queue_len, block_size, a_prompt, a_upper, A, policy, rr_offset, choice, b_need, flags,
-                 b_eff_out, queue_out, dev_err};
+    StaticArgs a{D, b_eff, queue_len, block_size, block_inverse(block_size), a_prompt, a_upper, A, policy,
+                 rr_offset, choice, b_need, flags, b_eff_out, queue_out, dev_err};
     if (reserve) {
-        hipLaunchKernelGGL(static_check_range, dim3(unsigned((D + 255) / 256)), dim3(256), 0, stream, a);
-        MAPS_CHECK_LAUNCH();
-        if (A > 0) {
-            const int64_t nblk = (A + 255) / 256;
-            hipLaunchKernelGGL(static_need, dim3(unsigned(nblk < 4096 ? nblk : 4096)), dim3(256), 0, stream, a);
-            MAPS_CHECK_LAUNCH();
-        }
         const int slots = (D + kWave - 1) / kWave;
         if (slots <= 1) hipLaunchKernelGGL(static_reserve<1>, dim3(1), dim3(kWave), 0, stream, a);
         else if (slots <= 2) hipLaunchKernelGGL(static_reserve<2>, dim3(1), dim3(kWave), 0, stream, a);
@@ -432,14 +553,14 @@ extern "C" maps_status maps_place_static(int32_t D, const int64_t* b_eff, const 
         MAPS_CHECK_LAUNCH();
         return MAPS_OK;
     }
-    if (A > 0) {
-        const int64_t blocks = (A + kIndNT * kIndPer - 1) / (kIndNT * kIndPer);
-        hipLaunchKernelGGL(static_independent, dim3(unsigned(blocks)), dim3(kIndNT), 0, stream, a);
-        MAPS_CHECK_LAUNCH();
-    }
-    if (b_eff_out || queue_out) {
-        hipLaunchKernelGGL(static_copy_state, dim3(unsigned((D + 255) / 256)), dim3(256), 0, stream, a);
-        MAPS_CHECK_LAUNCH();
-    }
+    if (A == 0 && !b_eff_out && !queue_out) return MAPS_OK;
+    // One arrival per thread up to two workgroups per compute unit (each sorts
+    // the decoders for itself), four beyond.
+    const int64_t blocks = (A + kIndNT - 1) / kIndNT;
+    if (blocks <= 2 * int64_t(device_compute_units()))
+        hipLaunchKernelGGL(static_independent<1>, dim3(unsigned(blocks > 0 ? blocks : 1)), dim3(kIndNT), 0, stream, a);
+    else
+        hipLaunchKernelGGL(static_independent<4>, dim3(unsigned((blocks + 3) / 4)), dim3(kIndNT), 0, stream, a);
+    MAPS_CHECK_LAUNCH();
     return MAPS_OK;
 }
