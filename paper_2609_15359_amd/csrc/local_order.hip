@@ -7,7 +7,8 @@ namespace maps {
 namespace {
 
 __global__ __launch_bounds__(order::kOrderNT) void local_order_kernel(order::LocalArgs g) {
-    order::order_queue(g, int32_t(blockIdx.x));
+    __shared__ order::LocalLds s;
+    order::order_queue(g, int32_t(blockIdx.x), s);
 }
 
 }  // namespace

@@ -313,6 +313,32 @@ __device__ inline T block_excl_scan(T v, T identity, T* tmp, T* total) {
     return kMax ? (wave_prefix > excl_in_wave ? wave_prefix : excl_in_wave) : wave_prefix + excl_in_wave;
 }
 
+// Ascending bitonic sort of one key per thread over the first n2 threads (a
+// power of two, at least 64 and at most the workgroup's threads); the other
+// threads only take part in the barriers.  Steps within a wavefront go through
+// lane exchanges, the wider ones through `lds` (n2 keys, free when every
+// thread arrives here; last read before the return without a barrier).
+__device__ inline uint64_t block_sort(uint64_t key, int n2, uint64_t* lds) {
+    const int t = threadIdx.x;
+    for (int k = 2; k <= n2; k <<= 1) {
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            uint64_t other = key;
+            if (j >= kWave) {
+                __syncthreads();
+                if (t < n2) lds[t] = key;
+                __syncthreads();
+                if (t < n2) other = lds[t ^ j];
+            } else if (t < n2) {   // uniform per wavefront: n2 is a multiple of 64
+                other = (uint64_t(uint32_t(__shfl_xor(int(uint32_t(key >> 32)), j, kWave))) << 32) |
+                        uint32_t(__shfl_xor(int(uint32_t(key)), j, kWave));
+            }
+            const bool keep_min = ((t & j) == 0) == ((t & k) == 0);
+            key = (other < key) == keep_min ? other : key;
+        }
+    }
+    return key;
+}
+
 // Scan of len elements reached through get(i)/put(i, v), each thread owning
 // one contiguous chunk.  Forward or reverse (suffix), inclusive or exclusive,
 // sum or max.  Returns the total.  Ends with a barrier.

@@ -879,9 +879,10 @@ __global__ __launch_bounds__(256) void place_finish(PlaceArgs g) {
 // runs beside the queue work.
 __global__ __launch_bounds__(order::kOrderNT) void place_finish_order(PlaceArgs g, order::LocalArgs o,
                                                                       int32_t fin_blocks) {
+    __shared__ order::LocalLds s;
     const int32_t D = o.L.D;
     if (int32_t(blockIdx.x) < D)
-        order::order_queue(o, int32_t(blockIdx.x));
+        order::order_queue(o, int32_t(blockIdx.x), s);
     else
         finish_arrivals(g, int64_t(int32_t(blockIdx.x) - D) * order::kOrderNT + threadIdx.x,
                         int64_t(fin_blocks) * order::kOrderNT, nullptr);

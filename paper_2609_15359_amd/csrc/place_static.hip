@@ -128,30 +128,6 @@ struct StaticArgs {
 // ---------------------------------------------------------------------------
 // Every arrival against the reported state
 // ---------------------------------------------------------------------------
-// Ascending bitonic sort of one key per thread over the first n2 threads (a
-// power of two, 64..kIndNT); the other threads only take part in the barriers.
-// Steps within a wavefront go through lane exchanges, the wider ones through LDS.
-__device__ inline uint64_t sort_keys(uint64_t key, int n2, uint64_t* lds) {
-    const int t = threadIdx.x;
-    for (int k = 2; k <= n2; k <<= 1) {
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            uint64_t other = key;
-            if (j >= kWave) {
-                __syncthreads();
-                if (t < n2) lds[t] = key;
-                __syncthreads();
-                if (t < n2) other = lds[t ^ j];
-            } else if (t < n2) {   // uniform per wavefront: n2 is a multiple of 64
-                other = (uint64_t(uint32_t(__shfl_xor(int(uint32_t(key >> 32)), j, kWave))) << 32) |
-                        uint32_t(__shfl_xor(int(uint32_t(key)), j, kWave));
-            }
-            const bool keep_min = ((t & j) == 0) == ((t & k) == 0);
-            key = (other < key) == keep_min ? other : key;
-        }
-    }
-    return key;
-}
-
 // The choice depends on the arrival only through its B_need: with the decoders
 // in (queue, index) order, the shortest feasible queue is the first whose
 // B_eff holds B_need, and only a B_eff above all those before it (a record)
@@ -197,7 +173,7 @@ __global__ __launch_bounds__(kIndNT) void static_independent(StaticArgs a) {
         if (a.policy != MAPS_POLICY_MQ) continue;
         int n2 = kWave;
         while (n2 < n) n2 <<= 1;
-        key = sort_keys(key, n2, skey);
+        key = block_sort(key, n2, skey);
         __syncthreads();
         rec[t] = B;
         __syncthreads();

@@ -368,6 +368,9 @@ __device__ void project_one(Arr a, int32_t d, int64_t lo, int64_t hi, const int3
             const int e = e0 + j;
             pmx[e] = cM[j];
             thr[e] = int32_t(cT[j]);
+            // the occupancy at the event, for the local order of the same
+            // launch (the counters were last read before the barriers above)
+            a.C(e) = cS[j] + a.T(e) * cN[j];
             cold[e] = make_int2(int32_t(cS[j]), int32_t(cN[j] + 1u));
         }
         for (int64_t w = tid; w < W; w += kNT) rank[w] = make_uint2(a.B(w), a.P(w));
@@ -402,7 +405,9 @@ __device__ void project_one(Arr a, int32_t d, int64_t lo, int64_t hi, const int3
 // workgroup of kNT threads; `lds` is the launch's dynamic LDS.
 // [lo, hi): the decoder's residents (seg_off[d], seg_off[d + 1], loaded by the
 // caller); hdr_out (nullable, LDS): receives the decoder header written.
-__device__ inline void project_decoder(int32_t d, int32_t D, int64_t lo, int64_t hi, int64_t n_total,
+// Returns whether the event arrays were kept in LDS: then the events' times are
+// left at lds[0..E) and the occupancies at lds[lds_cap..lds_cap + E).
+__device__ inline bool project_decoder(int32_t d, int32_t D, int64_t lo, int64_t hi, int64_t n_total,
                                        const int32_t* __restrict__ p, const int32_t* __restrict__ g,
                                        const int32_t* __restrict__ U, int32_t u_max, const SnapLayout& L,
                                        void* snap, int32_t* __restrict__ base_peak, int64_t lds_cap,
@@ -434,18 +439,19 @@ __device__ inline void project_decoder(int32_t d, int32_t D, int64_t lo, int64_t
     }
     if (lds_cap > 0 && hi - lo <= lds_cap) {
         LdsArrays a;
-        a.bits = lds;
-        a.wpre = lds + W;
-        a.cnt = lds + 2 * W;
-        a.wsum = a.cnt + lds_cap;
-        a.tau = a.wsum + lds_cap;
-        a.pmx = a.tau + lds_cap;
+        a.tau = lds;
+        a.cnt = lds + lds_cap;
+        a.bits = a.cnt + lds_cap;
+        a.wpre = a.bits + W;
+        a.wsum = a.wpre + W;
+        a.pmx = a.wsum + lds_cap;
         if (hi - lo <= int64_t(kNT) * 4)
             project_one<true, 4, 4>(a, d, lo, hi, p, g, U, u_max, W, L.P, V, slice_off, base_peak, dev_err, sc,
                                     hdr_out);
         else
             project_one<true, kResPer, kEvPer>(a, d, lo, hi, p, g, U, u_max, W, L.P, V, slice_off, base_peak,
                                                dev_err, sc, hdr_out);
+        return true;
     } else {
         HbmArrays a;
         a.rank = reinterpret_cast<uint32_t*>(V.slices + slice_off);
@@ -454,6 +460,7 @@ __device__ inline void project_decoder(int32_t d, int32_t D, int64_t lo, int64_t
         a.cold = nullptr;
         project_one<false, kResPer, kEvPer>(a, d, lo, hi, p, g, U, u_max, W, L.P, V, slice_off, base_peak, dev_err,
                                             sc, hdr_out);
+        return false;
     }
 }
 
@@ -481,17 +488,30 @@ __global__ __launch_bounds__(kNT) void project_order_decoders(int32_t D, const i
                                                               SnapLayout L, void* snap,
                                                               int32_t* __restrict__ base_peak, int64_t lds_cap,
                                                               uint32_t* dev_err, order::LocalArgs o) {
-    extern __shared__ uint32_t lds[];
+    extern __shared__ __align__(16) uint32_t lds[];
     __shared__ DecHeader hdr;
     const int32_t d = int32_t(blockIdx.x);
     // the residents' offsets and the queue's inputs are loaded together
     // first, so the queue's loads are in flight during the projection
     const int64_t lo = seg_off[d], hi = seg_off[d + 1];
     const order::QueueFetch qf = order::fetch_queue(o, d);
-    project_decoder(d, D, lo, hi, n_total, p, g, U, u_max, L, snap, base_peak, lds_cap, dev_err, lds, &hdr);
+    const bool kept =
+        project_decoder(d, D, lo, hi, n_total, p, g, U, u_max, L, snap, base_peak, lds_cap, dev_err, lds, &hdr);
     __syncthreads();   // the slice and header stores of this workgroup are done; hdr holds the header
-    order::order_queue(o, d, n_total, &hdr, &qf);
+    // the order takes the place of the projection's arrays behind the events' times and occupancies
+    order::order_queue(o, d, *reinterpret_cast<order::LocalLds*>(lds + 2 * lds_cap), n_total, &hdr, &qf,
+                       order::LdsEvents{lds, kept ? lds_cap : 0});
 }
+
+// Residents of the largest decoder whose arrays fit the LDS budget (and the
+// register chunks of the LDS path), a multiple of 4; 0: none does.
+int64_t lds_residents(int32_t W) {
+    const size_t fixed = size_t(2) * W * 4;
+    int64_t cap = fixed < kLdsBudget ? int64_t((kLdsBudget - fixed) / 16) : 0;
+    if (cap > int64_t(kNT) * kEvPer) cap = int64_t(kNT) * kEvPer;
+    return cap & ~int64_t(3);
+}
+size_t lds_bytes(int32_t W, int64_t cap) { return cap > 0 ? size_t(2) * W * 4 + size_t(cap) * 16 : 0; }
 
 }  // namespace
 }  // namespace maps
@@ -518,10 +538,8 @@ extern "C" maps_status maps_project(int32_t D, const int64_t* seg_off, int64_t n
         return MAPS_E_NULL;
     const SnapLayout L = snap_layout(D, n_total, u_max);
     if (snapshot_bytes < L.bytes) return MAPS_E_BUFFER;
-    const size_t fixed = size_t(2) * L.W * 4;
-    int64_t cap = fixed < kLdsBudget ? int64_t((kLdsBudget - fixed) / 16) : 0;
-    if (cap > int64_t(kNT) * kEvPer) cap = int64_t(kNT) * kEvPer;   // the register chunks of the LDS path
-    const size_t lds = cap > 0 ? fixed + size_t(cap) * 16 : 0;
+    const int64_t cap = lds_residents(L.W);
+    const size_t lds = lds_bytes(L.W, cap);
     allow_dynamic_lds(project_decoders, lds);
     hipLaunchKernelGGL(project_decoders, dim3(D), dim3(kNT), lds, stream, D, seg_off, n_total, prompt, generated,
                        upper, u_max, L, snapshot, base_peak, cap, dev_err);
@@ -542,13 +560,10 @@ extern "C" maps_status maps_project_order(int32_t D, const int64_t* seg_off, int
         return MAPS_E_NULL;
     const SnapLayout L = snap_layout(D, n_total, u_max);
     if (snapshot_bytes < L.bytes) return MAPS_E_BUFFER;
-    // the local order's LDS is static, beside the projection's: a smaller
-    // budget for the projection's arrays (larger decoders run from HBM)
-    constexpr size_t kFusedBudget = kLdsBudget - sizeof(order::LocalLds);
-    const size_t fixed = size_t(2) * L.W * 4;
-    int64_t cap = fixed < kFusedBudget ? int64_t((kFusedBudget - fixed) / 16) : 0;
-    if (cap > int64_t(kNT) * kEvPer) cap = int64_t(kNT) * kEvPer;
-    const size_t lds = cap > 0 ? fixed + size_t(cap) * 16 : 0;
+    // the local order's LDS lies in the projection's, behind two of its arrays
+    const int64_t cap = lds_residents(L.W);
+    const size_t order_end = size_t(2) * cap * 4 + sizeof(order::LocalLds);
+    const size_t lds = lds_bytes(L.W, cap) > order_end ? lds_bytes(L.W, cap) : order_end;
     order::LocalArgs o;
     o.L = L;
     o.snap = snapshot;

@@ -166,6 +166,37 @@ def test_workload_block16(orc, name):
             say(f"[static] {name} {tag} reserve={reserve}: feasible fraction {np.mean(want[2] & 1):.3f}")
 
 
+@pytest.mark.parametrize("D,A", [(64, 3000), (65, 3000), (1023, 2000), (1024, 2000), (1025, 2000), (2049, 2000),
+                                 (37, 530000)])
+@pytest.mark.parametrize("S", [1, 16, 2**31 - 1])
+def test_records_and_matching(orc, D, A, S):
+    """The records of the sorted decoders at the edges of a tile (equal, negative
+    and extreme queue lengths, a batch past two workgroups a compute unit) and
+    the matching of the reserving chain with about half of the arrivals
+    feasible, so that it is undone and repeated again and again."""
+    rng = np.random.default_rng(D + A + S % 97)
+    a_p, a_U = rng.integers(0, 4000, size=A), rng.integers(-1, 40000, size=A)
+    if S > 16:   # one block holds nearly anything, two the rest
+        a_p[::7] = a_U[::7] = 2**31 - 1
+    need = (a_p + np.maximum(a_U, 0) + S - 1) // S
+    B = rng.integers(-2 * need.mean() - 2, 2 * need.mean() + 3, size=D)
+    Q = rng.choice([0, 1, 1, 2, 5], size=D)
+    for queues in (Q, np.where(rng.random(D) < 0.2, rng.choice([-2**31, -1, 2**31 - 3], size=D), Q)):
+        want = orc.place_static(B, queues, S, a_p, a_U, 0, 3, False)
+        got = _static(B, queues, S, a_p, a_U, 0, 3, False)
+        assert got[5] == 0
+        _compare(got, want, f"records D{D} S{S}")
+    if D > 1024:
+        return
+    room = B + rng.integers(0, 2, size=D) * int(need.sum() // D + 1)
+    A = min(A, 20000)
+    want = orc.place_static(room, Q, S, a_p[:A], a_U[:A], 0, 3, True)
+    say(f"[static] matching D={D} S={S}: feasible {np.mean(want[2] & 1):.3f}")
+    got = _static(room, Q, S, a_p[:A], a_U[:A], 0, 3, True)
+    assert got[5] == 0
+    _compare(got, want, f"matching D{D} S{S}")
+
+
 def test_error_bits():
     _, _, _, err = _rsc([0, 2], [5, -1], [0, 0], [3, 3], [100], 16)
     assert err & 1
