@@ -118,3 +118,33 @@ def test_error_bits():
     n = 1100   # more admitted requests at once than a ready queue holds
     _, err = _gpu(1, 10**6, 500000, [np.zeros(n)], np.zeros(n), np.full(n, 3), np.full(n, 3), [0])
     assert err & 4096
+
+
+@pytest.mark.parametrize("N,C,tokens", [(1, 3000, 20), (3, 1500, 12), (8, 4000, 30)])
+def test_queues_outgrow_the_lanes(orc, N, C, tokens):
+    """Small requests in bursts: the ready queues pass 64 requests in the middle
+    of an event (arrivals, or a completion that makes room for many), where the
+    simulation goes over from one request per lane to the queues in LDS; in the
+    same launch one whose queues stay short and one with a last arrival past 32
+    bits of milliseconds."""
+    rng = np.random.default_rng(N)
+    n = 700
+    prompt = rng.integers(0, tokens, size=n)
+    output = rng.integers(1, tokens, size=n)
+    bound = np.where(rng.random(n) < 0.1, -1, output + rng.integers(0, 4, size=n))
+    prompt[rng.random(n) < 0.02] = C // 2
+    prompt[-1], output[-1], bound[-1] = 5, 7, 7
+    burst = np.sort(rng.integers(0, 12, size=n)) * 97
+    spread = np.arange(n) * (tokens * 2)
+    late = np.concatenate([burst[:-1], [2**33]])
+    rows = [burst, burst, spread, spread, late, late]
+    got, err = _gpu(N, C, 850000, rows, prompt, output, bound, [0, 1] * 3)
+    assert err == 0
+    for s in range(4):
+        _compare(got[s], orc.simulate(N, C, 850000, rows[s], prompt, output, bound, s % 2), f"N={N} case {s}")
+    for s in (4, 5):   # the oracle steps through every millisecond: without the last request
+        want = orc.simulate(N, C, 850000, burst[:-1], prompt[:-1], output[:-1], bound[:-1], s % 2)
+        assert_same(f"N={N} late finish", got[s]["finish_ms"][:-1], want.finish_ms)
+        assert_same(f"N={N} late routed", got[s]["routed"][:-1], want.routed)
+        assert_same(f"N={N} late queue area", got[s]["queue_area"], want.queue_area)
+        assert got[s]["finish_ms"][-1] == 2**33 + 7
