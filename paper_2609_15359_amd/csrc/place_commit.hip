@@ -30,7 +30,10 @@
 //                  that fits keeps its new O values in LDS for the two scans.
 //                  Queue lengths and capacities live in LDS; with at most 512
 //                  decoders the next arrival's lookups are issued with the
-//                  commit's loads.  The chain is serial by definition.
+//                  commit's loads.
+//   commit_rounds  the same chain with the commits of a round of arrivals in
+//                  parallel, for policy MQ while decoders are feasible: see
+//                  there.  commit_serial goes on where it ends.
 #include "maps_internal.hpp"
 
 namespace maps {
@@ -48,7 +51,26 @@ constexpr int kTailPer = kFloorBlock / kSerialNT;   // steps of a commit's own b
 
 struct CommitLayout {
     int32_t D, L, NB;      // decoders, steps per decoder (u_max + 1), floor blocks per decoder
-    size_t off_O, off_PF, off_SA, off_F, bytes;
+    size_t off_O, off_PF, off_SA, off_F, off_ctl, bytes;
+};
+
+// The exchange of commit_rounds between the master and the owners, in device
+// memory: every access is a device-coherent load or store (no cache holds it).
+constexpr int kWindow = 128;        // arrivals evaluated ahead in a round
+constexpr int kMaskWords = kWindow / 64;
+constexpr int kRoundDecoders = 1024;
+constexpr int kMaxOwners = 1024;
+struct RoundControl {
+    uint32_t checked;      // owners that run
+    uint32_t decision;     // 0 open, 1 the rounds run, 2 they do not
+    uint32_t round;        // the last round published
+    uint32_t more;         // of that round: whether another follows
+    int64_t next;          // the first arrival after it; after the last one, the serial chain's first
+    uint32_t ready[kMaxOwners];                      // the round each owner has evaluated
+    int32_t assign[kRoundDecoders];                  // the window's arrival committed to each decoder, or -1
+    uint64_t feasible[kRoundDecoders][kMaskWords];   // the window's arrivals that each decoder holds
+    int64_t over[kRoundDecoders];                    // overflow of the window's first arrival with a bound
+    int32_t queue[kRoundDecoders];                   // queue lengths after the rounds (for the next launch)
 };
 
 CommitLayout commit_layout(int32_t D, int32_t u_max) {
@@ -61,7 +83,8 @@ CommitLayout commit_layout(int32_t D, int32_t u_max) {
     c.off_PF = dense;
     c.off_SA = 2 * dense;
     c.off_F = 3 * dense;
-    c.bytes = c.off_F + align256(size_t(D) * size_t(c.NB) * sizeof(int64_t));
+    c.off_ctl = c.off_F + align256(size_t(D) * size_t(c.NB) * sizeof(int64_t));
+    c.bytes = c.off_ctl + align256(sizeof(RoundControl));
     return c;
 }
 // the blocks after a commit's own: at most NB - 1
@@ -91,6 +114,8 @@ struct CommitArgs {
     uint8_t* flags;
     int32_t* queue_out;
     uint32_t* dev_err;
+    RoundControl* ctl;
+    int32_t owners;      // workgroups of commit_rounds that own decoders
 };
 
 __device__ inline int64_t max64(int64_t a, int64_t b) { return a > b ? a : b; }
@@ -99,7 +124,7 @@ __device__ inline int64_t max64(int64_t a, int64_t b) { return a > b ? a : b; }
 // Dense curves of every decoder from the snapshot
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kCommitNT) void commit_init(CommitArgs a) {
-    __shared__ int64_t tmp[kWaves];
+    __shared__ int64_t tmp[2][kWaves];
     const int d = blockIdx.x;
     const int32_t L = a.L;
     int64_t* O = a.O + int64_t(d) * L;
@@ -107,6 +132,13 @@ __global__ __launch_bounds__(kCommitNT) void commit_init(CommitArgs a) {
     int64_t* SA = a.SA + int64_t(d) * L;
     int64_t* F = a.F + int64_t(d) * a.NB;
     for (int32_t i = threadIdx.x; i < a.NB; i += kCommitNT) F[i] = 0;
+    if (d == 0 && a.owners > 0) {   // the exchange of the rounds starts open
+        if (threadIdx.x == 0) {
+            a.ctl->checked = a.ctl->decision = a.ctl->round = a.ctl->more = 0;
+            a.ctl->next = 0;
+        }
+        for (int32_t i = threadIdx.x; i < kMaxOwners; i += kCommitNT) a.ctl->ready[i] = 0;
+    }
 
     const SnapView V = snap_view(const_cast<void*>(a.snap), a.S);
     const SnapHeader* hs = V.hdr;
@@ -133,43 +165,49 @@ __global__ __launch_bounds__(kCommitNT) void commit_init(CommitArgs a) {
         const int2 c = cold[e];
         return int64_t(c.x) + int64_t(t) * (c.y - 1);
     };
-    const int32_t chunk = (L + kCommitNT - 1) / kCommitNT;
-    const int32_t b = threadIdx.x * chunk, e = b + chunk < L ? b + chunk : L;
-    int64_t mpre = 0, msuf = 0;
-    for (int32_t t = b; t < e; ++t) {
-        const int64_t o = occ(t);
-        O[t] = o;
-        mpre = max64(mpre, o + t);
-        msuf = max64(msuf, o);
-    }
-    int64_t total;
-    int64_t run = block_excl_scan<kCommitNT, true>(mpre, int64_t(0), tmp, &total);
-    for (int32_t t = b; t < e; ++t) {
-        run = max64(run, O[t] + t);
-        PF[t] = run;
-    }
-    // suffix: the largest O over the chunks after this thread's
-    __syncthreads();
+    // Each wavefront takes one segment of whole rows of 64 steps, a step per
+    // lane, so that every array is written in whole cache lines (with a chunk
+    // of consecutive steps per thread the 201 MB of 256 decoders x 32,769 steps
+    // took 539 us): the segments' maxima first, then the rows upwards for PF and
+    // downwards for SA, each with a wavefront scan and a carry.
     const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
-    int64_t after = 0;
-    {
-        // reverse exclusive scan: thread i receives max over threads > i
-        int64_t incl = msuf;
-        // within the wavefront, from the top lane down: lane i sees lanes i..63
-        for (int k = 1; k < kWave; k <<= 1) {
-            const int64_t x = __shfl_down(incl, k, kWave);
-            if (lane + k < kWave) incl = max64(incl, x);
+    const int32_t rows = (L + kWave - 1) / kWave, per = (rows + kWaves - 1) / kWaves;
+    const int32_t r0 = wid * per < rows ? wid * per : rows, r1 = r0 + per < rows ? r0 + per : rows;
+    int64_t mpre = 0, msuf = 0;
+    for (int32_t r = r0; r < r1; ++r) {
+        const int32_t t = r * kWave + lane;
+        if (t < L) {
+            const int64_t o = occ(t);
+            mpre = max64(mpre, o + t);
+            msuf = max64(msuf, o);
         }
-        if (lane == 0) tmp[wid] = incl;
-        __syncthreads();
-        for (int i = wid + 1; i < kWaves; ++i) after = max64(after, tmp[i]);
-        const int64_t next = __shfl_down(incl, 1, kWave);
-        if (lane + 1 < kWave) after = max64(after, next);
     }
-    int64_t s = after;
-    for (int32_t t = e - 1; t >= b; --t) {
-        SA[t] = s;
-        s = max64(s, O[t]);
+    mpre = wave_reduce_max(mpre);
+    msuf = wave_reduce_max(msuf);
+    if (lane == 0) { tmp[0][wid] = mpre; tmp[1][wid] = msuf; }
+    __syncthreads();
+    int64_t run = 0, after = 0;   // over the segments below and above this one
+    for (int i = 0; i < kWaves; ++i) {
+        if (i < wid) run = max64(run, tmp[0][i]);
+        if (i > wid) after = max64(after, tmp[1][i]);
+    }
+    for (int32_t r = r0; r < r1; ++r) {
+        const int32_t t = r * kWave + lane;
+        const int64_t o = t < L ? occ(t) : 0;
+        const int64_t pf = max64(run, wave_incl_scan_max(t < L ? o + t : int64_t(0)));
+        if (t < L) {
+            O[t] = o;
+            PF[t] = pf;
+        }
+        run = wave_last(pf);
+    }
+    for (int32_t r = r1 - 1; r >= r0; --r) {
+        // lane i takes the row's step 63 - i: the scan runs down the steps
+        const int32_t t = r * kWave + (kWave - 1 - lane);
+        const int64_t o = t < L ? occ(t) : 0;
+        const int64_t incl = max64(after, wave_incl_scan_max(o));
+        if (t < L) SA[t] = wave_shift_up1(incl, after);
+        after = wave_last(incl);
     }
 }
 
@@ -397,41 +435,56 @@ __device__ inline int64_t commit_range(const CommitArgs& a, SType* stage, int32_
     return v;
 }
 
-// One workgroup for the whole chain.  kPre (D <= kSerialNT): thread d owns
+// LDS of the chain's workgroup beside the dynamic part.
+struct ChainLds {
+    int32_t tile_p[2][kSerialNT], tile_U[2][kSerialNT];   // arrivals of the current and next tile
+    int64_t skey[kSerialWaves], scan_tmp[kSerialWaves];
+    int32_t sd[kSerialWaves];
+    int64_t speak;
+    Capture cap;
+};
+
+// The new O values of a commit fit 32 bits when its peak plus U does: they are
+// at most peak + Uc (O(t) <= O(t) + t <= PF(Uc) <= peak - p, plus p + t), and
+// the stage holds twice as many of them.
+__device__ inline int64_t commit_any(const CommitArgs& a, int64_t* ostage, int64_t peak, int32_t bd, int64_t p,
+                                     int32_t Uc, int32_t un, int32_t pre_d, PeakIn* cur, ChainLds& w) {
+    const bool narrow = peak + Uc < int64_t(INT32_MAX);
+    return Uc < a.stage_cap ? commit_range<true>(a, ostage, bd, p, Uc, un, pre_d, cur, &w.cap, w.scan_tmp)
+           : narrow && Uc < 2 * int64_t(a.stage_cap)
+               ? commit_range<true, int32_t>(a, reinterpret_cast<int32_t*>(ostage), bd, p, Uc, un, pre_d, cur, &w.cap,
+                                             w.scan_tmp)
+               : commit_range<false>(a, ostage, bd, p, Uc, un, pre_d, cur, &w.cap, w.scan_tmp);
+}
+
+// One workgroup for the chain from arrival `first` on (the queue lengths in Q
+// and the capacities in C are ready).  kPre (D <= kSerialNT): thread d owns
 // decoder d, and the next arrival's peak inputs are loaded while the current
 // arrival is committed; only the committed decoder's inputs change, and its
 // thread patches them from the values the commit captured.  Otherwise every
 // thread evaluates its decoders d, d + kSerialNT, ... after each commit.
 template <bool kPre>
-__global__ __launch_bounds__(kSerialNT) void commit_serial(CommitArgs a) {
-    extern __shared__ int32_t lds[];
-    int32_t* Q = lds;                  // [D] running queue lengths
-    int32_t* C = lds + a.S.D;          // [D] capacities
-    int64_t* ostage = reinterpret_cast<int64_t*>(lds + 2 * a.S.D);   // [stage_cap] a commit's new O values
-    __shared__ int32_t tile_p[2][kSerialNT], tile_U[2][kSerialNT];   // arrivals of the current and next tile
-    __shared__ int64_t skey[kSerialWaves], scan_tmp[kSerialWaves];
-    __shared__ int32_t sd[kSerialWaves];
-    __shared__ int64_t speak;
-    __shared__ Capture cap;
+__device__ inline void serial_chain(const CommitArgs& a, int64_t first, int32_t* Q, int32_t* C, int64_t* ostage,
+                                    ChainLds& w) {
+    auto& tile_p = w.tile_p;
+    auto& tile_U = w.tile_U;
+    auto& skey = w.skey;
+    auto& sd = w.sd;
+    auto& speak = w.speak;
+    auto& cap = w.cap;
     const int32_t D = a.S.D, L = a.L, T = L - 1;
     const int tid = threadIdx.x;
-    bool neg = false;
-    for (int32_t d = tid; d < D; d += kSerialNT) {
-        Q[d] = a.qlen[d];
-        C[d] = a.cap[d];
-        neg |= Q[d] < 0 || C[d] < 0;
-    }
-    if (neg) raise_error(a.dev_err, MAPS_ERR_NEG_LEN);
     auto stage = [&](int64_t tile) {   // arrivals of `tile` into its buffer
         const int64_t j = tile * kSerialNT + tid;
         tile_p[tile & 1][tid] = j < a.A ? a.ap[j] : 0;
         tile_U[tile & 1][tid] = j < a.A ? a.aU[j] : -1;
     };
-    stage(0);
+    stage(first / kSerialNT);
+    if (first % kSerialNT != 0) stage(first / kSerialNT + 1);
     __syncthreads();
     PeakIn cur{0, 0, 0};
     int64_t have = -1;   // the arrival whose inputs `cur` holds
-    for (int64_t i = 0; i < a.A; ++i) {
+    for (int64_t i = first; i < a.A; ++i) {
         // the next tile is staged at the first arrival of a tile; the
         // barriers of that arrival precede every read of it
         if (i % kSerialNT == 0) stage(i / kSerialNT + 1);
@@ -497,15 +550,7 @@ __global__ __launch_bounds__(kSerialNT) void commit_serial(CommitArgs a) {
             if (Un >= 0) un = Un < T ? Un : T;
         }
         const int32_t pre_d = kPre && tid < D ? tid : -1;
-        // the new O values are at most peak + Uc (O(t) <= O(t) + t <= PF(Uc) <= peak - p, plus p + t): below
-        // 2^31 they fit the stage as 32-bit values, twice as many of them
-        const bool narrow = peak + Uc < int64_t(INT32_MAX);
-        const int64_t v =
-            Uc < a.stage_cap ? commit_range<true>(a, ostage, bd, p, Uc, un, pre_d, &cur, &cap, scan_tmp)
-            : narrow && Uc < 2 * int64_t(a.stage_cap)
-                ? commit_range<true, int32_t>(a, reinterpret_cast<int32_t*>(ostage), bd, p, Uc, un, pre_d, &cur,
-                                              &cap, scan_tmp)
-                : commit_range<false>(a, ostage, bd, p, Uc, un, pre_d, &cur, &cap, scan_tmp);
+        const int64_t v = commit_any(a, ostage, peak, bd, p, Uc, un, pre_d, &cur, w);
         if constexpr (kPre) {
             if (un >= 0) {
                 if (tid < D) {
@@ -521,6 +566,319 @@ __global__ __launch_bounds__(kSerialNT) void commit_serial(CommitArgs a) {
     }
     if (a.queue_out)
         for (int32_t d = tid; d < D; d += kSerialNT) a.queue_out[d] = Q[d];
+}
+
+// The chain over the whole batch, or from where the rounds ended.
+template <bool kPre>
+__global__ __launch_bounds__(kSerialNT) void commit_serial(CommitArgs a) {
+    extern __shared__ __align__(16) int32_t lds[];   // [D] queue lengths, [D] capacities, the stage
+    __shared__ ChainLds w;
+    const int32_t D = a.S.D;
+    int32_t* Q = lds;
+    int32_t* C = lds + D;
+    bool neg = false;
+    for (int32_t d = threadIdx.x; d < D; d += kSerialNT) {
+        Q[d] = a.qlen[d];
+        C[d] = a.cap[d];
+        neg |= Q[d] < 0 || C[d] < 0;
+        if (a.owners > 0 && a.ctl->next > 0) Q[d] = a.ctl->queue[d];
+    }
+    if (neg) raise_error(a.dev_err, MAPS_ERR_NEG_LEN);
+    serial_chain<kPre>(a, a.owners > 0 ? a.ctl->next : 0, Q, C, reinterpret_cast<int64_t*>(lds + 2 * D), w);
+}
+
+// ---------------------------------------------------------------------------
+// Rounds of arrivals with their commits in parallel (policy MQ)
+// ---------------------------------------------------------------------------
+//
+// With feasible decoders an arrival takes the first of them in (queue length,
+// index) order, and a commit only makes its decoder worse: a longer queue and
+// higher peaks.  So against the curves as they stand at the start of a round,
+// arrivals in order can each take their first feasible decoder until one meets
+// a decoder taken earlier in the round (which needs that decoder's new curve,
+// unless the old one did not hold the arrival either: then the new one does
+// not): up to there every choice is the serial one, the decoders are distinct,
+// and their commits run in parallel.  An arrival that no decoder holds takes
+// the smallest overflow, which is known exactly for the first of a round.
+// A round is about one level of the queue lengths: 4,096 arrivals on 256
+// decoders with queues of 0..63 take about 60 rounds.
+//
+// Each decoder belongs to one owner workgroup, which keeps its curves in the
+// L2 of its XCD: it evaluates the window of the next 128 arrivals against them
+// (a bit each), and commits what the round gives its decoders.  Workgroup 0,
+// the master, matches the window in one wavefront (decoder lane + 64 s in slot
+// s).  Only the bits and the matches pass between them, by device-coherent
+// stores followed by a round number; the curves never leave their XCD.
+//
+// The master starts the rounds only when every owner has checked in, so that
+// all of them run; when that takes longer than kCheckIn (workgroups of other
+// kernels hold the compute units) the owners are sent home, so no wait depends
+// on a workgroup that is not running.  The rounds also end when they hold too
+// few arrivals to pay (no decoder is feasible any more, and commits do not make
+// any feasible again).  The serial chain's launch takes up what is left.
+// Commit of 4,096 arrivals: COMMIT_FIGURES.
+constexpr int kReviewRounds = 32;            // rounds after which the master looks at what they held
+constexpr uint64_t kCheckIn = 20000;         // 200 us at the 100 MHz of the constant clock
+constexpr uint32_t kMostPolls = 1u << 22;    // an owner or the master that is not heard of for seconds
+
+template <typename T>
+__device__ inline T co_load(const T* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ inline void co_store(T* p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Every store of this wavefront has reached memory, and none of its later
+// accesses is issued before.
+__device__ inline void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// What the master published last, in every thread of an owner.
+struct Published {
+    uint32_t more;
+    int64_t next;
+};
+
+__device__ inline void owner_rounds(const CommitArgs& a, int64_t* ostage, ChainLds& w, Published& pub) {
+    const int tid = threadIdx.x, lane = tid % kWave;
+    const int32_t D = a.S.D, T = a.L - 1, P = a.owners;
+    const int32_t own = int32_t(blockIdx.x) - 1;   // decoders own, own + P, ...
+    if (tid == 0) {
+        __hip_atomic_fetch_add(&a.ctl->checked, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        uint32_t decision = 0;
+        for (uint32_t i = 0; i < kMostPolls && decision == 0; ++i) {
+            decision = co_load(&a.ctl->decision);
+            if (decision == 0) __builtin_amdgcn_s_sleep(4);
+        }
+        pub.more = decision;
+    }
+    __syncthreads();
+    if (pub.more != 1u) return;   // the rounds do not run
+    int64_t pos = 0;
+    for (uint32_t round = 1;; ++round) {
+        // the window against this owner's decoders: kSerialNT / kWindow of them at a time
+        constexpr int kTogether = kSerialNT / kWindow;
+        const int j = tid % kWindow;
+        const int64_t i = pos + j;
+        const int32_t U = i < a.A ? a.aU[i] : -1, p0 = i < a.A ? a.ap[i] : 0;
+        const int32_t Uc = U < T ? U : T;
+        const int64_t p = p0 < 0 ? 0 : p0;
+        // the window's first arrival with a bound: in the first half, else in the second
+        if (tid < kWindow) w.skey[tid / kWave] = int64_t(__builtin_amdgcn_ballot_w64(U >= 0));
+        __syncthreads();
+        const uint64_t b0 = uint64_t(w.skey[0]), b1 = uint64_t(w.skey[1]);
+        const int j0 = b0 != 0 ? __ffsll((unsigned long long)b0) - 1
+                               : b1 != 0 ? kWave + __ffsll((unsigned long long)b1) - 1 : -1;
+        for (int32_t k = tid / kWindow; own + int64_t(k) * P < D; k += kTogether) {
+            const int32_t d = own + k * P;
+            bool holds = false;
+            if (U >= 0) {
+                const PeakIn in = peak_load(a, d, Uc);
+                const int64_t over = max64(p + max64(in.pf, in.fl), in.sa) - a.cap[d];
+                holds = over <= 0;
+                if (j == j0) co_store(&a.ctl->over[d], over);
+            }
+            const uint64_t bits = __builtin_amdgcn_ballot_w64(holds);
+            if (lane == 0) co_store(&a.ctl->feasible[d][j / kWave], bits);
+        }
+        stores_done();
+        __syncthreads();
+        if (tid == 0) {
+            co_store(&a.ctl->ready[own], round);
+            uint32_t seen = 0;
+            for (uint32_t n = 0; n < kMostPolls && seen < round; ++n) {
+                seen = co_load(&a.ctl->round);
+                if (seen < round) __builtin_amdgcn_s_sleep(2);
+            }
+            asm volatile("" ::: "memory");
+            pub.more = seen < round ? 0u : co_load(&a.ctl->more);
+            pub.next = co_load(&a.ctl->next);
+            if (seen < round) raise_error(a.dev_err, MAPS_ERR_WAIT_TIMEOUT);
+        }
+        __syncthreads();
+        const uint32_t more = pub.more;
+        const int64_t next = pub.next;
+        for (int32_t d = own; d < D; d += P) {
+            const int32_t at = __builtin_amdgcn_readfirstlane(co_load(&a.ctl->assign[d]));
+            if (at < 0 || at >= kWindow || pos + at >= a.A) continue;
+            const int64_t i = pos + at;
+            const int32_t p0 = a.ap[i], U = a.aU[i], C = a.cap[d];
+            if (tid == 0) {
+                if (p0 < 0) raise_error(a.dev_err, MAPS_ERR_NEG_LEN);
+                if (U > T) raise_error(a.dev_err, MAPS_ERR_BOUND_RANGE);
+            }
+            const int64_t p = p0 < 0 ? 0 : p0;
+            const int32_t Uc = __builtin_amdgcn_readfirstlane(U < 0 ? 0 : U < T ? U : T);
+            const PeakIn in = peak_load(a, d, Uc);
+            const int64_t peak = max64(p + max64(in.pf, in.fl), in.sa);
+            if (tid == 0) {
+                const int64_t over = peak - C;
+                a.choice[i] = d;
+                a.chosen_peak[i] = peak;
+                a.chosen_over[i] = over > 0 ? over : 0;
+                a.flags[i] = over <= 0 ? 1 : 0;
+            }
+            __syncthreads();   // every thread has read the curves that the commit rewrites
+            PeakIn unused{0, 0, 0};
+            commit_any(a, ostage, peak, d, p, Uc, -1, -1, &unused, w);   // ends with a barrier
+        }
+        if (more == 0u) return;
+        pos = next;
+    }
+}
+
+// The master's rounds by one wavefront.
+template <int kSlots>
+__device__ inline void master_rounds(const CommitArgs& a) {
+    const int lane = threadIdx.x;
+    const int32_t D = a.S.D, P = a.owners;
+    // packed keys (Q << 10) | decoder: every queue stays in [0, 2^21)
+    bool wide = false;
+    uint32_t K[kSlots];
+#pragma unroll
+    for (int s = 0; s < kSlots; ++s) {
+        const int32_t d = lane + s * kWave;
+        const int32_t q = d < D ? a.qlen[d] : 0;
+        wide |= q < 0 || q + a.A >= (1 << 21);
+        K[s] = d < D ? (uint32_t(q) << 10) | uint32_t(d) : ~0u;
+    }
+    bool run = __builtin_amdgcn_ballot_w64(wide) == 0;
+    if (run) {
+        const uint64_t t0 = wall_clock64();
+        while (co_load(&a.ctl->checked) != uint32_t(P) && wall_clock64() - t0 < kCheckIn) __builtin_amdgcn_s_sleep(4);
+        run = __builtin_amdgcn_readfirstlane(co_load(&a.ctl->checked)) == P;
+    }
+    if (lane == 0) co_store(&a.ctl->decision, run ? 1u : 2u);
+    if (!run) return;   // ctl->next stays 0
+
+    int64_t pos = 0;
+    int held = 0;   // arrivals placed since the last review
+    for (uint32_t round = 1;; ++round) {
+        // every owner has evaluated the window
+        bool late = false;
+        for (int32_t o = lane; o - lane < P; o += kWave) {
+            uint32_t n = 0;
+            while (__builtin_amdgcn_ballot_w64(o < P && co_load(&a.ctl->ready[o < P ? o : 0]) < round) != 0)
+                if (++n > kMostPolls) { late = true; break; }
+        }
+        asm volatile("" ::: "memory");
+        uint32_t bits[kSlots][2 * kMaskWords];
+        uint64_t taken[kSlots];
+        int32_t mine[kSlots];   // the arrival assigned to this lane's decoder
+#pragma unroll
+        for (int s = 0; s < kSlots; ++s) {
+            const int32_t d = lane + s * kWave;
+#pragma unroll
+            for (int h = 0; h < kMaskWords; ++h) {
+                const uint64_t m = d < D ? co_load(&a.ctl->feasible[d][h]) : 0;
+                bits[s][2 * h] = uint32_t(m);
+                bits[s][2 * h + 1] = uint32_t(m >> 32);
+            }
+            taken[s] = 0;
+            mine[s] = -1;
+        }
+        const int32_t U0 = pos + lane < a.A ? a.aU[pos + lane] : 0;
+        const int32_t U1 = pos + kWave + lane < a.A ? a.aU[pos + kWave + lane] : 0;
+        const uint64_t none[2] = {__builtin_amdgcn_ballot_w64(U0 < 0), __builtin_amdgcn_ballot_w64(U1 < 0)};
+        const int cnt = a.A - pos < kWindow ? int(a.A - pos) : kWindow;
+        int done = 0;
+        bool first = true, stop = late;
+        auto take = [&](int32_t d, int j) {   // decoder d (uniform) takes the window's arrival j
+#pragma unroll
+            for (int s = 0; s < kSlots; ++s) {
+                const bool own = lane + s * kWave == d;
+                K[s] += own ? 1024u : 0u;
+                mine[s] = own ? j : mine[s];
+                taken[s] |= d / kWave == s ? 1ull << (d % kWave) : 0ull;
+            }
+        };
+#pragma unroll
+        for (int word = 0; word < 2 * kMaskWords; ++word) {
+            for (int jj = 0; jj < 32 && !stop; ++jj) {
+                const int j = word * 32 + jj;
+                if (j >= cnt) break;
+                if ((none[word / 2] >> (j % kWave)) & 1) {   // round robin: the request only joins the queue
+                    const int32_t d = int32_t((a.rr_offset + pos + j) % D);
+#pragma unroll
+                    for (int s = 0; s < kSlots; ++s) K[s] += lane + s * kWave == d ? 1024u : 0u;
+                    if (lane == 0) {
+                        a.choice[pos + j] = d;
+                        a.chosen_peak[pos + j] = -1;
+                        a.chosen_over[pos + j] = 0;
+                        a.flags[pos + j] = 2;
+                    }
+                    done = j + 1;
+                    continue;
+                }
+                uint32_t k = ~0u;
+#pragma unroll
+                for (int s = 0; s < kSlots; ++s) {
+                    const uint32_t k1 = (bits[s][word] >> jj) & 1u ? K[s] : ~0u;
+                    k = k1 < k ? k1 : k;
+                }
+                k = wave_last(wave_incl_scan(k, ~0u, [](uint32_t x, uint32_t y) { return x < y ? x : y; }));
+                int32_t d;
+                if (k != ~0u) {
+                    d = int32_t(k & 1023u);
+                    uint64_t t = 0;
+#pragma unroll
+                    for (int s = 0; s < kSlots; ++s) t = d / kWave == s ? taken[s] : t;
+                    if ((t >> (d % kWave)) & 1) { stop = true; break; }   // its new curve decides
+                } else {
+                    if (!first) { stop = true; break; }   // the overflows are those of the first
+                    int64_t least = INT64_MAX, over[kSlots];
+#pragma unroll
+                    for (int s = 0; s < kSlots; ++s) {
+                        over[s] = lane + s * kWave < D ? co_load(&a.ctl->over[lane + s * kWave]) : INT64_MAX;
+                        least = over[s] < least ? over[s] : least;
+                    }
+                    least = wave_last(wave_incl_scan(least, INT64_MAX, [](int64_t x, int64_t y) { return x < y ? x : y; }));
+                    d = 0;
+#pragma unroll
+                    for (int s = kSlots - 1; s >= 0; --s) {
+                        const uint64_t at = __builtin_amdgcn_ballot_w64(over[s] == least);
+                        d = at != 0 ? s * kWave + __ffsll((unsigned long long)at) - 1 : d;
+                    }
+                }
+                first = false;
+                take(d, j);
+                done = j + 1;
+            }
+        }
+        pos += done;
+        held += done;
+        uint32_t more = pos < a.A && !late ? 1u : 0u;
+        if (more != 0u && round % kReviewRounds == 0) {
+            if (held < kReviewRounds + kReviewRounds / 2) more = 0u;
+            held = 0;
+        }
+        if (late) {   // unreachable while every owner runs
+            if (lane == 0) raise_error(a.dev_err, MAPS_ERR_WAIT_TIMEOUT);
+            pos = a.A;
+        }
+#pragma unroll
+        for (int s = 0; s < kSlots; ++s)
+            if (lane + s * kWave < D) co_store(&a.ctl->assign[lane + s * kWave], mine[s]);
+        if (lane == 0) {
+            co_store(&a.ctl->more, more);
+            co_store(&a.ctl->next, pos);
+        }
+        stores_done();
+        if (lane == 0) co_store(&a.ctl->round, round);
+        if (more == 0u) break;
+    }
+#pragma unroll
+    for (int s = 0; s < kSlots; ++s)
+        if (lane + s * kWave < D) a.ctl->queue[lane + s * kWave] = int32_t(K[s] >> 10);
+}
+
+template <int kSlots>
+__global__ __launch_bounds__(kSerialNT) void commit_rounds(CommitArgs a) {
+    extern __shared__ __align__(16) int32_t lds[];   // an owner's stage, placed as in commit_serial
+    __shared__ ChainLds w;
+    __shared__ Published pub;
+    if (blockIdx.x != 0) owner_rounds(a, reinterpret_cast<int64_t*>(lds + 2 * a.S.D), w, pub);
+    else if (threadIdx.x < kWave) master_rounds<kSlots>(a);
 }
 
 }  // namespace
@@ -571,17 +929,33 @@ extern "C" maps_status maps_place_commit(const void* snapshot, int32_t D, int32_
     a.flags = flags;
     a.queue_out = queue_out;
     a.dev_err = dev_err;
+    a.ctl = reinterpret_cast<RoundControl*>(w + c.off_ctl);
+    // Rounds where arrivals can find different feasible decoders, from 8
+    // arrivals on (starting the owners costs about one serial arrival); the
+    // master and the owners fill a compute unit each.
+    const int cus = device_compute_units();
+    const bool rounds = policy == MAPS_POLICY_MQ && D >= 3 && D <= kRoundDecoders && A >= 8 && cus >= 4;
+    a.owners = rounds ? (D < cus - 1 ? D : cus - 1) : 0;
+    if (a.owners > kMaxOwners) a.owners = kMaxOwners;
+    auto serial = D <= kSerialNT ? commit_serial<true> : commit_serial<false>;
+    auto round = D <= 4 * kWave ? commit_rounds<4> : commit_rounds<kRoundDecoders / kWave>;
     // dynamic LDS of the chain: queue lengths and capacities, then as many
     // staged range entries as the workgroup's LDS holds beside the kernel's
     // static LDS (less 256 bytes for the alignment of the dynamic part)
-    auto serial = D <= kSerialNT ? commit_serial<true> : commit_serial<false>;
     const size_t qc = size_t(2) * D * sizeof(int32_t);   // a multiple of 8 bytes
-    const size_t fixed = kernel_static_lds(serial) + qc + 256;
+    size_t fixed = kernel_static_lds(serial);
+    if (rounds && kernel_static_lds(round) > fixed) fixed = kernel_static_lds(round);
+    fixed += qc + 256;
     if (fixed > kLdsPerWorkgroup) return MAPS_E_SIZE;   // unreachable with D <= MAPS_MAX_COMMIT_DECODERS
     a.stage_cap = int32_t((kLdsPerWorkgroup - fixed) / sizeof(int64_t));
     const size_t lds = qc + size_t(a.stage_cap) * sizeof(int64_t);
     hipLaunchKernelGGL(commit_init, dim3(unsigned(D)), dim3(kCommitNT), 0, stream, a);
     MAPS_CHECK_LAUNCH();
+    if (rounds) {
+        allow_dynamic_lds(round, lds);
+        hipLaunchKernelGGL(round, dim3(unsigned(1 + a.owners)), dim3(kSerialNT), lds, stream, a);
+        MAPS_CHECK_LAUNCH();
+    }
     allow_dynamic_lds(serial, lds);
     hipLaunchKernelGGL(serial, dim3(1), dim3(kSerialNT), lds, stream, a);
     MAPS_CHECK_LAUNCH();

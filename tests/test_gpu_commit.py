@@ -79,6 +79,30 @@ def test_random(orc, D, nmax, A, u_max):
         say(f"[commit] D={D} A={A} policy={policy}: feasible {np.mean(r.flags & 1):.3f}")
 
 
+# (D, A, u_max): batches at the edges of the rounds' window of 128 arrivals, decoders at the edges of a
+# wavefront's slots, one and several decoders an owner workgroup, and the most decoders the rounds take
+@pytest.mark.parametrize("D,A,u_max", [(3, 8, 300), (3, 129, 300), (64, 127, 500), (65, 128, 500), (255, 640, 400),
+                                       (256, 257, 400), (257, 900, 200), (600, 1500, 150), (1024, 2100, 100)])
+@pytest.mark.parametrize("room", ["most", "half", "none", "long queues"])
+def test_rounds(orc, D, A, u_max, room):
+    """Rounds of parallel commits: decoders that hold nearly every arrival, about
+    half of them and none (where the rounds give way to the serial chain), in
+    batches with arrivals without a bound, past u_max's profile and with equal
+    and unequal queues; and queues too long for the rounds."""
+    rng = np.random.default_rng(D + A)
+    seg, p, g, U, a_p, a_U = _random_case(rng, D, 12, A, u_max)
+    base = orc.project(seg, p, g, U)
+    demand = int((a_p + np.maximum(a_U, 0)).mean()) * max(1, A // D)
+    share = {"most": 4 * demand, "half": demand, "none": 0, "long queues": demand}[room]
+    cap = (base + rng.integers(0, share + 1, size=D)).astype(np.int32)
+    Q = rng.integers(0, 7, size=D) + (2**21 - 5 if room == "long queues" else 0)
+    rr = int(rng.integers(0, 2**40))
+    r, q_after = orc.place_commit(seg, p, g, U, cap, Q, a_p, a_U, policy=0, rr_offset=rr)
+    say(f"[commit] rounds D={D} A={A} {room}: feasible {np.mean(r.flags & 1):.3f}")
+    got = _gpu(seg, p, g, U, u_max, cap, Q, a_p, a_U, 0, rr)
+    _compare(got, r, q_after, f"rounds D={D} A={A} {room}")
+
+
 def test_ties_and_empty_decoders(orc):
     # identical decoders (every key ties: lowest index first, then queue growth spreads them), empty decoders
     D = 6
