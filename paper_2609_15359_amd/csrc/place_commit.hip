@@ -26,8 +26,7 @@
 //   commit_serial  one 512-thread workgroup for the whole chain: per arrival
 //                  every decoder's peak (PF, SA and the block floor at U), the
 //                  choice by a workgroup argmin, then the commit on [0, U] of
-//                  the chosen decoder with its tail and block floors; a range
-//                  that fits keeps its new O values in LDS for the two scans.
+//                  the chosen decoder with its tail and block floors.
 //                  Queue lengths and capacities live in LDS; with at most 512
 //                  decoders the next arrival's lookups are issued with the
 //                  commit's loads.
@@ -215,32 +214,13 @@ __global__ __launch_bounds__(kCommitNT) void commit_init(CommitArgs a) {
 // The serial chain
 // ---------------------------------------------------------------------------
 
-constexpr int kBatch = 24;                  // range entries a thread loads at once
+constexpr int kRowBatch = 8;   // rows of 64 steps a wavefront loads at once
 
 // Barrier that orders LDS traffic only: each wave waits for its own LDS
 // operations, not for its global stores in flight (a full __syncthreads waits
 // for those too, about a microsecond after the commit's stores).  The memory
 // clobber keeps the compiler from moving memory accesses across it.
 __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
-// Exclusive max-scan of one value per thread over the chain's workgroup, with
-// LDS-only barriers; the total goes to *total.
-__device__ inline int64_t chain_excl_max(int64_t v, int64_t* tmp, int64_t* total) {
-    const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
-    const int64_t incl = wave_incl_scan_max(v);
-    lds_barrier();   // every wave has read tmp's earlier contents
-    if (lane == kWave - 1) tmp[wid] = incl;
-    lds_barrier();
-    int64_t before = 0, all = 0;
-#pragma unroll
-    for (int i = 0; i < kSerialWaves; ++i) {
-        const int64_t x = tmp[i];
-        if (i < wid) before = max64(before, x);
-        all = max64(all, x);
-    }
-    *total = all;
-    return max64(before, wave_shift_up1(incl, int64_t(0)));
-}
 
 // One decoder's peak inputs at step u: the stored prefix maximum, the floor
 // of u's block, and the suffix maximum.
@@ -292,27 +272,33 @@ struct Capture {
 __device__ inline void pin(int64_t& x) { asm volatile("" : "+v"(x)); }
 
 // Commit (p, Uc) to decoder bd: O += p + t on [0, Uc], PF and SA derived
-// again there, and the new PF(Uc) recorded as a floor above Uc.  kStaged (a
-// range of at most a.stage_cap entries): the new O values stay in LDS
-// (`stage`) for the two scans; otherwise they are read back from HBM.  `un` is the next
-// arrival's step (-1: none): the threads that rewrite PF(un) and SA(un) below
-// Uc leave them in `cap`, and a thread with pre_d >= 0 loads decoder pre_d's
-// peak inputs at un into *pre_out, issued with the range's loads.  Returns
-// the new PF(Uc), the same in every thread.  Ends with a barrier after which
-// every store of the commit is visible to the workgroup.
-template <bool kStaged, typename SType = int64_t>
-__device__ inline int64_t commit_range(const CommitArgs& a, SType* stage, int32_t bd, int64_t p, int32_t Uc,
-                                       int32_t un, int32_t pre_d, PeakIn* pre_out, Capture* cap,
-                                       int64_t* scan_tmp) {
+// again there, and the new PF(Uc) recorded as a floor above Uc.  Each
+// wavefront takes one segment of whole rows of 64 steps, a step per lane, so
+// that every access covers whole cache lines; the segments' maxima are
+// exchanged once, then each row's PF and SA are a wavefront scan and a carry.
+// (With a chunk of consecutive steps per thread each access touched 64 lines,
+// and a range of 10,000 steps took 22 us, one past 18,000 about 60.)
+// V = int32_t: every value fits (see commit_any) and the new O values stay in
+// LDS (`stage`, Uc + 1 entries) between the passes; int64_t: they are read back
+// from HBM.  `un` is the next arrival's step (-1: none): the lanes that rewrite
+// PF(un) and SA(un) below Uc leave them in `cap`, and a thread with pre_d >= 0
+// loads decoder pre_d's peak inputs at un into *pre_out, issued with the
+// range's loads.  Returns the new PF(Uc), the same in every thread.  Ends with
+// a barrier after which every store of the commit is visible to the workgroup.
+template <typename V>
+__device__ inline int64_t commit_range(const CommitArgs& a, V* stage, int32_t bd, int64_t p, int32_t Uc, int32_t un,
+                                       int32_t pre_d, PeakIn* pre_out, Capture* cap, int64_t* scan_tmp,
+                                       int64_t* scan_tmp2) {
+    constexpr bool kStaged = sizeof(V) == 4;
     const int32_t L = a.L;
-    const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
-    int64_t* __restrict__ O = a.O + int64_t(bd) * L;
-    int64_t* __restrict__ PF = a.PF + int64_t(bd) * L;
-    int64_t* __restrict__ SA = a.SA + int64_t(bd) * L;
-    int64_t* __restrict__ Fd = a.F + int64_t(bd) * a.NB;
+    const int lane = threadIdx.x % kWave, wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    int64_t* O = a.O + int64_t(bd) * L;
+    int64_t* PF = a.PF + int64_t(bd) * L;
+    int64_t* SA = a.SA + int64_t(bd) * L;
+    int64_t* Fd = a.F + int64_t(bd) * a.NB;
     const int32_t n = Uc + 1;
-    const int32_t chunk = (n + kSerialNT - 1) / kSerialNT;
-    const int32_t b = threadIdx.x * chunk, e = b + chunk < n ? b + chunk : n;
+    const int32_t rows = (n + kWave - 1) / kWave, per = (rows + kSerialWaves - 1) / kSerialWaves;
+    const int32_t r0 = wid * per < rows ? wid * per : rows, r1 = r0 + per < rows ? r0 + per : rows;
     // above Uc: the rest of its block (up to kTailPer steps per thread) and
     // the block floors after it (up to kFloorPer per thread), read with the
     // range and raised to v last
@@ -334,13 +320,15 @@ __device__ inline int64_t commit_range(const CommitArgs& a, SType* stage, int32_
     const bool pre = un >= 0 && pre_d >= 0;
     PeakIn pl{0, 0, 0};
     if (pre) pl = peak_load(a, pre_d, un);
-    int64_t mpre = 0, msuf = 0;
-    int64_t o[kBatch];
-    auto load_batch = [&](int32_t t0) {
+    int64_t o[kRowBatch];
+    auto load_rows = [&](int32_t rb) {
 #pragma unroll
-        for (int j = 0; j < kBatch; ++j) o[j] = t0 + j < e ? O[t0 + j] : 0;
+        for (int j = 0; j < kRowBatch; ++j) {
+            const int32_t t = (rb + j) * kWave + lane;
+            o[j] = rb + j < r1 && t < n ? O[t] : 0;
+        }
     };
-    load_batch(b);
+    load_rows(r0);
     // the loads issued before the range's are waited for now, ahead of its stores
     pin(sa_top);
     pin(pl.pf);
@@ -350,74 +338,82 @@ __device__ inline int64_t commit_range(const CommitArgs& a, SType* stage, int32_
     for (int k = 0; k < kTailPer; ++k) pin(tail_old[k]);
 #pragma unroll
     for (int k = 0; k < kFloorPer; ++k) pin(fb_old[k]);
-    for (int32_t t0 = b; t0 < e; t0 += kBatch) {
-        if (t0 != b) load_batch(t0);
+    V mpre = 0, msuf = 0;
+    for (int32_t rb = r0; rb < r1; rb += kRowBatch) {
+        if (rb != r0) load_rows(rb);
 #pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-            const int32_t t = t0 + j;
-            if (t < e) {
-                o[j] += p + t;
-                O[t] = o[j];
-                if constexpr (kStaged) stage[t] = SType(o[j]);
-                mpre = max64(mpre, o[j] + t);
-                msuf = max64(msuf, o[j]);
+        for (int j = 0; j < kRowBatch; ++j) {
+            const int32_t t = (rb + j) * kWave + lane;
+            if (rb + j < r1 && t < n) {
+                const int64_t x = o[j] + p + t;
+                O[t] = x;
+                if constexpr (kStaged) stage[t] = V(x);
+                mpre = V(x) + t > mpre ? V(x) + t : mpre;
+                msuf = V(x) > msuf ? V(x) : msuf;
             }
         }
     }
-    int64_t v;
-    int64_t run = chain_excl_max(mpre, scan_tmp, &v);
-    if (pre) *pre_out = pl;
-    // suffix maxima over the chunks after this thread's (a scan in reversed thread order)
-    int64_t incl = msuf;
-    for (int k = 1; k < kWave; k <<= 1) {
-        const int64_t x = __shfl_down(incl, k, kWave);
-        if (lane + k < kWave) incl = max64(incl, x);
+    mpre = wave_reduce_max(mpre);
+    msuf = wave_reduce_max(msuf);
+    lds_barrier();   // every wave has read the scan arrays' earlier contents
+    if (lane == 0) {
+        scan_tmp[wid] = mpre;
+        scan_tmp2[wid] = msuf;
     }
-    lds_barrier();   // every wave has read scan_tmp
-    if (lane == 0) scan_tmp[wid] = incl;
     lds_barrier();
-    int64_t after = sa_top;
+    V run = 0, all = 0, after = V(sa_top);   // over the segments below and above this one
 #pragma unroll
-    for (int w = 0; w < kSerialWaves; ++w)   // independent reads, one LDS round trip
-        if (w > wid) after = max64(after, scan_tmp[w]);
-    const int64_t below = __shfl_down(incl, 1, kWave);
-    if (lane + 1 < kWave) after = max64(after, below);
-    // the new O of the thread's entries [t0, t0 + kBatch), from LDS or HBM
-    auto fetch = [&](int32_t t0, int64_t (&o)[kBatch]) {
-        if constexpr (kStaged) {
+    for (int i = 0; i < kSerialWaves; ++i) {
+        const V x = V(scan_tmp[i]), y = V(scan_tmp2[i]);
+        if (i < wid) run = x > run ? x : run;
+        if (i > wid) after = y > after ? y : after;
+        all = x > all ? x : all;
+    }
+    const int64_t v = all;
+    if (pre) *pre_out = pl;
+    // the wavefront's own new O values, a step per lane (kDown: from the row's top down)
+    V x[kRowBatch];
+    auto fetch_rows = [&](int32_t rb, bool down) {
 #pragma unroll
-            for (int j = 0; j < kBatch; ++j) o[j] = t0 + j < e ? int64_t(stage[t0 + j]) : 0;
-        } else {
-#pragma unroll
-            for (int j = 0; j < kBatch; ++j) o[j] = t0 + j < e ? O[t0 + j] : 0;
+        for (int j = 0; j < kRowBatch; ++j) {
+            const int32_t t = (rb + j) * kWave + (down ? kWave - 1 - lane : lane);
+            const bool in = rb + j >= r0 && rb + j < r1 && t < n;
+            if constexpr (kStaged) x[j] = in ? stage[t] : V(0);
+            else x[j] = in ? V(O[t]) : V(0);
         }
     };
-    for (int32_t t0 = b; t0 < e; t0 += kBatch) {
-        fetch(t0, o);
+    if constexpr (!kStaged) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's O stores
+    for (int32_t rb = r0; rb < r1; rb += kRowBatch) {
+        fetch_rows(rb, false);
 #pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-            const int32_t t = t0 + j;
-            if (t < e) {
-                run = max64(run, o[j] + t);
-                PF[t] = run;
-                if (t == un) cap->pf = run;
+        for (int j = 0; j < kRowBatch; ++j) {
+            const int32_t t = (rb + j) * kWave + lane;
+            const bool in = rb + j < r1 && t < n;
+            const V incl = wave_incl_scan_max(in ? V(x[j] + t) : V(0));
+            const V pf = incl > run ? incl : run;
+            if (in) {
+                PF[t] = pf;
+                if (t == un) cap->pf = pf;
             }
+            run = wave_last(pf);
         }
     }
-    // SA from the top down, in batches [t1 - kBatch, t1)
-    const int32_t last = b + ((e - b + kBatch - 1) / kBatch) * kBatch;   // past the thread's last batch
-    for (int32_t t1 = last; t1 > b; t1 -= kBatch) {
-        fetch(t1 - kBatch, o);
+    // SA from the top down; lane i takes a row's step 63 - i
+    const int32_t batches = (r1 - r0 + kRowBatch - 1) / kRowBatch;
+    for (int32_t rb = r0 + (batches - 1) * kRowBatch; rb >= r0; rb -= kRowBatch) {
+        fetch_rows(rb, true);
 #pragma unroll
-        for (int j = kBatch - 1; j >= 0; --j) {
-            const int32_t t = t1 - kBatch + j;
-            if (t < e) {
-                if (t < Uc) {
-                    SA[t] = after;
-                    if (t == un) cap->sa = after;
-                }
-                after = max64(after, o[j]);
+        for (int j = kRowBatch - 1; j >= 0; --j) {
+            if (rb + j >= r1) continue;   // uniform
+            const int32_t t = (rb + j) * kWave + (kWave - 1 - lane);
+            const V scan = wave_incl_scan_max(x[j]);
+            const V incl = scan > after ? scan : after;
+            const V sa = wave_shift_up1(incl, after);
+            if (t < Uc) {
+                SA[t] = sa;
+                if (t == un) cap->sa = sa;
             }
+            after = wave_last(incl);
         }
     }
     // the new PF(Uc) = v is a floor for every step above Uc
@@ -438,23 +434,20 @@ __device__ inline int64_t commit_range(const CommitArgs& a, SType* stage, int32_
 // LDS of the chain's workgroup beside the dynamic part.
 struct ChainLds {
     int32_t tile_p[2][kSerialNT], tile_U[2][kSerialNT];   // arrivals of the current and next tile
-    int64_t skey[kSerialWaves], scan_tmp[kSerialWaves];
+    int64_t skey[kSerialWaves], scan_tmp[kSerialWaves], scan_tmp2[kSerialWaves];
     int32_t sd[kSerialWaves];
     int64_t speak;
     Capture cap;
 };
 
-// The new O values of a commit fit 32 bits when its peak plus U does: they are
-// at most peak + Uc (O(t) <= O(t) + t <= PF(Uc) <= peak - p, plus p + t), and
-// the stage holds twice as many of them.
-__device__ inline int64_t commit_any(const CommitArgs& a, int64_t* ostage, int64_t peak, int32_t bd, int64_t p,
+// The new O values of a commit, and PF and SA on its range, fit 32 bits when
+// its peak plus U does: O(t) + t <= PF(Uc) <= peak - p before it, plus p + t
+// after it, and SA there is at most the larger of those and SA(Uc) <= peak.
+__device__ inline int64_t commit_any(const CommitArgs& a, int32_t* stage, int64_t peak, int32_t bd, int64_t p,
                                      int32_t Uc, int32_t un, int32_t pre_d, PeakIn* cur, ChainLds& w) {
-    const bool narrow = peak + Uc < int64_t(INT32_MAX);
-    return Uc < a.stage_cap ? commit_range<true>(a, ostage, bd, p, Uc, un, pre_d, cur, &w.cap, w.scan_tmp)
-           : narrow && Uc < 2 * int64_t(a.stage_cap)
-               ? commit_range<true, int32_t>(a, reinterpret_cast<int32_t*>(ostage), bd, p, Uc, un, pre_d, cur, &w.cap,
-                                             w.scan_tmp)
-               : commit_range<false>(a, ostage, bd, p, Uc, un, pre_d, cur, &w.cap, w.scan_tmp);
+    if (peak + Uc < int64_t(INT32_MAX) && Uc < a.stage_cap)
+        return commit_range<int32_t>(a, stage, bd, p, Uc, un, pre_d, cur, &w.cap, w.scan_tmp, w.scan_tmp2);
+    return commit_range<int64_t>(a, nullptr, bd, p, Uc, un, pre_d, cur, &w.cap, w.scan_tmp, w.scan_tmp2);
 }
 
 // One workgroup for the chain from arrival `first` on (the queue lengths in Q
@@ -464,7 +457,7 @@ __device__ inline int64_t commit_any(const CommitArgs& a, int64_t* ostage, int64
 // thread patches them from the values the commit captured.  Otherwise every
 // thread evaluates its decoders d, d + kSerialNT, ... after each commit.
 template <bool kPre>
-__device__ inline void serial_chain(const CommitArgs& a, int64_t first, int32_t* Q, int32_t* C, int64_t* ostage,
+__device__ inline void serial_chain(const CommitArgs& a, int64_t first, int32_t* Q, int32_t* C, int32_t* ostage,
                                     ChainLds& w) {
     auto& tile_p = w.tile_p;
     auto& tile_U = w.tile_U;
@@ -584,7 +577,7 @@ __global__ __launch_bounds__(kSerialNT) void commit_serial(CommitArgs a) {
         if (a.owners > 0 && a.ctl->next > 0) Q[d] = a.ctl->queue[d];
     }
     if (neg) raise_error(a.dev_err, MAPS_ERR_NEG_LEN);
-    serial_chain<kPre>(a, a.owners > 0 ? a.ctl->next : 0, Q, C, reinterpret_cast<int64_t*>(lds + 2 * D), w);
+    serial_chain<kPre>(a, a.owners > 0 ? a.ctl->next : 0, Q, C, lds + 2 * D, w);
 }
 
 // ---------------------------------------------------------------------------
@@ -616,8 +609,10 @@ __global__ __launch_bounds__(kSerialNT) void commit_serial(CommitArgs a) {
 // on a workgroup that is not running.  The rounds also end when they hold too
 // few arrivals to pay (no decoder is feasible any more, and commits do not make
 // any feasible again).  The serial chain's launch takes up what is left.
-// Commit of 4,096 arrivals: COMMIT_FIGURES.
-constexpr int kReviewRounds = 32;            // rounds after which the master looks at what they held
+// 4,096 arrivals on 256 decoders (queues of 0..63, bounds of 3,600 steps on
+// average, 32,768 at most), nearly all feasible: 49 ms in the serial chain
+// before, 4.1 ms with the rounds and the commits by rows.
+constexpr int kReviewRounds = 8;             // rounds after which the master looks at what they held
 constexpr uint64_t kCheckIn = 20000;         // 200 us at the 100 MHz of the constant clock
 constexpr uint32_t kMostPolls = 1u << 22;    // an owner or the master that is not heard of for seconds
 
@@ -639,7 +634,7 @@ struct Published {
     int64_t next;
 };
 
-__device__ inline void owner_rounds(const CommitArgs& a, int64_t* ostage, ChainLds& w, Published& pub) {
+__device__ inline void owner_rounds(const CommitArgs& a, int32_t* ostage, ChainLds& w, Published& pub) {
     const int tid = threadIdx.x, lane = tid % kWave;
     const int32_t D = a.S.D, T = a.L - 1, P = a.owners;
     const int32_t own = int32_t(blockIdx.x) - 1;   // decoders own, own + P, ...
@@ -753,6 +748,7 @@ __device__ inline void master_rounds(const CommitArgs& a) {
 
     int64_t pos = 0;
     int held = 0;   // arrivals placed since the last review
+    bool few = false;
     for (uint32_t round = 1;; ++round) {
         // every owner has evaluated the window
         bool late = false;
@@ -783,6 +779,20 @@ __device__ inline void master_rounds(const CommitArgs& a) {
         const int cnt = a.A - pos < kWindow ? int(a.A - pos) : kWindow;
         int done = 0;
         bool first = true, stop = late;
+        if (round == 1) {
+            // fewer than half of the window's arrivals find a decoder: the chain is better off from the start
+            int held_by_any = 0;
+#pragma unroll
+            for (int word = 0; word < 2 * kMaskWords; ++word) {
+                uint32_t m = 0;
+#pragma unroll
+                for (int s = 0; s < kSlots; ++s) m |= bits[s][word];
+                held_by_any += __popc(wave_last(wave_incl_scan(m, 0u, [](uint32_t x, uint32_t y) { return x | y; })));
+            }
+            const int bounded = cnt - __popcll(none[0]) - __popcll(none[1]);
+            few = 2 * held_by_any < bounded;
+            stop |= few;
+        }
         auto take = [&](int32_t d, int j) {   // decoder d (uniform) takes the window's arrival j
 #pragma unroll
             for (int s = 0; s < kSlots; ++s) {
@@ -847,7 +857,7 @@ __device__ inline void master_rounds(const CommitArgs& a) {
         }
         pos += done;
         held += done;
-        uint32_t more = pos < a.A && !late ? 1u : 0u;
+        uint32_t more = pos < a.A && !late && !few ? 1u : 0u;
         if (more != 0u && round % kReviewRounds == 0) {
             if (held < kReviewRounds + kReviewRounds / 2) more = 0u;
             held = 0;
@@ -877,7 +887,7 @@ __global__ __launch_bounds__(kSerialNT) void commit_rounds(CommitArgs a) {
     extern __shared__ __align__(16) int32_t lds[];   // an owner's stage, placed as in commit_serial
     __shared__ ChainLds w;
     __shared__ Published pub;
-    if (blockIdx.x != 0) owner_rounds(a, reinterpret_cast<int64_t*>(lds + 2 * a.S.D), w, pub);
+    if (blockIdx.x != 0) owner_rounds(a, lds + 2 * a.S.D, w, pub);
     else if (threadIdx.x < kWave) master_rounds<kSlots>(a);
 }
 
@@ -947,8 +957,8 @@ extern "C" maps_status maps_place_commit(const void* snapshot, int32_t D, int32_
     if (rounds && kernel_static_lds(round) > fixed) fixed = kernel_static_lds(round);
     fixed += qc + 256;
     if (fixed > kLdsPerWorkgroup) return MAPS_E_SIZE;   // unreachable with D <= MAPS_MAX_COMMIT_DECODERS
-    a.stage_cap = int32_t((kLdsPerWorkgroup - fixed) / sizeof(int64_t));
-    const size_t lds = qc + size_t(a.stage_cap) * sizeof(int64_t);
+    a.stage_cap = int32_t((kLdsPerWorkgroup - fixed) / sizeof(int32_t));
+    const size_t lds = qc + size_t(a.stage_cap) * sizeof(int32_t);
     hipLaunchKernelGGL(commit_init, dim3(unsigned(D)), dim3(kCommitNT), 0, stream, a);
     MAPS_CHECK_LAUNCH();
     if (rounds) {
