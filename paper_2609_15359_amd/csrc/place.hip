@@ -17,7 +17,8 @@
 // decoders in order, stages their snapshot data in LDS, and evaluates all its
 // arrivals against each, writing the decoder-major pair-peak row segment with
 // coalesced stores and keeping the running best choice per arrival (ties keep
-// the earlier, lower decoder).  Each group writes its best (key, decoder) per
+// the earlier, lower decoder).  Where the pair matrix is not wanted, the tile
+// walks only the decoders that one of its arrivals can choose.  Each group writes its best (key, decoder) per
 // arrival; place_finish picks the best group in group order, evaluates the
 // chosen pair's peak once more from the snapshot and writes the outputs.
 //
@@ -34,6 +35,11 @@ constexpr int kNT = 512;          // 8 waves per CU: 256 VGPRs per lane for the 
 constexpr size_t kLdsBytes = 160 * 1024;
 constexpr size_t kRedBytes = 256;   // record path: the tile's bound reduction, past the two buffers
 constexpr int kMaxGroups = 8;
+// Decisions without the pair matrix, groups of this many decoders: the tile
+// first lists the decoders that can be chosen (see list_candidates).  Below
+// the least a walk is shorter than the listing; the most fits the LDS past the
+// buffers as 16-bit indices.
+constexpr int32_t kListMin = 16, kListMax = 4096;
 
 struct PlaceArgs {
     SnapLayout L;
@@ -56,6 +62,7 @@ struct PlaceArgs {
     int32_t Dg;        // decoders per group
     int32_t buf_units; // record path: 16-byte units per LDS buffer (0: slices stay in HBM)
     int32_t nb;        // profile path: profiles per LDS batch
+    bool list;         // record path without pairs: the tile's candidates are listed first
     uint32_t* dev_err;
     bool dec16;        // D <= 65,536: the groups' decoders are written as 16-bit indices
 };
@@ -112,13 +119,22 @@ __device__ __forceinline__ int64_t key_peak(int32_t key, int32_t C) {
 // no load latency per decoder, and no wait on a fresh load (which would also
 // wait for every store issued before it) inside the decoder loop.
 struct DecLanes {
-    int32_t off_lo, off_hi, E, base, C, Q, pmx_end;
+    int32_t off_lo, off_hi, E, base, C, Q, pmx_end, d;
 };
 
-__device__ __forceinline__ DecLanes load_lanes(const PlaceArgs& g, const SnapView& V, int32_t d0, int32_t d_end) {
-    const int32_t d = d0 + int32_t(threadIdx.x % kWave);
-    DecLanes l{0, 0, -1, -1, 0, 0, 0};
-    if (d < d_end) {
+// The decoders a tile walks: place i in [begin, end) is decoder i itself, or
+// with a list decoder begin + list[i - begin].
+struct Walk {
+    int32_t begin, end;
+    const uint16_t* list;
+    __device__ __forceinline__ int32_t decoder(int32_t i) const { return list ? begin + list[i - begin] : i; }
+};
+
+__device__ __forceinline__ DecLanes load_lanes(const PlaceArgs& g, const SnapView& V, const Walk& w, int32_t i0) {
+    const int32_t i = i0 + int32_t(threadIdx.x % kWave);
+    DecLanes l{0, 0, -1, -1, 0, 0, 0, 0};
+    if (i < w.end) {
+        const int32_t d = w.decoder(i);
         const DecHeader h = V.dec[d];
         l.off_lo = int32_t(uint64_t(h.slice_off));
         l.off_hi = int32_t(uint64_t(h.slice_off) >> 32);
@@ -127,6 +143,7 @@ __device__ __forceinline__ DecLanes load_lanes(const PlaceArgs& g, const SnapVie
         l.C = g.cap[d];
         l.Q = g.qlen[d];
         l.pmx_end = h.pmx_end;
+        l.d = d;
     }
     return l;
 }
@@ -149,7 +166,7 @@ __device__ __forceinline__ DecHeader lane_header(const DecLanes& l, int32_t lane
 }
 
 // Largest total demand sum_r (p + g + R) and record count E + 1 over the
-// decoders [d0, d1), and the intersection of their hot windows, the same in
+// walk's decoders, and the intersection of their hot windows, the same in
 // every lane.
 struct GroupMax {
     int64_t tot;
@@ -158,11 +175,11 @@ struct GroupMax {
     int32_t flat_lo;   // largest max(flat_lo, hot_lo)
 };
 
-__device__ inline GroupMax group_max(const SnapView& V, int32_t d0, int32_t d1) {
+__device__ inline GroupMax group_max(const SnapView& V, const Walk& w) {
     int64_t t = 0;
     int32_t r = 0, lo = 0, hi = INT32_MAX, fl = 0;
-    for (int32_t d = d0 + int32_t(threadIdx.x % kWave); d < d1; d += kWave) {
-        const DecHeader h = V.dec[d];
+    for (int32_t i = w.begin + int32_t(threadIdx.x % kWave); i < w.end; i += kWave) {
+        const DecHeader h = V.dec[w.decoder(i)];
         t = t > h.tot ? t : h.tot;
         r = r > h.E + 1 ? r : h.E + 1;
         lo = lo > h.hot_lo ? lo : h.hot_lo;
@@ -442,12 +459,11 @@ __device__ __forceinline__ int64_t cold_units(int64_t E) { return (E + 2) / 2; }
 // fits (a header claiming more is reported and skipped).
 template <int kAPT, bool kFull, bool kPairs, int kPolicy, bool kMixed>
 __device__ __forceinline__ void records_tile(const PlaceArgs& g, const SnapView& V, int4* lds, int32_t grp,
-                                             int64_t a0, const GroupMax& gm, const int32_t (&rp)[kAPT],
+                                             int64_t a0, const Walk& w, const GroupMax& gm, const int32_t (&rp)[kAPT],
                                              const int32_t (&rU)[kAPT], const DecLanes& first_lanes) {
     const SnapLayout& L = g.L;
     const int32_t half_w = L.W / 2;                // rank words in 16-byte units
-    const int32_t d_begin = grp * g.Dg;
-    const int32_t d_end = d_begin + g.Dg < L.D ? d_begin + g.Dg : L.D;
+    const int32_t d_begin = w.begin, d_end = w.end;   // places of the walk
     const int64_t n_total = load_uniform(&V.hdr->n_total);
     const int32_t ucl_max = 32 * L.W - 1;          // ranks above every event
     const int32_t buf_units = g.buf_units;
@@ -530,7 +546,7 @@ __device__ __forceinline__ void records_tile(const PlaceArgs& g, const SnapView&
         };
         // loaded here rather than with the tile's first loads: holding them
         // across the preamble costs this walk registers and time
-        DecLanes lanes = load_lanes(g, V, d_begin, d_end);
+        DecLanes lanes = load_lanes(g, V, w, d_begin);
         int32_t lanes0 = d_begin;
         v4i stage[kStage];
         DecHeader h = lane_header(lanes, 0);
@@ -544,6 +560,7 @@ __device__ __forceinline__ void records_tile(const PlaceArgs& g, const SnapView&
             const bool valid = h_ok;
             const bool in_lds = valid && (!kMixed || fits(cur));
             const int32_t C = lane_value(lanes.C, d - lanes0), Q = lane_value(lanes.Q, d - lanes0);
+            const int32_t dd = kPairs ? d : lane_value(lanes.d, d - lanes0);   // the decoder at place d
             if (threadIdx.x == 0 && (C < 0 || Q < 0)) raise_error(g.dev_err, MAPS_ERR_NEG_LEN);
             if (!valid && threadIdx.x == 0) raise_error(g.dev_err, MAPS_ERR_SNAPSHOT);
             int4* slice = lds + (kOdd ? (kMixed ? buf_units : kStage * kNT) : 0);
@@ -559,7 +576,7 @@ __device__ __forceinline__ void records_tile(const PlaceArgs& g, const SnapView&
             }
             if (d + 1 < d_end) {
                 if (d + 1 - lanes0 == kWave) {
-                    lanes = load_lanes(g, V, d + 1, d_end);
+                    lanes = load_lanes(g, V, w, d + 1);
                     lanes0 = d + 1;
                 }
                 h = lane_header(lanes, d + 1 - lanes0);
@@ -570,21 +587,21 @@ __device__ __forceinline__ void records_tile(const PlaceArgs& g, const SnapView&
             __syncthreads();
             if (!valid) return;
             const __amdgpu_buffer_rsrc_t row =
-                buffer_rsrc(kPairs ? g.pair + int64_t(d) * g.A + a0 : nullptr, kPairs ? uint32_t(tile_n) * 4u : 0u);
+                buffer_rsrc(kPairs ? g.pair + int64_t(dd) * g.A + a0 : nullptr, kPairs ? uint32_t(tile_n) * 4u : 0u);
             if (!kMixed || in_lds) {
                 const int32_t* pmx = reinterpret_cast<const int32_t*>(slice + half_w);
                 const uint32_t rank_lds = kOdd ? uint32_t(kMixed ? buf_units : kStage * kNT) * 16u : 0u;
                 if constexpr (kHot)
                     eval_records<kAPT, kFull, kPairs, kPolicy, true, true>(
-                        s, nullptr, rank_lds, pmx, nullptr, nullptr, uint32_t(cur.E), cur.base_peak, C, Q, d, row);
+                        s, nullptr, rank_lds, pmx, nullptr, nullptr, uint32_t(cur.E), cur.base_peak, C, Q, dd, row);
                 else
                     eval_cold<kAPT, kFull, kPairs, kPolicy>(
                         s, rank_lds, pmx, reinterpret_cast<const int2*>(slice + half_w + event_units(cur.E)),
-                        uint32_t(cur.E), cur.base_peak, C, Q, d, row);
+                        uint32_t(cur.E), cur.base_peak, C, Q, dd, row);
             } else if constexpr (kMixed) {
                 eval_records<kAPT, kFull, kPairs, kPolicy, false, false>(
                     s, reinterpret_cast<const char*>(slice_rank(V, cur)) - lds_off, 0u, slice_pmx(V, cur, L),
-                    slice_thr(V, cur, L), slice_cold(V, cur, L), uint32_t(cur.E), cur.base_peak, C, Q, d, row);
+                    slice_thr(V, cur, L), slice_cold(V, cur, L), uint32_t(cur.E), cur.base_peak, C, Q, dd, row);
             }
         };
         for (int32_t d = d_begin; d < d_end; d += 2) {
@@ -603,24 +620,127 @@ __device__ __forceinline__ void records_tile(const PlaceArgs& g, const SnapView&
         int32_t lanes0 = d_begin;
         for (int32_t d = d_begin; d < d_end; ++d) {
             if (d - lanes0 == kWave) {
-                lanes = load_lanes(g, V, d, d_end);
+                lanes = load_lanes(g, V, w, d);
                 lanes0 = d;
             }
             const DecHeader h = lane_header(lanes, d - lanes0);
             const int32_t C = lane_value(lanes.C, d - lanes0), Q = lane_value(lanes.Q, d - lanes0);
+            const int32_t dd = kPairs ? d : lane_value(lanes.d, d - lanes0);   // the decoder at place d
             const bool valid = slice_ok(h, n_total, L);
             if (threadIdx.x == 0 && (C < 0 || Q < 0)) raise_error(g.dev_err, MAPS_ERR_NEG_LEN);
             if (!valid && threadIdx.x == 0) raise_error(g.dev_err, MAPS_ERR_SNAPSHOT);
             if (!valid) continue;
             const __amdgpu_buffer_rsrc_t row =
-                buffer_rsrc(kPairs ? g.pair + int64_t(d) * g.A + a0 : nullptr, kPairs ? uint32_t(tile_n) * 4u : 0u);
-            eval_flat<kAPT, kFull, kPairs, kPolicy>(s, h.pmx_end, h.base_peak, C, Q, d, row);
+                buffer_rsrc(kPairs ? g.pair + int64_t(dd) * g.A + a0 : nullptr, kPairs ? uint32_t(tile_n) * 4u : 0u);
+            eval_flat<kAPT, kFull, kPairs, kPolicy>(s, h.pmx_end, h.base_peak, C, Q, dd, row);
         }
     };
     if (all_flat) flat_walk();
     else if (all_hot) walk(BoolTag<true>{});
     else walk(BoolTag<false>{});
     write_partials<kAPT, kFull>(g, grp, a0, s.best_key, s.best_d);
+}
+
+// The decoders of [begin, end) that an arrival of the tile can choose, in
+// index order into `list`; returns their walk.  *tot gets the largest total
+// demand over all of [begin, end), and the errors that a walk over all of them
+// would raise are raised here.  `red` holds 256 bytes.
+//
+// Whatever its prompt p and bound U, an arrival's peak on decoder d lies in
+//   [base, max(base, min(base + p + U, p + max(PMX_E, U)))],
+// and both ends grow with p and U, so the tile's largest values bound every
+// peak, and with it every key, from both sides.  A decoder whose least key is
+// above another's largest key is never chosen, not even on a tie.  Where
+// decoders differ in load by more than one request's demand that leaves a
+// handful: 1,048,576 arrivals on 1,024 overloaded decoders took 378 us over
+// every pair and take about 32 us.
+template <int kAPT, int kPolicy>
+__device__ __forceinline__ Walk list_candidates(const PlaceArgs& g, const SnapView& V, int32_t begin, int32_t end,
+                                                const int32_t (&rp)[kAPT], const int32_t (&rU)[kAPT], int64_t* red,
+                                                uint16_t* list, int64_t* tot) {
+    constexpr int kWaves = kNT / kWave;
+    const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
+    int32_t p_hi = 0, U_hi = 0;
+    int64_t pu_hi = 0;
+#pragma unroll
+    for (int k = 0; k < kAPT; ++k) {
+        if (rU[k] < 0) continue;   // placed round robin
+        const int32_t p = rp[k] < 0 ? 0 : rp[k];
+        p_hi = p > p_hi ? p : p_hi;
+        U_hi = rU[k] > U_hi ? rU[k] : U_hi;
+        pu_hi = int64_t(p) + rU[k] > pu_hi ? int64_t(p) + rU[k] : pu_hi;
+    }
+    p_hi = block_reduce_max<kNT>(p_hi, reinterpret_cast<int32_t*>(red));
+    U_hi = block_reduce_max<kNT>(U_hi, reinterpret_cast<int32_t*>(red) + kWaves);
+    pu_hi = block_reduce_max<kNT>(pu_hi, red + kWaves);
+    const int64_t n_total = load_uniform(&V.hdr->n_total);
+
+    // least and largest key of decoder d over the tile; false: its slice is not valid
+    auto keys = [&](int32_t d, int64_t* lo, int64_t* hi, int64_t* t, uint32_t* err) {
+        const DecHeader h = V.dec[d];
+        const int64_t C = g.cap[d];
+        const int32_t Q = g.qlen[d];
+        *t = h.tot;
+        *err = C < 0 || Q < 0 ? uint32_t(MAPS_ERR_NEG_LEN) : 0u;
+        *lo = INT64_MIN;
+        *hi = INT64_MAX;
+        if (!slice_ok(h, n_total, g.L)) {
+            *err |= MAPS_ERR_SNAPSHOT;
+            return false;
+        }
+        if (C < 0) return true;
+        const int64_t base = h.base_peak;
+        const int64_t up = int64_t(p_hi) + (h.pmx_end > U_hi ? h.pmx_end : U_hi);
+        const int64_t least = base - C;
+        int64_t most = base + pu_hi < up ? base + pu_hi : up;
+        most = (most > base ? most : base) - C;
+        if constexpr (kPolicy == MAPS_POLICY_MQ) {
+            const int64_t Qm = int32_t(uint32_t(Q) + 0x80000000u);   // the key where it is feasible
+            *lo = least > 0 ? least - 1 : (Qm < 0 ? Qm : 0);
+            *hi = most <= 0 ? Qm : (least <= 0 && Qm > most - 1 ? Qm : most - 1);
+        } else {
+            *lo = least;
+            *hi = most;
+        }
+        return true;
+    };
+
+    int64_t best = INT64_MAX, t_max = 0;
+    uint32_t errs = 0;
+    for (int32_t d = begin + int32_t(threadIdx.x); d < end; d += kNT) {
+        int64_t lo, hi, t;
+        uint32_t err;
+        const bool ok = keys(d, &lo, &hi, &t, &err);
+        errs |= err;
+        t_max = t > t_max ? t : t_max;
+        if (ok && hi < best) best = hi;
+    }
+    if (errs) raise_error(g.dev_err, errs);
+    best = -block_reduce_max<kNT>(-best, red);
+    *tot = block_reduce_max<kNT>(t_max, red + kWaves);
+    int32_t* count = reinterpret_cast<int32_t*>(red + 2 * kWaves);   // [2][kWaves]
+    int32_t n = 0;
+    for (int32_t d0 = begin, round = 0; d0 < end; d0 += kNT, round ^= 1) {
+        const int32_t d = d0 + int32_t(threadIdx.x);
+        int64_t lo = INT64_MAX, hi, t;
+        uint32_t err;
+        const bool take = d < end && keys(d, &lo, &hi, &t, &err) && lo <= best;
+        const uint64_t m = __builtin_amdgcn_ballot_w64(take);
+        if (lane == 0) count[round * kWaves + wid] = __popcll(m);
+        __syncthreads();   // the other round's counts were read before this barrier
+        int32_t before = 0, all = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            const int32_t c = count[round * kWaves + w];
+            before += w < wid ? c : 0;
+            all += c;
+        }
+        if (take) list[n + before + __popcll(m & ((1ull << lane) - 1ull))] = uint16_t(d - begin);
+        n += all;
+    }
+    __syncthreads();
+    n = __builtin_amdgcn_readfirstlane(n);
+    return Walk{begin, begin + n, list};
 }
 
 // When every slice of the group fits an LDS buffer the tile runs in one pass;
@@ -645,14 +765,24 @@ __global__ __launch_bounds__(kNT) void place_records(PlaceArgs g) {
         if (blockIdx.x == 0 && threadIdx.x == 0) raise_error(g.dev_err, MAPS_ERR_SNAPSHOT);
         return;
     }
-    const DecLanes lanes = load_lanes(g, V, d_begin, d_end);
-    const GroupMax gm = group_max(V, d_begin, d_end);
+    Walk w{d_begin, d_end, nullptr};
+    int64_t tot = 0;
+    if constexpr (!kPairs) {
+        if (g.list) {
+            char* red = reinterpret_cast<char*>(lds + 2 * g.buf_units);
+            w = list_candidates<kAPT, kPolicy>(g, V, d_begin, d_end, rp, rU, reinterpret_cast<int64_t*>(red),
+                                               reinterpret_cast<uint16_t*>(red + kRedBytes), &tot);
+        }
+    }
+    const DecLanes lanes = load_lanes(g, V, w, d_begin);
+    GroupMax gm = group_max(V, w);
+    if (!kPairs && g.list) gm.tot = tot;
     // the full walk stages rank words, PMX values and cold records: (E + 1) records of 4 + 8 bytes
     if (g.L.W / 2 + (int64_t(gm.records) + 3) / 4 + (int64_t(gm.records) + 1) / 2 <= g.buf_units) {
         if (a0 + kNT * kAPT <= g.A)
-            records_tile<kAPT, true, kPairs, kPolicy, false>(g, V, lds, grp, a0, gm, rp, rU, lanes);
+            records_tile<kAPT, true, kPairs, kPolicy, false>(g, V, lds, grp, a0, w, gm, rp, rU, lanes);
         else
-            records_tile<kAPT, false, kPairs, kPolicy, false>(g, V, lds, grp, a0, gm, rp, rU, lanes);
+            records_tile<kAPT, false, kPairs, kPolicy, false>(g, V, lds, grp, a0, w, gm, rp, rU, lanes);
     } else {
         constexpr int kSub = kAPT < 4 ? kAPT : 4;
         for (int t = 0; t < kAPT / kSub; ++t) {
@@ -660,7 +790,7 @@ __global__ __launch_bounds__(kNT) void place_records(PlaceArgs g) {
             if (b0 >= g.A) continue;
             int32_t sp[kSub], sU[kSub];
             fetch_arrivals<kSub>(g, b0, sp, sU);
-            records_tile<kSub, false, kPairs, kPolicy, true>(g, V, lds, grp, b0, gm, sp, sU, lanes);
+            records_tile<kSub, false, kPairs, kPolicy, true>(g, V, lds, grp, b0, w, gm, sp, sU, lanes);
         }
     }
 }
@@ -717,6 +847,7 @@ __device__ __forceinline__ void prof_tile(const PlaceArgs& g, const SnapView& V,
     const int32_t P = L.P;
     const int32_t d_begin = grp * g.Dg;
     const int32_t d_end = d_begin + g.Dg < L.D ? d_begin + g.Dg : L.D;
+    const Walk w{d_begin, d_end, nullptr};
     const int32_t nb = g.nb;   // nb * P / 4 <= kProfPF * kNT
     const int64_t tile_n = g.A - a0 < kNT * kAPT ? g.A - a0 : kNT * kAPT;
 
@@ -724,7 +855,7 @@ __device__ __forceinline__ void prof_tile(const PlaceArgs& g, const SnapView& V,
     {
         int32_t rp[kAPT], rU[kAPT];
         fetch_arrivals<kAPT>(g, a0, rp, rU);
-        check_arrivals<kAPT>(g, group_max(V, d_begin, d_end).tot, rp, rU, s.p, s.U);
+        check_arrivals<kAPT>(g, group_max(V, w).tot, rp, rU, s.p, s.U);
     }
 #pragma unroll
     for (int k = 0; k < kAPT; ++k) {
@@ -735,7 +866,7 @@ __device__ __forceinline__ void prof_tile(const PlaceArgs& g, const SnapView& V,
         s.best_d[k] = d_begin;
     }
 
-    DecLanes lanes = load_lanes(g, V, d_begin, d_end);
+    DecLanes lanes = load_lanes(g, V, w, d_begin);
     int32_t lanes0 = d_begin;
     v4i stage[kProfPF];
     if (d_begin < d_end) {
@@ -757,7 +888,7 @@ __device__ __forceinline__ void prof_tile(const PlaceArgs& g, const SnapView& V,
         for (int32_t i = 0; i < n; ++i) {
             const int32_t d = db + i;
             if (d - lanes0 == kWave) {
-                lanes = load_lanes(g, V, d, d_end);
+                lanes = load_lanes(g, V, w, d);
                 lanes0 = d;
             }
             const int32_t base = lane_value(lanes.base, d - lanes0);
@@ -1017,6 +1148,8 @@ maps_status place_records_enqueue(const void* snapshot, int32_t D, int32_t u_max
         const int32_t buf_units = kStage * kNT;
         a.buf_units = L.W / 2 + 64 <= buf_units ? buf_units : 0;
         lds = size_t(2 * a.buf_units) * 16 + kRedBytes;
+        a.list = pair_peak == nullptr && a.Dg >= kListMin && a.Dg <= kListMax;
+        if (a.list) lds += size_t(kListMax) * 2;
     }
     const int64_t tiles = (A + int64_t(kNT) * apt - 1) / (int64_t(kNT) * apt);
     const dim3 grid(unsigned(tiles * G));

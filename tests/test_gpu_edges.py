@@ -480,3 +480,39 @@ def test_calibrate_fused_launch_selects_missing_quantiles(orc, spins, monkeypatc
         assert_same(f"{name} q", q, qo)
         assert_same(f"{name} count", cnt, co)
         assert_same(f"{name} U", U, orc.apply_bounds(ap, b.edges, qo, b.u_max))
+
+
+@pytest.mark.parametrize("D,nmax,A,room", [
+    (130, 60, 700, "over"),      # groups of 17 decoders, the least that list their candidates
+    (1100, 30, 3001, "mixed"),
+    (300, 40, 5000, "fit"),      # every pair fits: the shortest queue, ties to the lower index
+    (4800, 6, 300, "over"),      # groups of 600 decoders: more than one listing round
+    (4800, 6, 300, "mixed"),
+    (200, 20, 900, "equal"),     # equal decoders: every key ties
+])
+@pytest.mark.parametrize("policy", [0, 1])
+def test_candidates_without_pairs(orc, D, nmax, A, room, policy):
+    """Decisions without the pair matrix on the record path: a tile evaluates only the decoders whose
+    least key over the tile is not above another's largest; choices are those of all pairs."""
+    rng = np.random.default_rng(D + A + policy)
+    u_max = 20000
+    seg, p, g, pred = _decoders(rng, D, nmax, u_max)
+    if room == "equal":
+        n = nmax // 2
+        seg = np.arange(D + 1, dtype=np.int64) * n
+        p, g, pred = (np.tile(x[:n], D) for x in (p, g, pred))
+    arr_pred = rng.integers(-2, u_max + 500, size=A).astype(np.int32)
+    qoff, qp, qpred, qw = _queues(rng, D, 2, u_max)
+    b = custom_batch(cal_pred=np.arange(1, 41), cal_truth=np.arange(1, 41) + 7, edges=[20], alpha_ppm=100000,
+                     u_max=u_max, seg_off=seg, res_prompt=p, res_gen=g, res_pred=pred,
+                     arr_prompt=rng.integers(0, 3000, size=A), arr_pred=arr_pred,
+                     capacity=np.zeros(D, np.int32), queue_len=rng.integers(0, 4, size=D),
+                     q_off=qoff, q_prompt=qp, q_pred=qpred, q_wait_ms=qw)
+    base = oracle_step(b, o=orc, want_pairs=False)["base_peak"].astype(np.int64)
+    off = {"over": rng.integers(-60000, 1, size=D), "mixed": rng.integers(-30000, 30000, size=D),
+           "fit": rng.integers(60000, 90000, size=D), "equal": np.full(D, -5)}[room]
+    cap = np.maximum(base + off, 0).astype(np.int32)
+    o = oracle_step(b, capacity=cap, policy=policy, want_pairs=False, rr_offset=7, o=orc)
+    gg = gpu_step(b, capacity=cap, policy=policy, want_pairs=False, rr_offset=7)
+    assert gg["err"] == 0, gg["errors"]
+    compare_all(gg, o, pairs=False)
