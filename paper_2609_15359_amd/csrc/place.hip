@@ -60,7 +60,7 @@ struct PlaceArgs {
     int32_t G;
     int32_t policy;
     int32_t Dg;        // decoders per group
-    int32_t buf_units; // record path: 16-byte units per LDS buffer (0: slices stay in HBM)
+    int32_t buf_units; // record path: 16-byte units per LDS buffer (0: the rank words alone exceed one)
     int32_t nb;        // profile path: profiles per LDS batch
     bool list;         // record path without pairs: the tile's candidates are listed first
     uint32_t* dev_err;
@@ -286,18 +286,68 @@ __device__ __forceinline__ void write_partials(const PlaceArgs& g, int32_t grp, 
 // (and its cold records {S_e, N_e + 1}, unless the tile lies in every
 // decoder's hot window) are already on their way into registers, and they
 // are written to the other buffer before the single barrier of the next
-// step.  Every lookup then stays in LDS.  A slice whose staged part exceeds
-// a buffer is read from HBM altogether (with the thresholds, so that only
-// lanes past one read a cold record).
+// step.  Every lookup then stays in LDS.
+//
+// Where a slice of the group may exceed a buffer (kMixed), the slices take the
+// two ends of the whole area in turn: a slice that fits beside the one before
+// costs the same single barrier, one that overlaps it waits for a second
+// barrier before it is written.  Only a slice that exceeds the area is read
+// from HBM altogether (with the thresholds, so that only lanes past one read a
+// cold record).  262,144 arrivals on 256 decoders of up to 8,192 residents
+// early in their outputs took 303 us with every slice past a buffer read
+// through L2 four arrivals a thread at a time, and take about 140 us.
 // ---------------------------------------------------------------------------
 constexpr int kStage = 7;   // 16-byte units per thread staged in registers: a whole LDS buffer
+constexpr int kStageArea = 18;   // the same for the area, 147,456 bytes; the tile's reduction and list follow it
+constexpr int32_t kAreaUnits = kStageArea * kNT;
+static_assert(2 * kStage <= kStageArea && size_t(kAreaUnits) * 16 + kRedBytes + size_t(kListMax) * 2 <= kLdsBytes,
+              "two buffers in the area, the reduction and the list past it");
 
-template <int kAPT>
+// kCompact (kMixed, whose staging takes up to kStageArea rows of registers):
+// what follows from the bound is computed at each pair, five instructions,
+// instead of held.
+template <int kAPT_, bool kCompact_>
 struct RecArrivals {
-    int32_t p[kAPT], U[kAPT], neg[kAPT];
-    int32_t pU[kAPT];   // p + U, set by the walk without threshold tests
-    uint32_t roff[kAPT], mask[kAPT];
+    static constexpr int kAPT = kAPT_;
+    static constexpr bool kCompact = kCompact_;
+    static constexpr int kHeld = kCompact ? 1 : kAPT;
+    int32_t p[kAPT], U[kAPT];
     int32_t best_key[kAPT], best_d[kAPT];
+    int32_t neg_[kHeld], pU_[kHeld];   // pU: set by the walk without threshold tests
+    uint32_t roff_[kHeld], mask_[kHeld];
+    uint32_t lds_off;      // LDS address of buffer 0
+    int32_t ucl_max;       // 32 W - 1
+
+    // The bound of arrival k; kCompact: read anew at each pair, so that what is
+    // computed from it is not kept across the decoders after all.
+    __device__ __forceinline__ int32_t bound(int k) const {
+        int32_t u = U[k];
+        if constexpr (kCompact) asm volatile("" : "+v"(u));
+        return u;
+    }
+    __device__ __forceinline__ uint32_t clamped(int32_t u) const {
+        u = u < 0 ? 0 : u;
+        return uint32_t(u < ucl_max ? u : ucl_max);
+    }
+    __device__ __forceinline__ int32_t neg(int k) const {
+        if constexpr (kCompact) return bound(k) >> 31;
+        else return neg_[k];
+    }
+    __device__ __forceinline__ int32_t pU(int k) const {
+        if constexpr (kCompact) return p[k] + bound(k);
+        else return pU_[k];
+    }
+    // LDS address of the rank word and the mask of the bits below the bound in it
+    __device__ __forceinline__ void rank_at(int k, uint32_t* roff, uint32_t* mask) const {
+        if constexpr (kCompact) {
+            const uint32_t uc = clamped(bound(k));
+            *roff = (uc >> 5) * 8u + lds_off;
+            *mask = (1u << (uc & 31)) - 1u;
+        } else {
+            *roff = roff_[k];
+            *mask = mask_[k];
+        }
+    }
 };
 
 // Evaluate the thread's arrivals against one decoder whose PMX values are at
@@ -308,31 +358,35 @@ struct RecArrivals {
 // HBM rank words minus buffer 0's LDS address).  Only lanes whose bound reaches an event's
 // threshold read its cold record.  kHot: every bound of the tile lies in the
 // decoder's hot window (no threshold test) and every arrival has a bound.
-template <int kAPT, bool kFull, bool kPairs, int kPolicy, bool kHot, bool kLds>
-__device__ __forceinline__ void eval_records(RecArrivals<kAPT>& s, const char* rank_g, uint32_t rank_lds,
+template <typename Arrivals, bool kFull, bool kPairs, int kPolicy, bool kHot, bool kLds>
+__device__ __forceinline__ void eval_records(Arrivals& s, const char* rank_g, uint32_t rank_lds,
                                              const int32_t* pmx, const int32_t* thr, const int2* cold, uint32_t E,
                                              int32_t base, int32_t C, int32_t Q, int32_t d,
                                              __amdgpu_buffer_rsrc_t row) {
+    constexpr int kAPT = Arrivals::kAPT;
     constexpr int kChunk = kAPT < 4 ? kAPT : 4;   // arrivals whose lookups are in flight together
     int32_t Qm = int32_t(uint32_t(Q) + 0x80000000u);
     asm("" : "+s"(Qm));   // kept as is in a scalar register: the key select then needs no source modifier
 #pragma unroll
     for (int c = 0; c < kAPT; c += kChunk) {
         uint2 w[kChunk];
+        uint32_t mask[kChunk];
 #pragma unroll
         for (int i = 0; i < kChunk; ++i) {
+            uint32_t roff;
+            s.rank_at(c + i, &roff, &mask[i]);
             if constexpr (kLds) {
                 const uint64_t x =
-                    *reinterpret_cast<const __attribute__((address_space(3))) uint64_t*>(size_t(s.roff[c + i] + rank_lds));
+                    *reinterpret_cast<const __attribute__((address_space(3))) uint64_t*>(size_t(roff + rank_lds));
                 w[i] = make_uint2(uint32_t(x), uint32_t(x >> 32));
             } else
-                w[i] = *reinterpret_cast<const uint2*>(rank_g + s.roff[c + i]);
+                w[i] = *reinterpret_cast<const uint2*>(rank_g + roff);
         }
         uint32_t e[kChunk];
         int32_t m[kChunk], t[kChunk];
 #pragma unroll
         for (int i = 0; i < kChunk; ++i) {
-            e[i] = w[i].y + __popc(w[i].x & s.mask[c + i]);
+            e[i] = w[i].y + __popc(w[i].x & mask[i]);
             if constexpr (kHot)   // LDS only: a rank past E (malformed slice) reads other LDS data, or 0
                 asm("" : "+v"(e[i]));   // opaque: the table address stays one shift-add
             else
@@ -361,8 +415,8 @@ __device__ __forceinline__ void eval_records(RecArrivals<kAPT>& s, const char* r
         for (int i = 0; i < kChunk; ++i) {
             const int k = c + i;
             // without a threshold test pf = max(PMX, U), and p + pf = max(p + PMX, p + U)
-            const int32_t peak = kHot ? imax(imax(s.p[k] + m[i], s.pU[k]), base) : imax(s.p[k] + pf[i], base);
-            if constexpr (kPairs) store_pair<kFull>(row, k, kHot ? peak : peak | s.neg[k]);
+            const int32_t peak = kHot ? imax(imax(s.p[k] + m[i], s.pU(k)), base) : imax(s.p[k] + pf[i], base);
+            if constexpr (kPairs) store_pair<kFull>(row, k, kHot ? peak : peak | s.neg(k));
             const int32_t key = select_key<kPolicy>(peak, C, Qm);
             const bool take = key < s.best_key[k];
             s.best_key[k] = take ? key : s.best_key[k];
@@ -374,14 +428,15 @@ __device__ __forceinline__ void eval_records(RecArrivals<kAPT>& s, const char* r
 // Evaluate the thread's arrivals against one decoder whose bounds all lie in
 // its flat region (and hot window): PF(U) = max(PMX_E, U), so the peak is
 // max(p + PMX_E, p + U, base) with no lookup.
-template <int kAPT, bool kFull, bool kPairs, int kPolicy>
-__device__ __forceinline__ void eval_flat(RecArrivals<kAPT>& s, int32_t pmx_end, int32_t base, int32_t C, int32_t Q,
+template <typename Arrivals, bool kFull, bool kPairs, int kPolicy>
+__device__ __forceinline__ void eval_flat(Arrivals& s, int32_t pmx_end, int32_t base, int32_t C, int32_t Q,
                                           int32_t d, __amdgpu_buffer_rsrc_t row) {
+    constexpr int kAPT = Arrivals::kAPT;
     int32_t Qm = int32_t(uint32_t(Q) + 0x80000000u);
     asm("" : "+s"(Qm));
 #pragma unroll
     for (int k = 0; k < kAPT; ++k) {
-        const int32_t peak = imax(imax(s.p[k] + pmx_end, s.pU[k]), base);
+        const int32_t peak = imax(imax(s.p[k] + pmx_end, s.pU(k)), base);
         if constexpr (kPairs) store_pair<kFull>(row, k, peak);
         const int32_t key = select_key<kPolicy>(peak, C, Qm);
         const bool take = key < s.best_key[k];
@@ -395,11 +450,12 @@ __device__ __forceinline__ void eval_flat(RecArrivals<kAPT>& s, int32_t pmx_end,
 // Staged unit u comes from slice unit u below `split` and from u + skip at
 // or above it (the cold records follow the PMX values once the thresholds
 // are skipped); units past the slice's end read as 0.
-__device__ __forceinline__ void stage_slice(v4i (&stage)[kStage], const int4* src, int32_t units, int32_t split,
+template <int kRows>
+__device__ __forceinline__ void stage_slice(v4i (&stage)[kRows], const int4* src, int32_t units, int32_t split,
                                             int32_t skip) {
     const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(src, uint32_t(units + skip) * 16u);
 #pragma unroll
-    for (int j = 0; j < kStage; ++j)
+    for (int j = 0; j < kRows; ++j)
         if (j * kNT < units) {
             const int32_t u = int32_t(threadIdx.x) + j * kNT;
             stage[j] = __builtin_bit_cast(
@@ -411,10 +467,11 @@ __device__ __forceinline__ void stage_slice(v4i (&stage)[kStage], const int4* sr
 // values and cold records are all in LDS: PF(U) = max(PMX_e, S_e + U (N_e +
 // 1), U) for every lane, with no threshold test (see event_peak for why the
 // low 24 bits of U suffice in the product).
-template <int kAPT, bool kFull, bool kPairs, int kPolicy>
-__device__ __forceinline__ void eval_cold(RecArrivals<kAPT>& s, uint32_t rank_lds, const int32_t* pmx,
+template <typename Arrivals, bool kFull, bool kPairs, int kPolicy>
+__device__ __forceinline__ void eval_cold(Arrivals& s, uint32_t rank_lds, const int32_t* pmx,
                                           const int2* cold, uint32_t E, int32_t base, int32_t C, int32_t Q,
                                           int32_t d, __amdgpu_buffer_rsrc_t row) {
+    constexpr int kAPT = Arrivals::kAPT;
     constexpr int kChunk = kAPT < 4 ? kAPT : 4;
     int32_t Qm = int32_t(uint32_t(Q) + 0x80000000u);
     asm("" : "+s"(Qm));
@@ -423,9 +480,11 @@ __device__ __forceinline__ void eval_cold(RecArrivals<kAPT>& s, uint32_t rank_ld
         uint32_t e[kChunk];
 #pragma unroll
         for (int i = 0; i < kChunk; ++i) {
+            uint32_t roff, mask;
+            s.rank_at(c + i, &roff, &mask);
             const uint64_t x =
-                *reinterpret_cast<const __attribute__((address_space(3))) uint64_t*>(size_t(s.roff[c + i] + rank_lds));
-            e[i] = uint32_t(x >> 32) + __popc(uint32_t(x) & s.mask[c + i]);
+                *reinterpret_cast<const __attribute__((address_space(3))) uint64_t*>(size_t(roff + rank_lds));
+            e[i] = uint32_t(x >> 32) + __popc(uint32_t(x) & mask);
             e[i] = e[i] < E ? e[i] : E;   // stays inside the decoder's records
         }
         int32_t m[kChunk];
@@ -442,7 +501,7 @@ __device__ __forceinline__ void eval_cold(RecArrivals<kAPT>& s, uint32_t rank_ld
             const int32_t lin = cr[i].x + int32_t(__umul24(uint32_t(U), uint32_t(cr[i].y)));
             const int32_t pf = imax(imax(m[i], lin), U);
             const int32_t peak = imax(s.p[k] + pf, base);
-            if constexpr (kPairs) store_pair<kFull>(row, k, peak | s.neg[k]);
+            if constexpr (kPairs) store_pair<kFull>(row, k, peak | s.neg(k));
             const int32_t key = select_key<kPolicy>(peak, C, Qm);
             const bool take = key < s.best_key[k];
             s.best_key[k] = take ? key : s.best_key[k];
@@ -455,8 +514,8 @@ __device__ __forceinline__ void eval_cold(RecArrivals<kAPT>& s, uint32_t rank_ld
 __device__ __forceinline__ int64_t cold_units(int64_t E) { return (E + 2) / 2; }
 
 // One arrival tile against the decoders of group grp.  kMixed: some slices
-// may exceed an LDS buffer and are then read from HBM; otherwise every slice
-// fits (a header claiming more is reported and skipped).
+// may exceed an LDS buffer (see above); otherwise every slice fits one (a
+// header claiming more is reported and skipped).
 template <int kAPT, bool kFull, bool kPairs, int kPolicy, bool kMixed>
 __device__ __forceinline__ void records_tile(const PlaceArgs& g, const SnapView& V, int4* lds, int32_t grp,
                                              int64_t a0, const Walk& w, const GroupMax& gm, const int32_t (&rp)[kAPT],
@@ -466,28 +525,33 @@ __device__ __forceinline__ void records_tile(const PlaceArgs& g, const SnapView&
     const int32_t d_begin = w.begin, d_end = w.end;   // places of the walk
     const int64_t n_total = load_uniform(&V.hdr->n_total);
     const int32_t ucl_max = 32 * L.W - 1;          // ranks above every event
-    const int32_t buf_units = g.buf_units;
+    constexpr int kRows = kMixed ? kStageArea : kStage;
+    const int32_t room = kMixed ? kAreaUnits : g.buf_units;   // the largest staged slice
     const int64_t tile_n = g.A - a0 < kNT * kAPT ? g.A - a0 : kNT * kAPT;
 
     // LDS address of buffer 0 (where the dynamic LDS starts)
     const uint32_t lds_off = uint32_t(size_t((__attribute__((address_space(3))) char*)lds));
-    RecArrivals<kAPT> s;
+    using Arrivals = RecArrivals<kAPT, kMixed>;
+    Arrivals s;
+    s.lds_off = lds_off;
+    s.ucl_max = ucl_max;
     check_arrivals<kAPT>(g, gm.tot, rp, rU, s.p, s.U);
 #pragma unroll
     for (int k = 0; k < kAPT; ++k) {
-        const int32_t U = s.U[k];
-        s.neg[k] = U < 0 ? -1 : 0;
-        const int32_t uc = U < 0 ? 0 : (U < ucl_max ? U : ucl_max);
-        s.roff[k] = uint32_t(uc >> 5) * 8u + lds_off;
-        asm("" : "+v"(s.roff[k]));   // opaque: kept whole, so a read adds only an immediate offset
-        s.mask[k] = (1u << (uc & 31)) - 1u;
+        if constexpr (!kMixed) {
+            s.neg_[k] = s.U[k] < 0 ? -1 : 0;
+            const uint32_t uc = s.clamped(s.U[k]);
+            s.roff_[k] = (uc >> 5) * 8u + lds_off;
+            asm("" : "+v"(s.roff_[k]));   // opaque: kept whole, so a read adds only an immediate offset
+            s.mask_[k] = (1u << (uc & 31)) - 1u;
+        }
         s.best_key[k] = INT32_MAX;
         s.best_d[k] = d_begin;
     }
     // smallest and largest bound of the tile, and whether an arrival lacks one
-    // (reduced through LDS past the two buffers: with no static LDS the
+    // (reduced through LDS past the area: with no static LDS the
     // buffers start at address 0, so their offsets fold into the LDS reads)
-    int32_t (*red)[kNT / kWave] = reinterpret_cast<int32_t (*)[kNT / kWave]>(lds + 2 * buf_units);
+    int32_t (*red)[kNT / kWave] = reinterpret_cast<int32_t (*)[kNT / kWave]>(lds + kAreaUnits);
     int32_t t_lo = INT32_MAX, t_hi = -1, t_neg = 0;
 #pragma unroll
     for (int k = 0; k < kAPT; ++k) {
@@ -529,17 +593,17 @@ __device__ __forceinline__ void records_tile(const PlaceArgs& g, const SnapView&
         constexpr bool kHot = decltype(hot_tag)::value;
         if constexpr (kHot) {
 #pragma unroll
-            for (int k = 0; k < kAPT; ++k) {
-                s.pU[k] = s.p[k] + s.U[k];
-                asm("" : "+v"(s.pU[k]));   // opaque: keeps max(p + PMX, p + U, base) a single three-way max
+            for (int k = 0; k < Arrivals::kHeld; ++k) {
+                s.pU_[k] = s.p[k] + s.U[k];
+                asm("" : "+v"(s.pU_[k]));   // opaque: keeps max(p + PMX, p + U, base) a single three-way max
             }
         }
         // staged units: rank words and PMX, and (full walk) the cold records after them
         auto staged = [&](const DecHeader& h) {
             return int64_t(half_w) + event_units(h.E) + (kHot ? 0 : cold_units(h.E));
         };
-        auto fits = [&](const DecHeader& h) { return staged(h) <= buf_units; };
-        auto stage_next = [&](v4i (&st)[kStage], const DecHeader& h) {
+        auto fits = [&](const DecHeader& h) { return staged(h) <= room; };
+        auto stage_next = [&](v4i (&st)[kRows], const DecHeader& h) {
             const int32_t split = half_w + int32_t(event_units(h.E));
             stage_slice(st, V.slices + h.slice_off, int32_t(staged(h)), split,
                         kHot ? 0 : int32_t(event_units(h.E)));   // the cold records skip the thresholds
@@ -548,7 +612,8 @@ __device__ __forceinline__ void records_tile(const PlaceArgs& g, const SnapView&
         // across the preamble costs this walk registers and time
         DecLanes lanes = load_lanes(g, V, w, d_begin);
         int32_t lanes0 = d_begin;
-        v4i stage[kStage];
+        v4i stage[kRows];
+        int32_t before = 0;   // kMixed: units of the other end that the decoder before this one holds
         DecHeader h = lane_header(lanes, 0);
         bool h_ok = d_begin < d_end && slice_ok(h, n_total, L) && (kMixed || fits(h));
         if (h_ok && fits(h)) stage_next(stage, h);
@@ -563,16 +628,22 @@ __device__ __forceinline__ void records_tile(const PlaceArgs& g, const SnapView&
             const int32_t dd = kPairs ? d : lane_value(lanes.d, d - lanes0);   // the decoder at place d
             if (threadIdx.x == 0 && (C < 0 || Q < 0)) raise_error(g.dev_err, MAPS_ERR_NEG_LEN);
             if (!valid && threadIdx.x == 0) raise_error(g.dev_err, MAPS_ERR_SNAPSHOT);
-            int4* slice = lds + (kOdd ? (kMixed ? buf_units : kStage * kNT) : 0);
+            const int32_t units = in_lds ? int32_t(staged(cur)) : 0;
+            const int32_t at = kOdd ? (kMixed ? kAreaUnits - units : kStage * kNT) : 0;
+            int4* slice = lds + at;
+            if constexpr (kMixed) {
+                if (before + units > kAreaUnits) __syncthreads();   // uniform: every wave is done with the one before
+                before = units;
+            }
             if (in_lds) {
                 // This buffer was last read for decoder d-2, which every wave
-                // finished before passing the barrier of decoder d-1.  Staged
-                // units past the slice's end (0) stay inside the buffer:
-                // kStage * kNT units fit it.
-                const int32_t units = int32_t(staged(cur));
+                // finished before passing the barrier of decoder d-1.  In a
+                // buffer, staged units past the slice's end (0) stay inside:
+                // kStage * kNT units fit it; in the whole area they are left out.
 #pragma unroll
-                for (int j = 0; j < kStage; ++j)
-                    if (j * kNT < units) reinterpret_cast<v4i*>(slice)[int(threadIdx.x) + j * kNT] = stage[j];
+                for (int j = 0; j < kRows; ++j)
+                    if (j * kNT < units && (!kMixed || int(threadIdx.x) + j * kNT < units))
+                        reinterpret_cast<v4i*>(slice)[int(threadIdx.x) + j * kNT] = stage[j];
             }
             if (d + 1 < d_end) {
                 if (d + 1 - lanes0 == kWave) {
@@ -590,16 +661,16 @@ __device__ __forceinline__ void records_tile(const PlaceArgs& g, const SnapView&
                 buffer_rsrc(kPairs ? g.pair + int64_t(dd) * g.A + a0 : nullptr, kPairs ? uint32_t(tile_n) * 4u : 0u);
             if (!kMixed || in_lds) {
                 const int32_t* pmx = reinterpret_cast<const int32_t*>(slice + half_w);
-                const uint32_t rank_lds = kOdd ? uint32_t(kMixed ? buf_units : kStage * kNT) * 16u : 0u;
+                const uint32_t rank_lds = uint32_t(at) * 16u;
                 if constexpr (kHot)
-                    eval_records<kAPT, kFull, kPairs, kPolicy, true, true>(
+                    eval_records<Arrivals, kFull, kPairs, kPolicy, true, true>(
                         s, nullptr, rank_lds, pmx, nullptr, nullptr, uint32_t(cur.E), cur.base_peak, C, Q, dd, row);
                 else
-                    eval_cold<kAPT, kFull, kPairs, kPolicy>(
+                    eval_cold<Arrivals, kFull, kPairs, kPolicy>(
                         s, rank_lds, pmx, reinterpret_cast<const int2*>(slice + half_w + event_units(cur.E)),
                         uint32_t(cur.E), cur.base_peak, C, Q, dd, row);
             } else if constexpr (kMixed) {
-                eval_records<kAPT, kFull, kPairs, kPolicy, false, false>(
+                eval_records<Arrivals, kFull, kPairs, kPolicy, false, false>(
                     s, reinterpret_cast<const char*>(slice_rank(V, cur)) - lds_off, 0u, slice_pmx(V, cur, L),
                     slice_thr(V, cur, L), slice_cold(V, cur, L), uint32_t(cur.E), cur.base_peak, C, Q, dd, row);
             }
@@ -612,9 +683,9 @@ __device__ __forceinline__ void records_tile(const PlaceArgs& g, const SnapView&
     // the walk of a tile in every flat region: no slices, no LDS, no barrier
     auto flat_walk = [&]() {
 #pragma unroll
-        for (int k = 0; k < kAPT; ++k) {
-            s.pU[k] = s.p[k] + s.U[k];
-            asm("" : "+v"(s.pU[k]));   // opaque: keeps max(p + PMX_E, p + U, base) a single three-way max
+        for (int k = 0; k < Arrivals::kHeld; ++k) {
+            s.pU_[k] = s.p[k] + s.U[k];
+            asm("" : "+v"(s.pU_[k]));   // opaque: keeps max(p + PMX_E, p + U, base) a single three-way max
         }
         DecLanes lanes = first_lanes;
         int32_t lanes0 = d_begin;
@@ -632,7 +703,7 @@ __device__ __forceinline__ void records_tile(const PlaceArgs& g, const SnapView&
             if (!valid) continue;
             const __amdgpu_buffer_rsrc_t row =
                 buffer_rsrc(kPairs ? g.pair + int64_t(dd) * g.A + a0 : nullptr, kPairs ? uint32_t(tile_n) * 4u : 0u);
-            eval_flat<kAPT, kFull, kPairs, kPolicy>(s, h.pmx_end, h.base_peak, C, Q, dd, row);
+            eval_flat<Arrivals, kFull, kPairs, kPolicy>(s, h.pmx_end, h.base_peak, C, Q, dd, row);
         }
     };
     if (all_flat) flat_walk();
@@ -743,9 +814,8 @@ __device__ __forceinline__ Walk list_candidates(const PlaceArgs& g, const SnapVi
     return Walk{begin, begin + n, list};
 }
 
-// When every slice of the group fits an LDS buffer the tile runs in one pass;
-// otherwise it is split into sub-tiles of at most 4 arrivals per thread that
-// read the large slices from HBM.
+// When every slice of the walk fits an LDS buffer the two buffers alternate;
+// otherwise the slices share the whole area.
 template <int kAPT, bool kPairs, int kPolicy>
 __global__ __launch_bounds__(kNT) void place_records(PlaceArgs g) {
     extern __shared__ int4 lds[];
@@ -769,7 +839,7 @@ __global__ __launch_bounds__(kNT) void place_records(PlaceArgs g) {
     int64_t tot = 0;
     if constexpr (!kPairs) {
         if (g.list) {
-            char* red = reinterpret_cast<char*>(lds + 2 * g.buf_units);
+            char* red = reinterpret_cast<char*>(lds + kAreaUnits);
             w = list_candidates<kAPT, kPolicy>(g, V, d_begin, d_end, rp, rU, reinterpret_cast<int64_t*>(red),
                                                reinterpret_cast<uint16_t*>(red + kRedBytes), &tot);
         }
@@ -784,14 +854,10 @@ __global__ __launch_bounds__(kNT) void place_records(PlaceArgs g) {
         else
             records_tile<kAPT, false, kPairs, kPolicy, false>(g, V, lds, grp, a0, w, gm, rp, rU, lanes);
     } else {
-        constexpr int kSub = kAPT < 4 ? kAPT : 4;
-        for (int t = 0; t < kAPT / kSub; ++t) {
-            const int64_t b0 = a0 + int64_t(t) * kNT * kSub;
-            if (b0 >= g.A) continue;
-            int32_t sp[kSub], sU[kSub];
-            fetch_arrivals<kSub>(g, b0, sp, sU);
-            records_tile<kSub, false, kPairs, kPolicy, true>(g, V, lds, grp, b0, w, gm, sp, sU, lanes);
-        }
+        if (a0 + kNT * kAPT <= g.A)
+            records_tile<kAPT, true, kPairs, kPolicy, true>(g, V, lds, grp, a0, w, gm, rp, rU, lanes);
+        else
+            records_tile<kAPT, false, kPairs, kPolicy, true>(g, V, lds, grp, a0, w, gm, rp, rU, lanes);
     }
 }
 
@@ -1144,12 +1210,11 @@ maps_status place_records_enqueue(const void* snapshot, int32_t D, int32_t u_max
         a.nb = int32_t(nb < 8 ? nb : 8);
         lds = size_t(kProfPF) * kNT * 16;
     } else {
-        // two buffers of kStage * kNT 16-byte units: the staged part of a slice
+        // two buffers of kStage * kNT 16-byte units, or the whole area: the staged part of a slice
         const int32_t buf_units = kStage * kNT;
         a.buf_units = L.W / 2 + 64 <= buf_units ? buf_units : 0;
-        lds = size_t(2 * a.buf_units) * 16 + kRedBytes;
         a.list = pair_peak == nullptr && a.Dg >= kListMin && a.Dg <= kListMax;
-        if (a.list) lds += size_t(kListMax) * 2;
+        lds = size_t(kAreaUnits) * 16 + kRedBytes + (a.list ? size_t(kListMax) * 2 : 0);
     }
     const int64_t tiles = (A + int64_t(kNT) * apt - 1) / (int64_t(kNT) * apt);
     const dim3 grid(unsigned(tiles * G));

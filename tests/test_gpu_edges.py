@@ -516,3 +516,36 @@ def test_candidates_without_pairs(orc, D, nmax, A, room, policy):
     gg = gpu_step(b, capacity=cap, policy=policy, want_pairs=False, rr_offset=7)
     assert gg["err"] == 0, gg["errors"]
     compare_all(gg, o, pairs=False)
+
+
+@pytest.mark.parametrize("counts,u_max,A,pairs", [
+    ([5000, 4600, 9000, 30, 0, 7000], 20000, 3000, True),            # slices that overlap at the two ends, and small ones
+    ([12000, 9800, 200, 13000, 12500, 40, 10000], 60000, 1500, True),  # slices past the whole area, read through L2
+    ([12000, 9800, 200, 13000, 12500, 40, 10000], 60000, 1500, False),
+    ([4700] * 3, 20000, 140000, True),                               # 16 arrivals a thread, a ragged last tile
+    ([4700] * 3, 20000, 140000, False),
+    ([10, 10], 300000, 600, True),                                   # rank words past the area
+])
+@pytest.mark.parametrize("policy", [0, 1])
+def test_slices_past_a_buffer(orc, counts, u_max, A, pairs, policy):
+    """Decoders whose staged slice exceeds an LDS buffer (57,344 bytes of rank words and 12 bytes an event): the
+    slices share the whole LDS area from its two ends, the largest stay in HBM."""
+    rng = np.random.default_rng(len(counts) + A + policy)
+    D = len(counts)
+    seg = np.zeros(D + 1, np.int64)
+    seg[1:] = np.cumsum(counts)
+    n = int(seg[-1])
+    p = rng.integers(0, 40, size=n).astype(np.int32)
+    g = rng.integers(0, 5, size=n).astype(np.int32)
+    pred = rng.integers(5, u_max, size=n).astype(np.int32)
+    arr = rng.integers(-1, u_max + 900, size=A).astype(np.int32)
+    b = custom_batch(cal_pred=np.arange(1, 41), cal_truth=np.arange(1, 41) + 7, edges=[20], alpha_ppm=100000,
+                     u_max=u_max, seg_off=seg, res_prompt=p, res_gen=g, res_pred=pred,
+                     arr_prompt=rng.integers(0, 500, size=A), arr_pred=arr, capacity=np.zeros(D, np.int32),
+                     queue_len=rng.integers(0, 4, size=D))
+    base = oracle_step(b, o=orc, want_pairs=False)["base_peak"].astype(np.int64)
+    cap = (base + rng.integers(-3000, 30000, size=D)).clip(0).astype(np.int32)
+    o = oracle_step(b, capacity=cap, policy=policy, want_pairs=pairs, o=orc)
+    gg = gpu_step(b, capacity=cap, policy=policy, want_pairs=pairs)
+    assert gg["err"] == 0, gg["errors"]
+    compare_all(gg, o, pairs=pairs)
