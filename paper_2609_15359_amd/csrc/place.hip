@@ -295,7 +295,7 @@ __device__ __forceinline__ void write_partials(const PlaceArgs& g, int32_t grp, 
 // from HBM altogether (with the thresholds, so that only lanes past one read a
 // cold record).  262,144 arrivals on 256 decoders of up to 8,192 residents
 // early in their outputs took 303 us with every slice past a buffer read
-// through L2 four arrivals a thread at a time, and take about 140 us.
+// through L2 four arrivals a thread at a time, and take 124 us.
 // ---------------------------------------------------------------------------
 constexpr int kStage = 7;   // 16-byte units per thread staged in registers: a whole LDS buffer
 constexpr int kStageArea = 18;   // the same for the area, 147,456 bytes; the tile's reduction and list follow it
@@ -357,7 +357,8 @@ struct RecArrivals {
 // constant where the buffer is fixed), otherwise at `rank_g` plus them (the
 // HBM rank words minus buffer 0's LDS address).  Only lanes whose bound reaches an event's
 // threshold read its cold record.  kHot: every bound of the tile lies in the
-// decoder's hot window (no threshold test) and every arrival has a bound.
+// decoder's hot window (no threshold test) and every arrival whose pairs are
+// written has a bound.
 template <typename Arrivals, bool kFull, bool kPairs, int kPolicy, bool kHot, bool kLds>
 __device__ __forceinline__ void eval_records(Arrivals& s, const char* rank_g, uint32_t rank_lds,
                                              const int32_t* pmx, const int32_t* thr, const int2* cold, uint32_t E,
@@ -427,8 +428,9 @@ __device__ __forceinline__ void eval_records(Arrivals& s, const char* rank_g, ui
 
 // Evaluate the thread's arrivals against one decoder whose bounds all lie in
 // its flat region (and hot window): PF(U) = max(PMX_E, U), so the peak is
-// max(p + PMX_E, p + U, base) with no lookup.
-template <typename Arrivals, bool kFull, bool kPairs, int kPolicy>
+// max(p + PMX_E, p + U, base) with no lookup.  kNeg: an arrival of the tile may
+// lack a bound (its row entries are -1; its choice is made later).
+template <typename Arrivals, bool kFull, bool kPairs, int kPolicy, bool kNeg>
 __device__ __forceinline__ void eval_flat(Arrivals& s, int32_t pmx_end, int32_t base, int32_t C, int32_t Q,
                                           int32_t d, __amdgpu_buffer_rsrc_t row) {
     constexpr int kAPT = Arrivals::kAPT;
@@ -437,7 +439,7 @@ __device__ __forceinline__ void eval_flat(Arrivals& s, int32_t pmx_end, int32_t 
 #pragma unroll
     for (int k = 0; k < kAPT; ++k) {
         const int32_t peak = imax(imax(s.p[k] + pmx_end, s.pU(k)), base);
-        if constexpr (kPairs) store_pair<kFull>(row, k, peak);
+        if constexpr (kPairs) store_pair<kFull>(row, k, kNeg ? peak | s.neg(k) : peak);
         const int32_t key = select_key<kPolicy>(peak, C, Qm);
         const bool take = key < s.best_key[k];
         s.best_key[k] = take ? key : s.best_key[k];
@@ -582,10 +584,10 @@ __device__ __forceinline__ void records_tile(const PlaceArgs& g, const SnapView&
     t_hi = __builtin_amdgcn_readfirstlane(t_hi);
     t_neg = __builtin_amdgcn_readfirstlane(t_neg);
     // the tile skips every threshold test when the hot windows of all the
-    // group's decoders hold all its bounds (and every arrival has a bound)
-    const bool all_hot = !kMixed && t_neg == 0 && t_lo >= gm.hot_lo && t_hi <= gm.hot_hi;
+    // group's decoders hold all its bounds
+    const bool all_hot = !kMixed && t_lo >= gm.hot_lo && t_hi <= gm.hot_hi;
     // ... and needs no lookup at all when they also lie in every flat region
-    const bool all_flat = t_neg == 0 && t_lo >= gm.flat_lo && t_hi <= gm.hot_hi;
+    const bool all_flat = t_lo >= gm.flat_lo && t_hi <= gm.hot_hi;
 
     // the decoder walk, with or without the threshold tests: it stages the
     // rank words and the PMX values, and the thresholds when it tests them
@@ -681,7 +683,7 @@ __device__ __forceinline__ void records_tile(const PlaceArgs& g, const SnapView&
         }
     };
     // the walk of a tile in every flat region: no slices, no LDS, no barrier
-    auto flat_walk = [&]() {
+    auto flat_walk = [&](auto neg_tag) {
 #pragma unroll
         for (int k = 0; k < Arrivals::kHeld; ++k) {
             s.pU_[k] = s.p[k] + s.U[k];
@@ -703,12 +705,23 @@ __device__ __forceinline__ void records_tile(const PlaceArgs& g, const SnapView&
             if (!valid) continue;
             const __amdgpu_buffer_rsrc_t row =
                 buffer_rsrc(kPairs ? g.pair + int64_t(dd) * g.A + a0 : nullptr, kPairs ? uint32_t(tile_n) * 4u : 0u);
-            eval_flat<Arrivals, kFull, kPairs, kPolicy>(s, h.pmx_end, h.base_peak, C, Q, dd, row);
+            eval_flat<Arrivals, kFull, kPairs, kPolicy, decltype(neg_tag)::value>(s, h.pmx_end, h.base_peak, C, Q, dd, row);
         }
     };
-    if (all_flat) flat_walk();
-    else if (all_hot) walk(BoolTag<true>{});
-    else walk(BoolTag<false>{});
+    // One arrival without a bound in five hundred puts nearly every large tile
+    // on the kNeg walk, an instruction a pair more; such tiles took the walk
+    // with the cold records before (262,144 such arrivals on 256 decoders of
+    // 4,096 residents: 273 us the step, now 113 us).  Without the matrix nothing
+    // of theirs is written.  Bounds in every hot window that reach below a flat
+    // region are rare, and with arrivals without a bound go to the last walk.
+    if (all_flat) {
+        if (kPairs && t_neg != 0) flat_walk(BoolTag<kPairs>{});
+        else flat_walk(BoolTag<false>{});
+    } else if (!kMixed && all_hot && (!kPairs || t_neg == 0)) {
+        walk(BoolTag<true>{});
+    } else {
+        walk(BoolTag<false>{});
+    }
     write_partials<kAPT, kFull>(g, grp, a0, s.best_key, s.best_d);
 }
 
@@ -724,7 +737,7 @@ __device__ __forceinline__ void records_tile(const PlaceArgs& g, const SnapView&
 // above another's largest key is never chosen, not even on a tie.  Where
 // decoders differ in load by more than one request's demand that leaves a
 // handful: 1,048,576 arrivals on 1,024 overloaded decoders took 378 us over
-// every pair and take about 32 us.
+// every pair and take 15 us.
 template <int kAPT, int kPolicy>
 __device__ __forceinline__ Walk list_candidates(const PlaceArgs& g, const SnapView& V, int32_t begin, int32_t end,
                                                 const int32_t (&rp)[kAPT], const int32_t (&rU)[kAPT], int64_t* red,

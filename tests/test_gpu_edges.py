@@ -549,3 +549,29 @@ def test_slices_past_a_buffer(orc, counts, u_max, A, pairs, policy):
     gg = gpu_step(b, capacity=cap, policy=policy, want_pairs=pairs)
     assert gg["err"] == 0, gg["errors"]
     compare_all(gg, o, pairs=pairs)
+
+
+@pytest.mark.parametrize("A", [700, 140001])
+@pytest.mark.parametrize("policy,pairs", [(0, True), (1, True), (0, False)])
+def test_missing_bounds_in_flat_regions(orc, A, policy, pairs):
+    """Tiles whose bounds lie in every decoder's flat region (no lookup), with arrivals without a bound among them: their row entries are -1, their choice round robin."""
+    rng = np.random.default_rng(A + policy)
+    D, u_max = 5, 20000
+    seg, p, g, pred = _decoders(rng, D, 300, u_max)
+    p = rng.integers(2000, 9000, size=p.size).astype(np.int32)   # the occupancy falls from the first step on
+    pred = np.minimum(pred, u_max * 3 // 10)
+    arr = rng.integers(u_max * 3 // 10, u_max + 500, size=A).astype(np.int32)
+    arr[rng.random(A) < 0.01] = -1
+    b = custom_batch(cal_pred=np.arange(1, 41), cal_truth=np.arange(1, 41) + 7, edges=[20], alpha_ppm=100000,
+                     u_max=u_max, seg_off=seg, res_prompt=p, res_gen=g, res_pred=pred,
+                     arr_prompt=rng.integers(0, 3000, size=A), arr_pred=arr, capacity=np.zeros(D, np.int32),
+                     queue_len=rng.integers(0, 3, size=D))
+    base = oracle_step(b, o=orc, want_pairs=False)["base_peak"].astype(np.int64)
+    cap = (base + rng.integers(-3000, 9000, size=D)).clip(0).astype(np.int32)
+    o = oracle_step(b, capacity=cap, policy=policy, want_pairs=pairs, rr_offset=3, o=orc)
+    gg = gpu_step(b, capacity=cap, policy=policy, want_pairs=pairs, rr_offset=3)
+    assert gg["err"] == 0, gg["errors"]
+    hot_lo, hot_hi, flat_lo = gg["dec_hdr"][:, 6].max(), gg["dec_hdr"][:, 7].min(), gg["dec_hdr"][:, 8].max()
+    U = o["U"][p.size:p.size + A]
+    assert max(hot_lo, flat_lo) <= U[U >= 0].min() and U.max() <= hot_hi
+    compare_all(gg, o, pairs=pairs)
