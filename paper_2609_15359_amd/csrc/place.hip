@@ -298,7 +298,7 @@ __device__ __forceinline__ void write_partials(const PlaceArgs& g, int32_t grp, 
 // through L2 four arrivals a thread at a time, and take 124 us.
 // ---------------------------------------------------------------------------
 constexpr int kStage = 7;   // 16-byte units per thread staged in registers: a whole LDS buffer
-constexpr int kStageArea = 18;   // the same for the area, 147,456 bytes; the tile's reduction and list follow it
+constexpr int kStageArea = 16;   // the same for the area, 131,072 bytes; the tile's reduction and list follow it
 constexpr int32_t kAreaUnits = kStageArea * kNT;
 static_assert(2 * kStage <= kStageArea && size_t(kAreaUnits) * 16 + kRedBytes + size_t(kListMax) * 2 <= kLdsBytes,
               "two buffers in the area, the reduction and the list past it");
