@@ -12,7 +12,7 @@
 //                     size and start of every bucket's run in the chunk, the
 //                     chunk's largest score;
 //   cal_bucket_select per bucket: n_b and k_b from its runs' sizes, its runs
-//                     gathered into LDS and registers, then a most-
+//                     gathered into LDS, then a most-
 //                     significant-digit-first radix select of the k_b-th
 //                     score, 8 bits a pass from the top digit of the largest
 //                     score, histograms in LDS;
@@ -293,11 +293,16 @@ constexpr int64_t kChunk = int64_t(kSortNT) * kJ;      // residuals per workgrou
 constexpr int64_t kSortMaxChunks = 1024;               // larger sets take the all-bucket path
 constexpr int kSelNT = 1024;
 constexpr int kSelWaves = kSelNT / kWave;
-constexpr int kKeep = 24;         // scores per thread the bucket select keeps in registers across passes
 constexpr int kGatherRuns = 16;   // runs a wavefront of the select loads at once
-constexpr size_t kSelStageBytes = size_t(kSelNT) * kKeep * 4;
+constexpr int kStagePer = 36;     // scores per thread the bucket select holds in LDS
+constexpr int kKeep = 24;         // of those, kept in registers across passes where they were gathered at once
+constexpr int kStageReads = 3;    // 16-byte reads of the stage in flight a thread
+constexpr int kRunLoads = 8;      // loads a wavefront keeps in flight along one long run
+constexpr uint32_t kStageScores = uint32_t(kSelNT) * kStagePer;
+constexpr size_t kSelStageBytes = size_t(kStageScores) * 4;
 static_assert(kSortMaxChunks <= kSelNT, "the select holds one run of its bucket per thread");
-static_assert(kKeep % 4 == 0 && kGatherRuns <= kWave, "select slots come in groups of four");
+static_assert(kStagePer % (4 * kStageReads) == 0 && kKeep % (4 * kStageReads) == 0, "the stage is read in whole rounds");
+static_assert(kGatherRuns <= kWave, "one lane a gathered run");
 
 int64_t sort_chunks(int64_t n) { return (n + kChunk - 1) / kChunk; }
 
@@ -428,7 +433,8 @@ __global__ __launch_bounds__(kSortNT) void cal_chunk_sort(const int32_t* __restr
         for (int i = threadIdx.x; i < nb; i += kSortNT) qflag[i] = 0u;
 }
 
-// Digit of the k-th element among the 256 bins of hist (one wavefront).
+// Digit of the k-th element among the 256 bins of hist, its rank among that
+// digit's elements and their number (one wavefront).
 __device__ inline void pick_digit(const uint32_t* hist, int32_t k, uint32_t* pick) {
     const int lane = threadIdx.x;
     uint32_t h[4];
@@ -438,7 +444,11 @@ __device__ inline void pick_digit(const uint32_t* hist, int32_t k, uint32_t* pic
     uint32_t c = wave_incl_scan_add(mine) - mine;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        if (c < uint32_t(k) && c + h[j] >= uint32_t(k)) { pick[0] = uint32_t(lane * 4 + j); pick[1] = uint32_t(k) - c; }
+        if (c < uint32_t(k) && c + h[j] >= uint32_t(k)) {
+            pick[0] = uint32_t(lane * 4 + j);
+            pick[1] = uint32_t(k) - c;
+            pick[2] = h[j];
+        }
         c += h[j];
     }
 }
@@ -478,13 +488,34 @@ struct SelectArgs {
     uint64_t* qflag;   // NULL when no apply workgroup waits
 };
 
+struct SelectLds {
+    uint32_t roff[kSortMaxChunks];   // where each run starts among the bucket's scores
+    uint32_t rcnt[kSortMaxChunks];   // its size
+    uint32_t rsrc[kSortMaxChunks];   // its first score's index in `sorted`
+    uint32_t hist[2][256];           // digit histograms of alternate passes
+    uint32_t red[kSelWaves];
+    uint32_t pick[2][3];             // digit, remaining rank and digit count of alternate passes
+    uint32_t appended;               // scores of a larger bucket gathered so far
+};
+static_assert(kSelStageBytes + sizeof(SelectLds) + kFastBuckets / 8 <= kLdsPerWorkgroup,
+              "stage, run tables, histograms and the missing buckets' bits in one workgroup's LDS");
+
 // Workgroup b of a selection: bucket b's size n_b and rank k_b (Eq. (3))
 // from the run sizes, then the k_b-th smallest score of its runs, most
 // significant 8-bit digit first from the top digit of the largest score.  A
-// bucket of at most kSelNT * kKeep scores is gathered once (runs into LDS,
-// then into registers) and kept across passes; a larger one is read from its
-// runs on every pass.
-__device__ int32_t select_bucket(const SelectArgs& A, int b) {
+// bucket of at most kStageScores scores is gathered into LDS once.  Of a
+// larger one, every pass reads the runs until the digits found so far leave no
+// more than that; the pass after gathers those.  What bounds it is the latency
+// of one workgroup's loads, so the first 128 scores of 16 runs, then 8 loads
+// along a long run, are in flight a wavefront.  With 24,576 scores held and
+// longer runs and larger buckets read a load at a time, 128 buckets of 31,250
+// took 89 us (now 50) and a step with one of 1,000,000 took 630 us (now 393).
+//
+// kHold false: nothing is held, every pass reads the runs a load at a time.
+// For the waiting workgroups' rare use: a second whole copy in their kernel
+// costs the first one registers.
+template <bool kHold>
+__device__ __forceinline__ int32_t select_bucket(const SelectArgs& A, int b, SelectLds& lds) {
     const int nb = A.nb;
     const int64_t chunks = A.chunks;
     const int32_t alpha_ppm = A.alpha_ppm;
@@ -492,16 +523,18 @@ __device__ int32_t select_bucket(const SelectArgs& A, int b) {
     int32_t* q_out = A.q_out;
     int32_t* count_out = A.count_out;
     (void)nb;
-    extern __shared__ __align__(16) uint32_t stage[];   // [kSelNT * kKeep] the bucket's scores
-    __shared__ uint32_t roff[kSortMaxChunks];           // where each run starts among the bucket's scores
-    __shared__ uint32_t rcnt[kSortMaxChunks];           // its size
-    __shared__ uint32_t rsrc[kSortMaxChunks];           // its first score's index in `sorted`
-    __shared__ uint32_t hist[2][256];                   // digit histograms of alternate passes
-    __shared__ uint32_t red[kSelWaves];
-    __shared__ uint32_t pick[2][2];                     // digit and remaining rank of alternate passes
+    extern __shared__ __align__(16) uint32_t stage[];   // [kStageScores] the bucket's scores
+    auto& roff = lds.roff;
+    auto& rcnt = lds.rcnt;
+    auto& rsrc = lds.rsrc;
+    auto& hist = lds.hist;
+    auto& red = lds.red;
+    auto& pick = lds.pick;
+    auto& appended = lds.appended;
     const int t = threadIdx.x;
     const int lane = t % kWave, w = t / kWave;
     if (t < 256) hist[0][t] = 0;   // published by the barriers of the scans below
+    if (t == 0) appended = 0;
     uint32_t c = 0, m = 0, src = 0;
     if (t < chunks) {
         c = A.run_cnt[int64_t(b) * chunks + t];
@@ -525,19 +558,25 @@ __device__ int32_t select_bucket(const SelectArgs& A, int b) {
     }
     int32_t k = int32_t(k64);
     const int top = mx >> 24 ? 24 : (mx >> 16 ? 16 : (mx >> 8 ? 8 : 0));
-    const bool in_regs = nbk <= uint32_t(kSelNT) * kKeep;
-    // Slot j = 4g + e of thread t holds score g * 4 * kSelNT + 4t + e of the
-    // bucket (16-byte LDS reads); groups past n_b are skipped whole.
-    uint32_t x[kKeep] = {};
-    auto slot = [&](int j) { return uint32_t(j / 4) * (4 * kSelNT) + 4 * uint32_t(t) + uint32_t(j % 4); };
+    uint32_t held = kHold && nbk <= kStageScores ? nbk : 0;   // scores in LDS (0: still in the runs)
+    const bool at_once = held != 0;
+    uint4 x[kKeep / 4] = {};
     uint32_t zeros = 0;   // the first pass's digit-0 count of this wavefront
-    if (in_regs) {
-        // wavefront w gathers runs w, w + kSelWaves, ...: the first 128
-        // scores of kGatherRuns runs in flight per lane, longer runs' rest
-        // after.  Lane q reads run q's table entry; the wavefront shares it.
-        // Every score also enters the first pass's histogram (its top digit:
-        // every score lies below 256 << top) as it arrives, so that pass
-        // needs no loop of its own.
+    // Every score of the bucket, by whole wavefronts: fn(score, whether the
+    // lane holds one, its place among the bucket's scores).  Wavefront w takes
+    // runs w, w + kSelWaves, ...; lane q reads run q's table entry and the
+    // wavefront shares it.
+    auto each_score = [&](auto fn) __attribute__((always_inline)) {
+        if constexpr (!kHold) {
+            for (int64_t r = w; r < chunks; r += kSelWaves) {
+                const uint32_t cn = rcnt[r], s0 = rsrc[r], d0 = roff[r];
+                for (uint32_t i0 = 0; i0 < cn; i0 += kWave) {   // bounds uniform across the wavefront
+                    const uint32_t i = i0 + lane;
+                    fn(i < cn ? uint32_t(sorted[s0 + i]) : 0u, i < cn, d0 + i);
+                }
+            }
+            return;
+        }
         for (int64_t r0 = w; r0 < chunks; r0 += int64_t(kSelWaves) * kGatherRuns) {
             const int64_t rq = r0 + int64_t(lane) * kSelWaves;
             const bool has = lane < kGatherRuns && rq < chunks;
@@ -551,59 +590,104 @@ __device__ int32_t select_bucket(const SelectArgs& A, int b) {
             }
 #pragma unroll
             for (int q = 0; q < kGatherRuns; ++q) {
+                const uint32_t cn = __builtin_amdgcn_readlane(tc, q), d0 = __builtin_amdgcn_readlane(to, q);
+                fn(v0[q], uint32_t(lane) < cn, d0 + lane);
+                fn(v1[q], uint32_t(lane) + kWave < cn, d0 + kWave + lane);
+            }
+            // the rest of longer runs; bounds uniform across the wavefront
+            for (uint64_t more = __ballot(tc > 2 * kWave); more != 0; more &= more - 1) {
+                const int q = __ffsll((unsigned long long)more) - 1;
                 const uint32_t cn = __builtin_amdgcn_readlane(tc, q), s0 = __builtin_amdgcn_readlane(ts, q);
                 const uint32_t d0 = __builtin_amdgcn_readlane(to, q);
-                if (uint32_t(lane) < cn) stage[d0 + lane] = v0[q];
-                if (uint32_t(lane) + kWave < cn) stage[d0 + kWave + lane] = v1[q];
-                hist_add(hist[0], uint32_t(lane) < cn, v0[q] >> top, zeros);
-                hist_add(hist[0], uint32_t(lane) + kWave < cn, v1[q] >> top, zeros);
-                for (uint32_t i0 = 2 * kWave; i0 < cn; i0 += kWave) {   // bounds uniform across the wavefront
-                    const uint32_t i = i0 + lane;
-                    const uint32_t v = i < cn ? uint32_t(sorted[s0 + i]) : 0u;
-                    if (i < cn) stage[d0 + i] = v;
-                    hist_add(hist[0], i < cn, v >> top, zeros);
+                for (uint32_t i0 = 2 * kWave; i0 < cn; i0 += kRunLoads * kWave) {
+                    uint32_t v[kRunLoads];
+#pragma unroll
+                    for (int u = 0; u < kRunLoads; ++u) {
+                        const uint32_t i = i0 + u * kWave + lane;
+                        v[u] = i < cn ? uint32_t(sorted[s0 + i]) : 0u;
+                    }
+#pragma unroll
+                    for (int u = 0; u < kRunLoads; ++u) {
+                        const uint32_t i = i0 + u * kWave + lane;
+                        if (i0 + u * kWave < cn) fn(v[u], i < cn, d0 + i);
+                    }
                 }
             }
         }
+    };
+    if (kHold && at_once) {
+        // Every score also enters the first pass's histogram (its top digit:
+        // every score lies below 256 << top) as it arrives, so that pass
+        // needs no loop of its own.
+        each_score([&](uint32_t v, bool has, uint32_t at) __attribute__((always_inline)) {
+            if (has) stage[at] = v;
+            hist_add(hist[0], has, v >> top, zeros);
+        });
         hist_flush_zeros(hist[0], zeros);
         __syncthreads();
+        // read beside the first pick rather than after it
 #pragma unroll
-        for (int g = 0; g < kKeep / 4; ++g) {
-            if (uint32_t(g) * (4 * kSelNT) >= nbk) break;
-            const uint4 v = reinterpret_cast<const uint4*>(stage)[g * kSelNT + t];
-            x[4 * g] = v.x;
-            x[4 * g + 1] = v.y;
-            x[4 * g + 2] = v.z;
-            x[4 * g + 3] = v.w;
+        for (int r = 0; r < kKeep / 4; ++r) {
+            if (uint32_t(r) * 4 * kSelNT >= nbk) break;
+            x[r] = reinterpret_cast<const uint4*>(stage)[uint32_t(r) * kSelNT + t];
         }
     }
     // Pass p builds hist[p & 1] and picks into pick[p & 1]; the other
     // histogram is cleared meanwhile for the next pass.  Two barriers a pass:
     // after the histogram (before the pick) and after the pick (before
     // everyone reads it); a buffer is reused two passes later, past both.
-    uint32_t prefix = 0;
+    uint32_t prefix = 0, matching = nbk;   // scores whose higher digits are `prefix`
     int pass = 0;
     for (int shift = top; shift >= 0; shift -= 8, ++pass) {
         const int cur = pass & 1;
         if (t < 256) hist[cur ^ 1][t] = 0;   // last read by the pick of the previous pass
-        if (!(in_regs && pass == 0)) {       // the gather built the first in-register pass
+        if (!(at_once && pass == 0)) {       // the gather built the first pass
             zeros = 0;
-            if (in_regs) {
+            if (kHold && held != 0) {
+                // four scores of the thread, the first at place i of the stage
+                auto add4 = [&](const uint4& v, uint32_t i) __attribute__((always_inline)) {
+                    const uint32_t e[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-                for (int j = 0; j < kKeep; ++j) {
-                    if (j % 4 == 0 && uint32_t(j / 4) * (4 * kSelNT) >= nbk) break;
-                    const uint32_t y = x[j] >> shift;
-                    hist_add(hist[cur], slot(j) < nbk && (y >> 8) == prefix, y & 255u, zeros);
+                    for (int u = 0; u < 4; ++u) {
+                        const uint32_t y = e[u] >> shift;
+                        hist_add(hist[cur], i + u < held && (y >> 8) == prefix, y & 255u, zeros);
+                    }
+                };
+                uint32_t i0 = 0;
+                if (at_once) {
+#pragma unroll
+                    for (int r = 0; r < kKeep / 4; ++r) {
+                        if (uint32_t(r) * 4 * kSelNT >= held) break;
+                        add4(x[r], (uint32_t(r) * kSelNT + t) * 4);
+                    }
+                    i0 = uint32_t(kSelNT) * kKeep;
                 }
-            } else {
-                for (int64_t r = w; r < chunks; r += kSelWaves) {
-                    const uint32_t cn = rcnt[r], s0 = rsrc[r];
-                    for (uint32_t i0 = 0; i0 < cn; i0 += kWave) {   // bounds uniform across the wavefront
-                        const uint32_t i = i0 + lane;
-                        const uint32_t y = i < cn ? uint32_t(sorted[s0 + i]) >> shift : 0u;
-                        hist_add(hist[cur], i < cn && (y >> 8) == prefix, y & 255u, zeros);
+                for (; i0 < held; i0 += kStageReads * 4 * kSelNT) {
+                    uint4 v[kStageReads];   // inside the stage; read before the histogram's atomics
+#pragma unroll
+                    for (int r = 0; r < kStageReads; ++r)
+                        v[r] = reinterpret_cast<const uint4*>(stage)[i0 / 4 + uint32_t(r) * kSelNT + t];
+#pragma unroll
+                    for (int r = 0; r < kStageReads; ++r) {
+                        if (i0 + uint32_t(r) * 4 * kSelNT >= held) break;   // uniform
+                        add4(v[r], i0 + (uint32_t(r) * kSelNT + t) * 4);
                     }
                 }
+            } else {
+                const bool gather = kHold && pass > 0 && matching <= kStageScores;
+                each_score([&](uint32_t v, bool has, uint32_t) __attribute__((always_inline)) {
+                    const uint32_t y = v >> shift;
+                    const bool take = has && (y >> 8) == prefix;
+                    hist_add(hist[cur], take, y & 255u, zeros);
+                    const uint64_t m = __ballot(take);
+                    if (gather && m != 0) {
+                        uint32_t at = 0;
+                        if (lane == 0) at = atomicAdd(&appended, uint32_t(__popcll(m)));
+                        at = __builtin_amdgcn_readfirstlane(at) + uint32_t(__popcll(m & ((1ull << lane) - 1ull)));
+                        if (take) stage[at] = v;   // at < matching <= kStageScores
+                    }
+                });
+                if (gather) held = matching;   // read past the barriers below
             }
             hist_flush_zeros(hist[cur], zeros);
             __syncthreads();
@@ -612,6 +696,7 @@ __device__ int32_t select_bucket(const SelectArgs& A, int b) {
         __syncthreads();
         prefix = (prefix << 8) | pick[cur][0];
         k = int32_t(pick[cur][1]);
+        matching = pick[cur][2];
     }
     if (t == 0) q_out[b] = int32_t(prefix);
     publish_q(A.qflag, b, int32_t(prefix));
@@ -619,7 +704,10 @@ __device__ int32_t select_bucket(const SelectArgs& A, int b) {
 }
 
 // The selection alone: one workgroup per bucket.
-__global__ __launch_bounds__(kSelNT) void cal_bucket_select(SelectArgs A) { (void)select_bucket(A, int(blockIdx.x)); }
+__global__ __launch_bounds__(kSelNT) void cal_bucket_select(SelectArgs A) {
+    __shared__ SelectLds lds;
+    (void)select_bucket<true>(A, int(blockIdx.x), lds);
+}
 
 struct ApplyArgs {
     const int32_t* edges;
@@ -645,7 +733,7 @@ static_assert(kFastBuckets <= kSelNT, "one waiting thread per bucket");
 // selected by this workgroup itself from the same sorted runs -- the same
 // deterministic computation, so the same value -- so the launch completes
 // and is exact whether or not its workgroups run at the same time.
-__device__ void apply_after_select(const SelectArgs& S, const ApplyArgs& A, int j, int ga) {
+__device__ void apply_after_select(const SelectArgs& S, const ApplyArgs& A, int j, int ga, SelectLds& lds) {
     extern __shared__ __align__(16) uint32_t stage[];
     __shared__ uint32_t missing[kFastBuckets / 32];   // buckets whose quantile did not arrive
     const int nb = S.nb, ne = nb - 1;
@@ -704,7 +792,7 @@ __device__ void apply_after_select(const SelectArgs& S, const ApplyArgs& A, int 
     if (any) {   // uniform: every thread read the same bitmap
         for (int b = 0; b < nb; ++b) {
             if (!((missing[b / 32] >> (b % 32)) & 1u)) continue;
-            const int32_t qb = select_bucket(S, b);   // overwrites `stage`: edges reloaded below
+            const int32_t qb = select_bucket<false>(S, b, lds);   // overwrites `stage`: edges reloaded below
             if (t == b) q_own = qb;
         }
         __syncthreads();
@@ -727,8 +815,9 @@ __device__ void apply_after_select(const SelectArgs& S, const ApplyArgs& A, int 
 // missing ones themselves after a bounded wait (no workgroup waits without
 // bound on another).
 __global__ __launch_bounds__(kSelNT) void cal_select_apply(SelectArgs S, ApplyArgs A) {
-    if (int(blockIdx.x) < S.nb) select_bucket(S, int(blockIdx.x));
-    else apply_after_select(S, A, int(blockIdx.x) - S.nb, int(gridDim.x) - S.nb);
+    __shared__ SelectLds lds;
+    if (int(blockIdx.x) < S.nb) (void)select_bucket<true>(S, int(blockIdx.x), lds);
+    else apply_after_select(S, A, int(blockIdx.x) - S.nb, int(gridDim.x) - S.nb, lds);
 }
 
 int grid_for(int64_t n, int nt, int per_thread, int cap) {

@@ -56,6 +56,11 @@ CAL_CASES = {
     "sorted_pred_long_runs": dict(n=30000, nb=4, alpha=100000, sort=True),
     "ragged_last_chunk": dict(n=4097, nb=3, alpha=100000),
     "chunks_at_limit": dict(n=1024 * 4096, nb=128, alpha=100000),
+    # a bucket holds 36,864 scores in LDS; of a larger one the scores that match the digits found so far
+    "bucket_fills_lds": dict(n=36864, nb=1, alpha=100000),
+    "bucket_one_past_lds": dict(n=36865, nb=1, alpha=100000),
+    "single_bucket_many_runs": dict(n=700001, nb=1, alpha=50000, wide=True),
+    "large_buckets_of_ties": dict(n=250000, nb=2, alpha=100000, tie=True),
     "one_past_chunk_limit": dict(n=1024 * 4096 + 1, nb=16, alpha=50000),
 }
 
