@@ -341,8 +341,14 @@ maps_status maps_place(const void* snapshot, int32_t D, int32_t u_max,
  * With A = 1 the outputs equal maps_place's.
  * workspace: maps_place_commit_workspace_size(D, u_max) bytes (three dense
  * int64 arrays over the step axis and one int64 per 1,024 steps per decoder:
- * about 24 (u_max + 1) bytes per decoder), caller-owned, not shared by calls
- * in flight.  The chain is serial: one workgroup takes the arrivals in order.
+ * about 24 (u_max + 1) bytes per decoder, and about 37 KB for the exchange of
+ * the rounds), caller-owned, not shared by calls in flight.
+ * Policy MQ with 3 to 1,024 decoders and 8 or more arrivals runs in rounds
+ * while they pay: a workgroup per compute unit commits the arrivals that go to
+ * different decoders at the same time.  Otherwise, and from where the rounds
+ * end, one workgroup takes the arrivals in order.  The rounds' workgroups wait
+ * for each other a bounded time; a wait that expires ends the rounds and the
+ * single workgroup goes on, with the same results.
  * dev_err bits: NEG_LEN (a_prompt of an arrival with a bound, capacity or
  * queue_len < 0), BOUND_RANGE (a_upper > u_max: evaluated at u_max),
  * SNAPSHOT.

@@ -387,7 +387,24 @@ inline size_t kernel_static_lds(Kernel* fn) {
     return kernel_static_lds(reinterpret_cast<const void*>(fn));
 }
 
+// How long the rounds of sequential commit wait: for all owners to check in
+// (ticks of the 100 MHz clock), and polls of an owner for that decision, of an
+// owner for a round, and of the master for the owners.
+struct CommitWaits {
+    uint32_t check_in, entry_polls, owner_polls, master_polls;
+};
+
 }  // namespace maps
+
+// maps_place_commit with its waits given: the same outputs for any of them.
+extern "C" maps_status maps_internal_place_commit(const void* snapshot, int32_t D, int32_t u_max,
+                                                  const int32_t* capacity, const int32_t* queue_len,
+                                                  const int32_t* a_prompt, const int32_t* a_upper, int64_t A,
+                                                  int32_t policy, int64_t rr_offset, int32_t* choice,
+                                                  int64_t* chosen_peak, int64_t* chosen_overflow, uint8_t* flags,
+                                                  int32_t* queue_out, uint32_t* dev_err, void* workspace,
+                                                  size_t workspace_bytes, hipStream_t stream,
+                                                  maps::CommitWaits waits);
 
 // Host-side launch check: returns MAPS_E_HIP from the enclosing function when
 // the last launch failed.

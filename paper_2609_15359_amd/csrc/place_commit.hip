@@ -59,12 +59,18 @@ constexpr int kWindow = 128;        // arrivals evaluated ahead in a round
 constexpr int kMaskWords = kWindow / 64;
 constexpr int kRoundDecoders = 1024;
 constexpr int kMaxOwners = 1024;
+constexpr uint32_t kRun = 1u << 30, kDeclined = 1u << 31, kOwnerCount = kRun - 1u;   // of `entry`
+// `round`, one word: the last round published above the arrivals it placed and
+// whether another follows; kEnded: none does, whatever that says.
+constexpr uint64_t kEnded = 1ull << 63;
+constexpr uint32_t kMore = 1u << 31;
+__host__ __device__ inline uint64_t round_word(uint32_t r, uint32_t placed, bool more) {
+    return (uint64_t(r) << 32) | placed | (more ? kMore : 0u);
+}
 struct RoundControl {
-    uint32_t checked;      // owners that run
-    uint32_t decision;     // 0 open, 1 the rounds run, 2 they do not
-    uint32_t round;        // the last round published
-    uint32_t more;         // of that round: whether another follows
-    int64_t next;          // the first arrival after it; after the last one, the serial chain's first
+    uint64_t round;
+    uint32_t entry;        // owners that have checked in, and whether the rounds run
+    int64_t resume;        // the serial chain's first arrival
     uint32_t ready[kMaxOwners];                      // the round each owner has evaluated
     int32_t assign[kRoundDecoders];                  // the window's arrival committed to each decoder, or -1
     uint64_t feasible[kRoundDecoders][kMaskWords];   // the window's arrivals that each decoder holds
@@ -115,6 +121,7 @@ struct CommitArgs {
     uint32_t* dev_err;
     RoundControl* ctl;
     int32_t owners;      // workgroups of commit_rounds that own decoders
+    CommitWaits waits;
 };
 
 __device__ inline int64_t max64(int64_t a, int64_t b) { return a > b ? a : b; }
@@ -133,8 +140,9 @@ __global__ __launch_bounds__(kCommitNT) void commit_init(CommitArgs a) {
     for (int32_t i = threadIdx.x; i < a.NB; i += kCommitNT) F[i] = 0;
     if (d == 0 && a.owners > 0) {   // the exchange of the rounds starts open
         if (threadIdx.x == 0) {
-            a.ctl->checked = a.ctl->decision = a.ctl->round = a.ctl->more = 0;
-            a.ctl->next = 0;
+            a.ctl->round = 0;
+            a.ctl->entry = 0;
+            a.ctl->resume = 0;
         }
         for (int32_t i = threadIdx.x; i < kMaxOwners; i += kCommitNT) a.ctl->ready[i] = 0;
     }
@@ -574,10 +582,10 @@ __global__ __launch_bounds__(kSerialNT) void commit_serial(CommitArgs a) {
         Q[d] = a.qlen[d];
         C[d] = a.cap[d];
         neg |= Q[d] < 0 || C[d] < 0;
-        if (a.owners > 0 && a.ctl->next > 0) Q[d] = a.ctl->queue[d];
+        if (a.owners > 0 && a.ctl->resume > 0) Q[d] = a.ctl->queue[d];
     }
     if (neg) raise_error(a.dev_err, MAPS_ERR_NEG_LEN);
-    serial_chain<kPre>(a, a.owners > 0 ? a.ctl->next : 0, Q, C, lds + 2 * D, w);
+    serial_chain<kPre>(a, a.owners > 0 ? a.ctl->resume : 0, Q, C, lds + 2 * D, w);
 }
 
 // ---------------------------------------------------------------------------
@@ -605,15 +613,25 @@ __global__ __launch_bounds__(kSerialNT) void commit_serial(CommitArgs a) {
 //
 // The master starts the rounds only when every owner has checked in, so that
 // all of them run; when that takes longer than kCheckIn (workgroups of other
-// kernels hold the compute units) the owners are sent home, so no wait depends
-// on a workgroup that is not running.  The rounds also end when they hold too
-// few arrivals to pay (no decoder is feasible any more, and commits do not make
-// any feasible again).  The serial chain's launch takes up what is left.
+// kernels hold the compute units) the owners are sent home.  The rounds also
+// end when they hold too few arrivals to pay (no decoder is feasible any more,
+// and commits do not make any feasible again).  The serial chain's launch takes
+// up what is left.
+//
+// Every wait is bounded, and one that expires costs time but no arrival: two
+// words change by compare-and-swap only, so that everyone agrees on what they
+// hold.  `entry` goes to kRun or to kDeclined once: an owner that stops waiting
+// for the master declines the rounds for all, or finds that they run and joins
+// them.  `round` is that of the next round, or gets kEnded once: an owner that stops waiting
+// for a round, and a master that stops waiting for an owner, end the rounds
+// after the last one published, whose commits every owner still makes (the
+// exchange of a round is written only when all have read the one before).  The
+// serial chain goes on after that round.
 // 4,096 arrivals on 256 decoders (queues of 0..63, bounds of 3,600 steps on
 // average, 32,768 at most), nearly all feasible: 49 ms in the serial chain
 // before, 4.1 ms with the rounds and the commits by rows.
 constexpr int kReviewRounds = 8;             // rounds after which the master looks at what they held
-constexpr uint64_t kCheckIn = 20000;         // 200 us at the 100 MHz of the constant clock
+constexpr uint32_t kCheckIn = 20000;         // 200 us at the 100 MHz of the constant clock
 constexpr uint32_t kMostPolls = 1u << 22;    // an owner or the master that is not heard of for seconds
 
 template <typename T>
@@ -624,32 +642,59 @@ template <typename T>
 __device__ inline void co_store(T* p, T v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// *p goes from `from` to `to`; returns what it held before.
+template <typename T>
+__device__ inline T co_swap(T* p, T from, T to) {
+    __hip_atomic_compare_exchange_strong(p, &from, to, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return from;
+}
 // Every store of this wavefront has reached memory, and none of its later
 // accesses is issued before.
 __device__ inline void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// What the master published last, in every thread of an owner.
+// What an owner's first thread learned, for the others.
 struct Published {
-    uint32_t more;
-    int64_t next;
+    bool go;          // the rounds run
+    uint64_t round;   // the round's word, or the last one before it
 };
+
+// The check-in of an owner (one thread): whether the rounds run.
+__device__ inline bool owner_enters(const CommitArgs& a) {
+    uint32_t e = __hip_atomic_fetch_add(&a.ctl->entry, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (uint32_t i = 0; i < a.waits.entry_polls && (e & (kRun | kDeclined)) == 0; ++i) {
+        __builtin_amdgcn_s_sleep(4);
+        e = co_load(&a.ctl->entry);
+    }
+    // not decided for seconds: decline (a swap fails only when another owner
+    // checks in or the word is decided)
+    while ((e & (kRun | kDeclined)) == 0) {
+        const uint32_t held = co_swap(&a.ctl->entry, e, e | kDeclined);
+        e = held == e ? e | kDeclined : held;
+    }
+    return (e & kRun) != 0;
+}
+
+// Waits for the round after the word `last` (one thread of an owner): its word,
+// or `last` where the rounds have ended before it.
+__device__ inline uint64_t owner_waits(const CommitArgs& a, uint64_t last) {
+    uint64_t seen = co_load(&a.ctl->round);
+    for (uint32_t i = 0; i < a.waits.owner_polls && seen == last; ++i) {
+        __builtin_amdgcn_s_sleep(2);
+        seen = co_load(&a.ctl->round);
+    }
+    if (seen == last) seen = co_swap(&a.ctl->round, last, last | kEnded);   // not heard of for seconds: end there
+    return seen & ~kEnded;
+}
 
 __device__ inline void owner_rounds(const CommitArgs& a, int32_t* ostage, ChainLds& w, Published& pub) {
     const int tid = threadIdx.x, lane = tid % kWave;
     const int32_t D = a.S.D, T = a.L - 1, P = a.owners;
     const int32_t own = int32_t(blockIdx.x) - 1;   // decoders own, own + P, ...
-    if (tid == 0) {
-        __hip_atomic_fetch_add(&a.ctl->checked, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        uint32_t decision = 0;
-        for (uint32_t i = 0; i < kMostPolls && decision == 0; ++i) {
-            decision = co_load(&a.ctl->decision);
-            if (decision == 0) __builtin_amdgcn_s_sleep(4);
-        }
-        pub.more = decision;
-    }
+    if (tid == 0) pub.go = owner_enters(a);
     __syncthreads();
-    if (pub.more != 1u) return;   // the rounds do not run
+    if (!pub.go) return;   // the rounds do not run
     int64_t pos = 0;
+    uint64_t last = 0;
     for (uint32_t round = 1;; ++round) {
         // the window against this owner's decoders: kSerialNT / kWindow of them at a time
         constexpr int kTogether = kSerialNT / kWindow;
@@ -680,19 +725,12 @@ __device__ inline void owner_rounds(const CommitArgs& a, int32_t* ostage, ChainL
         __syncthreads();
         if (tid == 0) {
             co_store(&a.ctl->ready[own], round);
-            uint32_t seen = 0;
-            for (uint32_t n = 0; n < kMostPolls && seen < round; ++n) {
-                seen = co_load(&a.ctl->round);
-                if (seen < round) __builtin_amdgcn_s_sleep(2);
-            }
+            pub.round = owner_waits(a, last);
             asm volatile("" ::: "memory");
-            pub.more = seen < round ? 0u : co_load(&a.ctl->more);
-            pub.next = co_load(&a.ctl->next);
-            if (seen < round) raise_error(a.dev_err, MAPS_ERR_WAIT_TIMEOUT);
         }
         __syncthreads();
-        const uint32_t more = pub.more;
-        const int64_t next = pub.next;
+        if (pub.round == last) return;   // the rounds have ended before this one
+        last = pub.round;
         for (int32_t d = own; d < D; d += P) {
             const int32_t at = __builtin_amdgcn_readfirstlane(co_load(&a.ctl->assign[d]));
             if (at < 0 || at >= kWindow || pos + at >= a.A) continue;
@@ -717,8 +755,8 @@ __device__ inline void owner_rounds(const CommitArgs& a, int32_t* ostage, ChainL
             PeakIn unused{0, 0, 0};
             commit_any(a, ostage, peak, d, p, Uc, -1, -1, &unused, w);   // ends with a barrier
         }
-        if (more == 0u) return;
-        pos = next;
+        if ((uint32_t(last) & kMore) == 0u) return;
+        pos += uint32_t(last) & ~kMore;
     }
 }
 
@@ -738,31 +776,67 @@ __device__ inline void master_rounds(const CommitArgs& a) {
         K[s] = d < D ? (uint32_t(q) << 10) | uint32_t(d) : ~0u;
     }
     bool run = __builtin_amdgcn_ballot_w64(wide) == 0;
-    if (run) {
-        const uint64_t t0 = wall_clock64();
-        while (co_load(&a.ctl->checked) != uint32_t(P) && wall_clock64() - t0 < kCheckIn) __builtin_amdgcn_s_sleep(4);
-        run = __builtin_amdgcn_readfirstlane(co_load(&a.ctl->checked)) == P;
+    uint32_t e = 0;
+    if (lane == 0) {
+        e = co_load(&a.ctl->entry);
+        if (run) {
+            const uint64_t t0 = wall_clock64();
+            while (e < uint32_t(P) && wall_clock64() - t0 < a.waits.check_in) {   // kDeclined is above every count
+                __builtin_amdgcn_s_sleep(4);
+                e = co_load(&a.ctl->entry);
+            }
+        }
+        while ((e & (kRun | kDeclined)) == 0) {
+            const uint32_t to = e | (run && e == uint32_t(P) ? kRun : kDeclined);
+            const uint32_t held = co_swap(&a.ctl->entry, e, to);
+            e = held == e ? to : held;
+        }
     }
-    if (lane == 0) co_store(&a.ctl->decision, run ? 1u : 2u);
-    if (!run) return;   // ctl->next stays 0
+    run = (__builtin_amdgcn_readfirstlane(e) & kRun) != 0;
+    if (!run) return;   // ctl->resume stays 0
 
-    int64_t pos = 0;
+    int64_t pos = 0, pos0 = 0;   // the first arrival after the rounds so far, and before the last of them
+    uint32_t K0[kSlots];         // the queues before the last round
+    uint64_t word = 0, word0 = 0, swapped = 0;   // the last round's, the one before, and what its publication found
+#pragma unroll
+    for (int s = 0; s < kSlots; ++s) K0[s] = K[s];
+    // an owner has ended the rounds before the last one, which is void then
+    auto void_last = [&]() {
+        if (__builtin_amdgcn_ballot_w64(lane == 0 && swapped != word0) == 0) return false;
+#pragma unroll
+        for (int s = 0; s < kSlots; ++s) K[s] = K0[s];
+        pos = pos0;
+        return true;
+    };
     int held = 0;   // arrivals placed since the last review
     bool few = false;
     for (uint32_t round = 1;; ++round) {
         // every owner has evaluated the window
         bool late = false;
-        for (int32_t o = lane; o - lane < P; o += kWave) {
+        uint32_t heard = co_load(&a.ctl->ready[lane < P ? lane : 0]);
+        // looked at with a load in flight behind it: waiting for the swap at
+        // once took 0.7 us a round
+        if (round > 1 && void_last()) break;
+        for (int32_t o = lane; o - lane < P && !late; o += kWave) {
+            if (o != lane) heard = co_load(&a.ctl->ready[o < P ? o : 0]);
             uint32_t n = 0;
-            while (__builtin_amdgcn_ballot_w64(o < P && co_load(&a.ctl->ready[o < P ? o : 0]) < round) != 0)
-                if (++n > kMostPolls) { late = true; break; }
+            while (__builtin_amdgcn_ballot_w64(o < P && heard < round) != 0) {
+                if (++n > a.waits.master_polls) { late = true; break; }
+                heard = co_load(&a.ctl->ready[o < P ? o : 0]);
+            }
+        }
+        if (late) {   // end after the round before; an owner may have done so already
+            if (lane == 0) (void)co_swap(&a.ctl->round, word, word | kEnded);
+            break;
         }
         asm volatile("" ::: "memory");
         uint32_t bits[kSlots][2 * kMaskWords];
         uint64_t taken[kSlots];
         int32_t mine[kSlots];   // the arrival assigned to this lane's decoder
+        pos0 = pos;
 #pragma unroll
         for (int s = 0; s < kSlots; ++s) {
+            K0[s] = K[s];
             const int32_t d = lane + s * kWave;
 #pragma unroll
             for (int h = 0; h < kMaskWords; ++h) {
@@ -778,7 +852,7 @@ __device__ inline void master_rounds(const CommitArgs& a) {
         const uint64_t none[2] = {__builtin_amdgcn_ballot_w64(U0 < 0), __builtin_amdgcn_ballot_w64(U1 < 0)};
         const int cnt = a.A - pos < kWindow ? int(a.A - pos) : kWindow;
         int done = 0;
-        bool first = true, stop = late;
+        bool first = true, stop = false;
         if (round == 1) {
             // fewer than half of the window's arrivals find a decoder: the chain is better off from the start
             int held_by_any = 0;
@@ -855,28 +929,26 @@ __device__ inline void master_rounds(const CommitArgs& a) {
                 done = j + 1;
             }
         }
-        pos += done;
         held += done;
-        uint32_t more = pos < a.A && !late && !few ? 1u : 0u;
-        if (more != 0u && round % kReviewRounds == 0) {
-            if (held < kReviewRounds + kReviewRounds / 2) more = 0u;
+        bool more = pos + done < a.A && !few;
+        if (more && round % kReviewRounds == 0) {
+            more = held >= kReviewRounds + kReviewRounds / 2;
             held = 0;
-        }
-        if (late) {   // unreachable while every owner runs
-            if (lane == 0) raise_error(a.dev_err, MAPS_ERR_WAIT_TIMEOUT);
-            pos = a.A;
         }
 #pragma unroll
         for (int s = 0; s < kSlots; ++s)
             if (lane + s * kWave < D) co_store(&a.ctl->assign[lane + s * kWave], mine[s]);
-        if (lane == 0) {
-            co_store(&a.ctl->more, more);
-            co_store(&a.ctl->next, pos);
-        }
         stores_done();
-        if (lane == 0) co_store(&a.ctl->round, round);
-        if (more == 0u) break;
+        word0 = word;
+        word = round_word(round, uint32_t(done), more);
+        if (lane == 0) swapped = co_swap(&a.ctl->round, word0, word);
+        pos += done;
+        if (!more) {
+            (void)void_last();
+            break;
+        }
     }
+    if (lane == 0) a.ctl->resume = pos;
 #pragma unroll
     for (int s = 0; s < kSlots; ++s)
         if (lane + s * kWave < D) a.ctl->queue[lane + s * kWave] = int32_t(K[s] >> 10);
@@ -901,12 +973,13 @@ extern "C" size_t maps_place_commit_workspace_size(int32_t D, int32_t u_max) {
     return commit_layout(D, u_max).bytes;
 }
 
-extern "C" maps_status maps_place_commit(const void* snapshot, int32_t D, int32_t u_max, const int32_t* capacity,
-                                         const int32_t* queue_len, const int32_t* a_prompt, const int32_t* a_upper,
-                                         int64_t A, int32_t policy, int64_t rr_offset, int32_t* choice,
-                                         int64_t* chosen_peak, int64_t* chosen_overflow, uint8_t* flags,
-                                         int32_t* queue_out, uint32_t* dev_err, void* workspace,
-                                         size_t workspace_bytes, hipStream_t stream) {
+extern "C" maps_status maps_internal_place_commit(const void* snapshot, int32_t D, int32_t u_max,
+                                                  const int32_t* capacity, const int32_t* queue_len,
+                                                  const int32_t* a_prompt, const int32_t* a_upper, int64_t A,
+                                                  int32_t policy, int64_t rr_offset, int32_t* choice,
+                                                  int64_t* chosen_peak, int64_t* chosen_overflow, uint8_t* flags,
+                                                  int32_t* queue_out, uint32_t* dev_err, void* workspace,
+                                                  size_t workspace_bytes, hipStream_t stream, CommitWaits waits) {
     if (D < 1 || D > MAPS_MAX_COMMIT_DECODERS || A < 0 || rr_offset < 0 || u_max < 0 ||
         u_max > MAPS_MAX_COMMIT_U_MAX)
         return MAPS_E_SIZE;
@@ -940,6 +1013,7 @@ extern "C" maps_status maps_place_commit(const void* snapshot, int32_t D, int32_
     a.queue_out = queue_out;
     a.dev_err = dev_err;
     a.ctl = reinterpret_cast<RoundControl*>(w + c.off_ctl);
+    a.waits = waits;
     // Rounds where arrivals can find different feasible decoders, from 8
     // arrivals on (starting the owners costs about one serial arrival); the
     // master and the owners fill a compute unit each.
@@ -970,4 +1044,15 @@ extern "C" maps_status maps_place_commit(const void* snapshot, int32_t D, int32_
     hipLaunchKernelGGL(serial, dim3(1), dim3(kSerialNT), lds, stream, a);
     MAPS_CHECK_LAUNCH();
     return MAPS_OK;
+}
+
+extern "C" maps_status maps_place_commit(const void* snapshot, int32_t D, int32_t u_max, const int32_t* capacity,
+                                         const int32_t* queue_len, const int32_t* a_prompt, const int32_t* a_upper,
+                                         int64_t A, int32_t policy, int64_t rr_offset, int32_t* choice,
+                                         int64_t* chosen_peak, int64_t* chosen_overflow, uint8_t* flags,
+                                         int32_t* queue_out, uint32_t* dev_err, void* workspace,
+                                         size_t workspace_bytes, hipStream_t stream) {
+    return maps_internal_place_commit(snapshot, D, u_max, capacity, queue_len, a_prompt, a_upper, A, policy, rr_offset,
+                                      choice, chosen_peak, chosen_overflow, flags, queue_out, dev_err, workspace,
+                                      workspace_bytes, stream, CommitWaits{kCheckIn, kMostPolls, kMostPolls, kMostPolls});
 }

@@ -4,6 +4,8 @@ decoder's projected occupancy and queue before the next (Sec. 3.3, Algorithm
 1).  Random ragged decoders and arrival mixes, both policies, round-robin
 arrivals, capacity ties, the seeded workloads (literal and with room), the
 single-arrival case against maps_place, and the device error bits."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -24,16 +26,54 @@ def _cuda(x, dtype=np.int32):
     return torch.from_numpy(np.ascontiguousarray(x, dtype=dtype)).cuda()
 
 
-def _gpu(seg, p, g, U, u_max, cap, Q, a_p, a_U, policy=0, rr=0):
+class Waits(ctypes.Structure):
+    """Of the rounds: ticks of the 100 MHz clock for all owners to check in, and polls of an owner for
+    that decision, of an owner for a round and of the master for the owners."""
+    _fields_ = [(n, ctypes.c_uint32) for n in ("check_in", "entry_polls", "owner_polls", "master_polls")]
+
+
+MOST = 1 << 22
+PATIENT = (10**8, MOST, MOST, MOST)   # a second for the check-in, whatever else the card is busy with
+RUN, DECLINED = 1 << 30, 1 << 31      # of the entry word
+
+
+def _exchange(ws, D, u_max):
+    """The entry word and the first arrival that the rounds left to the serial chain, from the exchange
+    behind the curves (three of u_max + 1 int64 a decoder) and the floors (one int64 per 1,024 steps)."""
+    a = lambda x: (x + 255) // 256 * 256  # noqa: E731
+    at = 3 * a(8 * D * (u_max + 1)) + a(8 * D * (u_max // 1024 + 1))
+    words = ws[at:at + 24].cpu().numpy()
+    return int(words[8:12].view(np.uint32)[0]), int(words[16:].view(np.int64)[0])
+
+
+def _gpu(seg, p, g, U, u_max, cap, Q, a_p, a_U, policy=0, rr=0, waits=None):
+    """maps_place_commit's outputs, and the exchange of its rounds; waits: through the internal entry."""
     import torch
 
     import paper_2609_15359_amd as maps
+    D, A = len(cap), len(a_p)
     snap, _, err = maps.project(_cuda(seg, np.int64), _cuda(p), _cuda(g), _cuda(U), u_max)
-    out = maps.place_commit(snap, _cuda(cap), _cuda(Q), _cuda(a_p), _cuda(a_U), policy, rr, dev_err=err)
+    ws = torch.zeros(maps.place_commit_workspace_bytes(D, u_max), dtype=torch.uint8, device="cuda")
+    args = _cuda(cap), _cuda(Q), _cuda(a_p), _cuda(a_U)
+    if waits is None:
+        out = maps.place_commit(snap, *args, policy, rr, dev_err=err, workspace=ws)
+    else:
+        new = lambda n, t: torch.empty(n, dtype=t, device="cuda")  # noqa: E731
+        out = maps.CommitPlacement(choice=new(A, torch.int32), chosen_peak=new(A, torch.int64),
+                                   chosen_overflow=new(A, torch.int64), flags=new(A, torch.uint8),
+                                   queue_out=new(D, torch.int32), dev_err=err)
+        fn = maps.library().maps_internal_place_commit
+        fn.restype, fn.argtypes = ctypes.c_int32, maps.library().maps_place_commit.argtypes + [Waits]
+        ptr = lambda t: ctypes.c_void_p(t.data_ptr())  # noqa: E731
+        st = fn(ptr(snap.data), D, u_max, *(ptr(t) for t in args), A, policy, rr, ptr(out.choice),
+                ptr(out.chosen_peak), ptr(out.chosen_overflow), ptr(out.flags), ptr(out.queue_out), ptr(err),
+                ptr(ws), ws.numel(), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream), Waits(*waits))
+        assert st == 0
     torch.cuda.synchronize()
+    entry, resume = _exchange(ws, D, u_max)
     return dict(choice=out.choice.cpu().numpy(), chosen_peak=out.chosen_peak.cpu().numpy(),
                 chosen_overflow=out.chosen_overflow.cpu().numpy(), flags=out.flags.cpu().numpy(),
-                queue_out=out.queue_out.cpu().numpy(), err=int(err.item()) & 0xFFFFFFFF)
+                queue_out=out.queue_out.cpu().numpy(), err=int(err.item()) & 0xFFFFFFFF, entry=entry, resume=resume)
 
 
 def _compare(g, r, q_after, tag):
@@ -101,6 +141,28 @@ def test_rounds(orc, D, A, u_max, room):
     say(f"[commit] rounds D={D} A={A} {room}: feasible {np.mean(r.flags & 1):.3f}")
     got = _gpu(seg, p, g, U, u_max, cap, Q, a_p, a_U, 0, rr)
     _compare(got, r, q_after, f"rounds D={D} A={A} {room}")
+
+
+@pytest.mark.parametrize("waits", [(0, MOST, MOST, MOST), (10**8, 0, MOST, MOST), (10**8, MOST, 0, MOST),
+                                   (10**8, MOST, 2, MOST), (10**8, MOST, 20, MOST), (10**8, MOST, 100, MOST),
+                                   (10**8, MOST, MOST, 0), (10**8, MOST, MOST, 3), (10**8, MOST, MOST, 20),
+                                   (10**8, MOST, MOST, 100), (10**8, MOST, 15, 15), (0, 0, 0, 0)])
+def test_waits_that_expire(orc, waits):
+    """Owners and a master that stop waiting, before the rounds and anywhere in them: every arrival is placed
+    and no error raised, whoever gave up first."""
+    for D, A, u_max in ((3, 300, 300), (65, 700, 9000), (300, 900, 2000)):
+        rng = np.random.default_rng(D + A)
+        seg, p, g, U, a_p, a_U = _random_case(rng, D, 12, A, u_max)
+        base = orc.project(seg, p, g, U)
+        demand = int((a_p + np.maximum(a_U, 0)).mean()) * max(1, A // D)
+        cap = (base + rng.integers(0, 4 * demand + 1, size=D)).astype(np.int32)
+        Q = rng.integers(0, 7, size=D)
+        r, q_after = orc.place_commit(seg, p, g, U, cap, Q, a_p, a_U, policy=0, rr_offset=5)
+        say(f"[commit] waits {waits} D={D} A={A}")
+        got = _gpu(seg, p, g, U, u_max, cap, Q, a_p, a_U, 0, 5, waits=waits)
+        _compare(got, r, q_after, f"waits {waits} D={D} A={A}")
+        say(f"[commit] waits {waits} D={D} A={A}: the serial chain took up at {got['resume']}")
+        assert 0 <= got["resume"] <= A and bool(got["entry"] & RUN) != bool(got["entry"] & DECLINED)
 
 
 def test_ties_and_empty_decoders(orc):
