@@ -38,12 +38,13 @@ RUN, DECLINED = 1 << 30, 1 << 31      # of the entry word
 
 
 def _exchange(ws, D, u_max):
-    """The entry word and the first arrival that the rounds left to the serial chain, from the exchange
-    behind the curves (three of u_max + 1 int64 a decoder) and the floors (one int64 per 1,024 steps)."""
+    """The entry word, the owners of the rounds and the first arrival left to the serial chain, from the
+    exchange behind the curves (three of u_max + 1 int64 a decoder) and the floors (one int64 per 1,024 steps)."""
     a = lambda x: (x + 255) // 256 * 256  # noqa: E731
     at = 3 * a(8 * D * (u_max + 1)) + a(8 * D * (u_max // 1024 + 1))
     words = ws[at:at + 24].cpu().numpy()
-    return int(words[8:12].view(np.uint32)[0]), int(words[16:].view(np.int64)[0])
+    entry, owners = words[8:16].view(np.uint32)
+    return int(entry), int(owners), int(words[16:].view(np.int64)[0])
 
 
 def _gpu(seg, p, g, U, u_max, cap, Q, a_p, a_U, policy=0, rr=0, waits=None):
@@ -70,10 +71,11 @@ def _gpu(seg, p, g, U, u_max, cap, Q, a_p, a_U, policy=0, rr=0, waits=None):
                 ptr(ws), ws.numel(), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream), Waits(*waits))
         assert st == 0
     torch.cuda.synchronize()
-    entry, resume = _exchange(ws, D, u_max)
+    entry, owners, resume = _exchange(ws, D, u_max)
     return dict(choice=out.choice.cpu().numpy(), chosen_peak=out.chosen_peak.cpu().numpy(),
                 chosen_overflow=out.chosen_overflow.cpu().numpy(), flags=out.flags.cpu().numpy(),
-                queue_out=out.queue_out.cpu().numpy(), err=int(err.item()) & 0xFFFFFFFF, entry=entry, resume=resume)
+                queue_out=out.queue_out.cpu().numpy(), err=int(err.item()) & 0xFFFFFFFF, entry=entry, owners=owners,
+                resume=resume)
 
 
 def _compare(g, r, q_after, tag):
@@ -139,8 +141,9 @@ def test_rounds(orc, D, A, u_max, room):
     rr = int(rng.integers(0, 2**40))
     r, q_after = orc.place_commit(seg, p, g, U, cap, Q, a_p, a_U, policy=0, rr_offset=rr)
     say(f"[commit] rounds D={D} A={A} {room}: feasible {np.mean(r.flags & 1):.3f}")
-    got = _gpu(seg, p, g, U, u_max, cap, Q, a_p, a_U, 0, rr)
+    got = _gpu(seg, p, g, U, u_max, cap, Q, a_p, a_U, 0, rr, waits=PATIENT)
     _compare(got, r, q_after, f"rounds D={D} A={A} {room}")
+    say(f"[commit] rounds D={D} A={A} {room}: entry {got['entry']:#x}, {got['owners']} owners, serial from {got['resume']}")
 
 
 @pytest.mark.parametrize("waits", [(0, MOST, MOST, MOST), (10**8, 0, MOST, MOST), (10**8, MOST, 0, MOST),
@@ -163,6 +166,37 @@ def test_waits_that_expire(orc, waits):
         _compare(got, r, q_after, f"waits {waits} D={D} A={A}")
         say(f"[commit] waits {waits} D={D} A={A}: the serial chain took up at {got['resume']}")
         assert 0 <= got["resume"] <= A and bool(got["entry"] & RUN) != bool(got["entry"] & DECLINED)
+
+
+def test_rounds_without_a_compute_unit(orc):
+    """A kernel of another stream holds a compute unit for longer than the owners have to check in: the rounds
+    run with the others.  One simulation of 8 decoders takes 96 KB of its compute unit's LDS for some
+    20 ms, so that an owner, which takes all of it, finds no place there."""
+    import torch
+
+    import paper_2609_15359_amd as maps
+    D, A, u_max = 300, 900, 2000
+    rng = np.random.default_rng(1)
+    seg, p, g, U, a_p, a_U = _random_case(rng, D, 12, A, u_max)
+    cap = (orc.project(seg, p, g, U) + 40000).astype(np.int32)
+    Q = rng.integers(0, 7, size=D)
+    r, q_after = orc.place_commit(seg, p, g, U, cap, Q, a_p, a_U, policy=0, rr_offset=5)
+    n = 8000
+    requests = [_cuda(rng.integers(lo, hi, size=n)) for lo, hi in ((1, 2000), (1, 800), (1, 800))]
+    arrival = _cuda(np.sort(rng.integers(0, 60 * n, size=n))[None, :], np.int64)
+    policy = _cuda([1])
+    other = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(other):
+        sim = maps.simulate(8, 50000, 850000, arrival, *requests, policy)
+    done = torch.cuda.Event()
+    done.record(other)
+    got = _gpu(seg, p, g, U, u_max, cap, Q, a_p, a_U, 0, 5)   # ends with a synchronize
+    _compare(got, r, q_after, "a compute unit less")
+    launched = min(D, torch.cuda.get_device_properties(0).multi_processor_count - 1)
+    say(f"[commit] a compute unit less: {got['owners']} of {launched} owners, serial from {got['resume']}")
+    assert got["entry"] & RUN and got["resume"] == A and 0 < got["owners"] < launched
+    assert int(sim.dev_err.item()) == 0
 
 
 def test_ties_and_empty_decoders(orc):
