@@ -144,6 +144,10 @@ def test_rounds(orc, D, A, u_max, room):
     got = _gpu(seg, p, g, U, u_max, cap, Q, a_p, a_U, 0, rr, waits=PATIENT)
     _compare(got, r, q_after, f"rounds D={D} A={A} {room}")
     say(f"[commit] rounds D={D} A={A} {room}: entry {got['entry']:#x}, {got['owners']} owners, serial from {got['resume']}")
+    # who placed the arrivals: the rounds, the rounds until too few of a window fit, or the serial chain alone
+    assert got["entry"] & (DECLINED if room == "long queues" else RUN)
+    first, last = {"most": (A, A), "half": (1, A), "none": (0, 0), "long queues": (0, 0)}[room]
+    assert first <= got["resume"] <= last
 
 
 @pytest.mark.parametrize("waits", [(0, MOST, MOST, MOST), (10**8, 0, MOST, MOST), (10**8, MOST, 0, MOST),
@@ -197,6 +201,91 @@ def test_rounds_without_a_compute_unit(orc):
     say(f"[commit] a compute unit less: {got['owners']} of {launched} owners, serial from {got['resume']}")
     assert got["entry"] & RUN and got["resume"] == A and 0 < got["owners"] < launched
     assert int(sim.dev_err.item()) == 0
+
+
+def _two_batches(orc, seed):
+    """Two batches for the rounds: inputs, and what the oracle makes of them."""
+    out = []
+    for D, A, u_max in ((300, 700, 2000), (65, 500, 3000)):
+        rng = np.random.default_rng(seed + D)
+        seg, p, g, U, a_p, a_U = _random_case(rng, D, 12, A, u_max)
+        cap = (orc.project(seg, p, g, U) + rng.integers(0, 60000, size=D)).astype(np.int32)
+        Q = rng.integers(0, 7, size=D)
+        out.append(((seg, p, g, U, u_max, cap, Q, a_p, a_U), orc.place_commit(seg, p, g, U, cap, Q, a_p, a_U, rr_offset=3)))
+    return out
+
+
+class _Call:
+    """maps.place_commit with its buffers, for calls on several streams and under capture."""
+
+    def __init__(self, seg, p, g, U, u_max, cap, Q, a_p, a_U):
+        import torch
+
+        import paper_2609_15359_amd as maps
+        self.snap, _, self.err = maps.project(_cuda(seg, np.int64), _cuda(p), _cuda(g), _cuda(U), u_max)
+        self.args = [_cuda(cap), _cuda(Q), _cuda(a_p), _cuda(a_U)]
+        self.ws = torch.empty(maps.place_commit_workspace_bytes(len(cap), u_max), dtype=torch.uint8, device="cuda")
+        self.out = None
+        self.place()
+
+    def place(self):
+        import paper_2609_15359_amd as maps
+        self.out = maps.place_commit(self.snap, *self.args, 0, 3, dev_err=self.err, workspace=self.ws, out=self.out)
+
+    def forget(self):
+        for t in (self.out.choice, self.out.chosen_peak, self.out.chosen_overflow, self.out.queue_out):
+            t.fill_(-7)
+        self.out.flags.fill_(77)
+
+    def check(self, want, tag):
+        o = self.out
+        _compare(dict(choice=o.choice.cpu().numpy(), chosen_peak=o.chosen_peak.cpu().numpy(),
+                      chosen_overflow=o.chosen_overflow.cpu().numpy(), flags=o.flags.cpu().numpy(),
+                      queue_out=o.queue_out.cpu().numpy(), err=int(self.err.item()) & 0xFFFFFFFF), *want, tag)
+
+
+def test_two_streams(orc):
+    """Two calls in flight on two streams, whose owners compete for the compute units."""
+    import torch
+    batches = _two_batches(orc, 40)
+    calls, streams = [_Call(*b) for b, _ in batches], [torch.cuda.Stream() for _ in batches]
+    for turn in range(4):
+        for c in calls:
+            c.forget()
+        torch.cuda.synchronize()
+        for c, s in list(zip(calls, streams))[:: 1 if turn % 2 else -1]:
+            with torch.cuda.stream(s):
+                c.place()
+        torch.cuda.synchronize()
+        for i, (c, (_, want)) in enumerate(zip(calls, batches)):
+            c.check(want, f"two streams, turn {turn}, call {i}")
+
+
+def test_capture_and_replay(orc):
+    """A captured call, replayed on other arrivals, capacities and queues with eager work between the replays."""
+    import torch
+    (seg, p, g, U, u_max, cap, Q, a_p, a_U), _ = _two_batches(orc, 50)[0]
+    call, stream = _Call(seg, p, g, U, u_max, cap, Q, a_p, a_U), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        call.place()
+    rng = np.random.default_rng(6)
+    for turn in range(4):
+        if turn:
+            cap, Q = rng.permutation(cap), rng.permutation(Q)
+            a_p, a_U = rng.permutation(a_p), rng.permutation(a_U)
+        want = orc.place_commit(seg, p, g, U, cap, Q, a_p, a_U, rr_offset=3)
+        for old, x in zip(call.args, (cap, Q, a_p, a_U)):
+            old.copy_(_cuda(x))
+        call.forget()
+        graph.replay()
+        torch.cuda.synchronize()
+        call.check(want, f"replay, turn {turn}")
+        call.forget()
+        call.place()   # eager, on the same workspace
+        torch.cuda.synchronize()
+        call.check(want, f"eager, turn {turn}")
 
 
 def test_ties_and_empty_decoders(orc):
