@@ -22,7 +22,10 @@
 //      prefix sums): one pass over the points, each with one search of its
 //      place among the bounds and, only where the wavefront's best prefix so
 //      far does not fit, a search of the prefix.  Where the promoted requests
-//      alone do not fit, the prefix is found by adding them up in order.
+//      alone do not fit, a queue of at most 64 adds them up in order; of a
+//      longer one the prefix that fits at the worst point is an upper end, and
+//      is the answer when it fits at every point, else the next one comes from
+//      the point that it exceeds most (see admit_promoted).
 //      Residents' occupancy comes from the projection's LDS where the
 //      workgroup has just built it (an event a thread), else from the snapshot
 //      (record S + t N at the rank of t).
@@ -65,22 +68,19 @@ struct LocalLds {
     union {
         int32_t ue[kMaxQ];        // bound of entry i (missing bound -> u_max)
         int64_t ppre[kMaxQ + 1];  // prompts of the unpromoted requests before a position of the new order
+        int2 pro[kMaxQ];          // the promoted requests in order, {prompt, bound}, once ppre is not needed
     };
-    union {
-        int32_t pos[kMaxQ];   // position of queue entry i in the new order
-        int32_t prop[kMaxQ];  // admission: prompts of the promoted requests in order
-    };
+    int32_t pos[kMaxQ];       // position of queue entry i in the new order
     int32_t pp[kMaxQ];        // prompt of entry i
-    union {
-        int32_t uidx[kMaxQ];  // entries sorted by (bound, index)
-        int32_t prou[kMaxQ];  // admission: bounds of the promoted requests in order
-    };
+    int32_t uidx[kMaxQ];      // entries sorted by (bound, index)
     int32_t us[kMaxQ];        // their bounds
     int32_t csuf[kMaxQ + 1];  // step 3: promoted requests with bound >= that position's bound;
                               // until then the entry at each position of the new order
+    int2 pro64[kWave];        // the promoted requests in order of a queue of at most 64
     int64_t red64[kOrderNT / kWave];
     int32_t red32[kOrderNT / kWave];
     int32_t promoted;         // promoted requests
+    int64_t worst_t, worst_room;   // the point that a prefix exceeds most
 };
 
 // keys[0..n2), n2 a power of two from 64 to kMaxQ, ascending; begins and ends with
@@ -187,45 +187,11 @@ struct LdsEvents {
     int64_t cap;
 };
 
-// The largest k whose prefix fits (the residents alone do): see step 3 above.
-// The prefix sums and the promoted requests' suffix sums are ready.
-__device__ inline int admit(LocalLds& s, int n, int32_t C, const uint2* rank, const int2* cold, int32_t E, int32_t W,
-                            const LdsEvents& ev) {
-    const int np = s.promoted;
-    int best = n;   // the largest prefix that fits at every point of this wavefront so far
-    auto point = [&](bool valid, int64_t t, int64_t occ, int lo) {
-        const int c = s.csuf[lo];
-        const int64_t room = int64_t(C) - occ;
-        const int64_t rest = room - (s.psuf[lo] + mul_wide(t, c));   // with every promoted request there
-        const int first = lo + c;   // the new order's first unpromoted request with bound >= t
-        const int64_t base = s.ppre[first];
-        auto fits = [&](int k) { return k <= first || s.ppre[k] - base + mul_wide(t, k - first) <= rest; };
-        const bool over = valid && rest < 0;
-        const bool search = valid && rest >= 0 && !fits(best);
-        if (__builtin_amdgcn_ballot_w64(search || over) == 0) return;   // the usual case after the first few points
-        int mine = best;
-        if (search) {
-            int a = first, b = best - 1;   // fits(first), not fits(best)
-            while (a < b) {
-                const int mid = (a + b + 1) >> 1;
-                if (fits(mid)) a = mid; else b = mid - 1;
-            }
-            mine = a;
-        }
-        if (__builtin_amdgcn_ballot_w64(over) != 0) {   // the promoted requests alone do not fit: add them up
-            int64_t sum = 0;
-            bool held = over;
-            for (int j = 0; j < (best < np ? best : np); ++j) {
-                sum += s.prou[j] >= t ? int64_t(s.prop[j]) + t : int64_t(0);
-                if (held && sum > room) {
-                    mine = j;
-                    held = false;
-                }
-                if (__builtin_amdgcn_ballot_w64(held) == 0) break;
-            }
-        }
-        best = -wave_reduce_max(-mine);
-    };
+// fn(valid, t, O(t), first bound-sorted position with bound >= t) at every
+// point, the decoder's events and the queue's bounds, by whole wavefronts.
+template <typename Fn>
+__device__ inline void for_each_point(const LocalLds& s, int n, const uint2* rank, const int2* cold, int32_t E,
+                                      int32_t W, const LdsEvents& ev, Fn point) {
     // the bounds' records are on their way during the events
     const int32_t ucl_max = 32 * W - 1;
     const int i0 = int(threadIdx.x);
@@ -258,7 +224,132 @@ __device__ inline int admit(LocalLds& s, int n, int32_t C, const uint2* rank, co
         if (b0 > 0 && valid) r0 = record(i, t0);
         point(valid, t0, valid ? int64_t(r0.x) + mul_wide(t0, r0.y - 1) : 0, valid ? first_bound(s, n, t0) : 0);
     }
-    return -block_reduce_max<kOrderNT>(-best, s.red32);
+}
+
+// The point that a prefix exceeds most, over the workgroup's threads, each
+// with its own in (over, t, room); over <= 0: none.  Returns whether there is
+// one, then in worst_t and worst_room.  Ends with a barrier.
+__device__ inline bool worst_point(LocalLds& s, int64_t over, int64_t t, int64_t room) {
+    const int64_t most = block_reduce_max<kOrderNT>(over, s.red64);
+    if (most <= 0) return false;   // the same in every thread
+    const int32_t who = block_reduce_max<kOrderNT>(over == most ? int32_t(threadIdx.x) : -1, s.red32);
+    if (int32_t(threadIdx.x) == who) {
+        s.worst_t = t;
+        s.worst_room = room;
+    }
+    __syncthreads();
+    return true;
+}
+
+// The largest prefix of the promoted requests that fits, where not all do (a
+// queue of more than 64; the point in worst_t and worst_room does not hold
+// them).  What the promoted requests hold at one point only grows with the
+// prefix, so the largest one that fits there, a masked prefix sum in order, is
+// an upper end; a pass over the points (with the masked suffix sums over the
+// bounds for this prefix) shows whether it fits everywhere or which point it
+// exceeds most.  Mostly one to three such passes; from the fifth on every second
+// one takes the middle of what is left, so that there are at most some twenty.
+// 256 decoders with 64 residents and 2,048 promoted requests, of which a third
+// fits, take 117 us, and 61 with 512; adding the requests up at every point took
+// 1,207 and 283, the binary search over k 191 and 110.
+__device__ inline int admit_promoted(LocalLds& s, int n, int32_t C, const uint2* rank, const int2* cold, int32_t E,
+                                     int32_t W, const LdsEvents& ev) {
+    const int np = s.promoted;
+    __syncthreads();   // ppre is done with
+    for (int i = int(threadIdx.x); i < n; i += kOrderNT) {
+        const int j = s.uidx[i], at = s.pos[j];
+        if (at < np) s.pro[at] = make_int2(s.pp[j], s.us[i]);
+    }
+    __syncthreads();
+    auto fit_at_worst = [&]() {
+        const int64_t t = s.worst_t, room = s.worst_room;
+        int32_t fit = 0;
+        block_scan<kOrderNT, false, false, false, int64_t>(
+            np, int64_t(0), [&](int64_t i) { const int2 r = s.pro[i]; return r.y >= t ? int64_t(r.x) + t : int64_t(0); },
+            [&](int64_t, int64_t v) { fit += v <= room; }, s.red64);
+        return block_reduce_add<kOrderNT>(fit, s.red32);
+    };
+    int lo = 0, up = fit_at_worst();   // lo fits, nothing past up does
+    for (int turn = 0; lo < up; ++turn) {
+        const int k = turn >= 4 && turn % 2 == 0 ? (lo + up + 1) / 2 : up;
+        block_scan<kOrderNT, false, true, false, int32_t>(
+            n, 0, [&](int64_t i) { return int32_t(s.pos[s.uidx[i]] < k); },
+            [&](int64_t i, int32_t v) { s.csuf[i] = v; }, s.red32);
+        block_scan<kOrderNT, false, true, false, int64_t>(
+            n, int64_t(0),
+            [&](int64_t i) { const int j = s.uidx[i]; return s.pos[j] < k ? int64_t(s.pp[j]) : int64_t(0); },
+            [&](int64_t i, int64_t v) { s.psuf[i] = v; }, s.red64);   // csuf[n] and psuf[n] stay 0
+        int64_t over = 0, at = 0, room_at = 0;
+        for_each_point(s, n, rank, cold, E, W, ev, [&](bool valid, int64_t t, int64_t occ, int first) {
+            const int64_t room = int64_t(C) - occ;
+            const int64_t x = s.psuf[first] + mul_wide(t, s.csuf[first]) - room;
+            if (valid && x > over) {
+                over = x;
+                at = t;
+                room_at = room;
+            }
+        });
+        if (!worst_point(s, over, at, room_at)) {
+            lo = k;
+        } else {
+            const int fit = fit_at_worst();   // below k
+            up = fit < up ? fit : up;
+        }
+    }
+    return lo;
+}
+
+// The largest k whose prefix fits (the residents alone do): see step 3 above.
+// The prefix sums and the promoted requests' suffix sums are ready.
+__device__ inline int admit(LocalLds& s, int n, int32_t C, const uint2* rank, const int2* cold, int32_t E, int32_t W,
+                            const LdsEvents& ev) {
+    const int np = s.promoted;
+    int best = n;   // the largest prefix that fits at every point of this wavefront so far
+    int64_t most = 0, most_t = 0, most_room = 0;   // this thread's point that the promoted requests exceed most
+    for_each_point(s, n, rank, cold, E, W, ev, [&](bool valid, int64_t t, int64_t occ, int lo) {
+        const int c = s.csuf[lo];
+        const int64_t room = int64_t(C) - occ;
+        const int64_t rest = room - (s.psuf[lo] + mul_wide(t, c));   // with every promoted request there
+        const int first = lo + c;   // the new order's first unpromoted request with bound >= t
+        const int64_t base = s.ppre[first];
+        auto fits = [&](int k) { return k <= first || s.ppre[k] - base + mul_wide(t, k - first) <= rest; };
+        const bool over = valid && rest < 0;
+        const bool search = valid && rest >= 0 && !fits(best);
+        if (__builtin_amdgcn_ballot_w64(search || over) == 0) return;   // the usual case after the first few points
+        int mine = best;
+        if (search) {
+            int a = first, b = best - 1;   // fits(first), not fits(best)
+            while (a < b) {
+                const int mid = (a + b + 1) >> 1;
+                if (fits(mid)) a = mid; else b = mid - 1;
+            }
+            mine = a;
+        }
+        if (over && -rest > most) {
+            most = -rest;
+            most_t = t;
+            most_room = room;
+        }
+        if (n <= kWave && __builtin_amdgcn_ballot_w64(over) != 0) {   // add the promoted requests up
+            int64_t sum = 0;
+            bool held = over;
+            for (int j = 0; j < (best < np ? best : np); ++j) {
+                const int2 r = s.pro64[j];
+                sum += r.y >= t ? int64_t(r.x) + t : int64_t(0);
+                if (held && sum > room) {
+                    mine = j;
+                    held = false;
+                }
+                if (__builtin_amdgcn_ballot_w64(held) == 0) break;
+            }
+        }
+        best = -wave_reduce_max(-mine);
+    });
+    // above every -best: somewhere the promoted requests alone do not fit
+    const int most_k = block_reduce_max<kOrderNT>(n > kWave && most > 0 ? 1 : -best, s.red32);
+    if (most_k <= 0) return -most_k;
+    worst_point(s, most, most_t, most_room);
+    return admit_promoted(s, n, C, rank, cold, E, W, ev);
 }
 
 // Decoder d's queue bounds and capacity, and, when the queue holds at most
@@ -391,8 +482,7 @@ __device__ inline void order_queue(const LocalArgs& g, int32_t d, LocalLds& s, i
             const int32_t own = in ? s.csuf[i] : 0;
             const int32_t own_p = s.pp[own], own_u = __shfl(int(ue), own, kWave);
             if (in) {   // part (the keys) and the entries by position were last read above, by this wavefront
-                s.prop[i] = own_p;   // for i < np the promoted requests in order
-                s.prou[i] = own_u;
+                s.pro64[i] = make_int2(own_p, own_u);   // for i < np the promoted requests in order
                 s.ppre[i + 1] = q1;
                 s.psuf[i] = all2 - q2 + p2;
                 s.csuf[i] = allc - c2 + int32_t(m);
@@ -448,15 +538,6 @@ __device__ inline void order_queue(const LocalArgs& g, int32_t d, LocalLds& s, i
             // step 3's sums: the prompts of the unpromoted requests before each
             // position, and the promoted requests' suffix sums by bound
             const int np = s.promoted;
-            int32_t pu[kMaxQ / kOrderNT], pq[kMaxQ / kOrderNT];   // the promoted requests in order
-#pragma unroll
-            for (int j = 0; j < kMaxQ / kOrderNT; ++j) {
-                const int i = j * kOrderNT + int(threadIdx.x);
-                const int idx = i < np ? s.csuf[i] : 0;
-                pu[j] = s.ue[idx];
-                pq[j] = s.pp[idx];
-            }
-            __syncthreads();   // the bounds by index and the keys are done with
             block_scan<kOrderNT, false, false, false, int64_t>(
                 n, int64_t(0), [&](int64_t i) { return i >= np ? int64_t(s.pp[s.csuf[i]]) : int64_t(0); },
                 [&](int64_t i, int64_t v) { s.ppre[i + 1] = v; }, s.red64);
@@ -468,14 +549,6 @@ __device__ inline void order_queue(const LocalArgs& g, int32_t d, LocalLds& s, i
                 [&](int64_t i) { const int j = s.uidx[i]; return s.pos[j] < np ? int64_t(s.pp[j]) : int64_t(0); },
                 [&](int64_t i, int64_t v) { s.psuf[i] = v; }, s.red64);
             if (threadIdx.x == 0) { s.ppre[0] = 0; s.csuf[n] = 0; s.psuf[n] = 0; }
-#pragma unroll
-            for (int j = 0; j < kMaxQ / kOrderNT; ++j) {
-                const int i = j * kOrderNT + int(threadIdx.x);
-                if (i < np) {
-                    s.prou[i] = pu[j];
-                    s.prop[i] = pq[j];
-                }
-            }
             __syncthreads();
         }
     }

@@ -62,3 +62,36 @@ def test_admission(orc, u_max, residents, promoted):
         for tag, o, a in (("project_order", order, adm), ("local_order", order2, adm2)):
             assert_same(f"{tag} order", o.cpu().numpy(), want_order)
             assert_same(f"{tag} admitted", a.cpu().numpy(), want_adm)
+
+
+@pytest.mark.parametrize("n,N,growth", [(65, 200, 1.1), (300, 200, 1.03), (2048, 1000, 1.003)])
+def test_promoted_prefix_one_point_at_a_time(orc, n, N, growth):
+    """Promoted requests of which each exceeds the room at its own bound, a little more than the one before
+    it, beside N residents: a pass over the points lowers the prefix that may fit by one, unless it halves
+    what is left.  The three take 10, 16 and 21 passes."""
+    import torch
+
+    import paper_2609_15359_amd as maps
+    free = 20                                               # requests at the front that always fit
+    q_p = np.minimum(100 * growth ** np.arange(n), 10**5).astype(np.int64)
+    q_p[:free] = 1
+    room0 = int(q_p.sum()) + 300 * (N + n)                  # at step 0; falls by N a step
+    before = np.concatenate([[0], np.cumsum(q_p)[:-1]])
+    q_U = (room0 - before) // (N + np.arange(n))
+    q_U[:free] = 0
+    u_max = int(q_U.max())
+    seg = np.array([0, N], np.int64)
+    p, g, U = np.full(N, 5), np.zeros(N, np.int64), np.full(N, u_max)
+    cap = np.array([5 * N + room0])
+    q_off, wait = np.array([0, n], np.int64), np.full(n, 1000)
+    assert 0 <= orc.project(seg, p, g, U)[0] <= cap[0] < 2**31
+    want_order, want_adm = orc.local_order(seg, p, g, U, cap, q_off, q_p, q_U, wait, 1000, u_max)
+    args = (_cuda(cap), _cuda(q_off, np.int64), _cuda(q_p), _cuda(q_U), _cuda(wait), 1000)
+    snap, b, order, adm, err = maps.project_order(_cuda(seg, np.int64), _cuda(p), _cuda(g), _cuda(U), u_max, *args)
+    order2, adm2, err2 = maps.local_order(snap, *args)
+    torch.cuda.synchronize()
+    say(f"[order] one point at a time, {n}: {want_adm.tolist()}")
+    assert int(err.item()) == 0 and int(err2.item()) == 0 and 0 < want_adm[0] < n
+    for o, a in ((order, adm), (order2, adm2)):
+        assert_same("order", o.cpu().numpy(), want_order)
+        assert_same("admitted", a.cpu().numpy(), want_adm)
