@@ -245,6 +245,12 @@ __device__ inline uint64_t wave_min_u64(uint64_t v) {
     return ~wave_max_u64(~v);
 }
 
+// A value that is the same in every lane, as a scalar.
+__device__ inline int64_t uniform64(int64_t v) {
+    return int64_t((uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int32_t(uint64_t(v) >> 32)))) << 32) |
+                   uint32_t(__builtin_amdgcn_readfirstlane(int32_t(v))));
+}
+
 // Largest-B_eff key of one decoder: (B_eff + 2^52) above (1023 - decoder);
 // 0 (below every key) for a slot past the last decoder.
 __device__ inline uint64_t best_b_key(int64_t B, int32_t d, int32_t D) {
@@ -322,13 +328,19 @@ __device__ __forceinline__ void reserve_run_wide(const StaticArgs& a, int cnt, i
     top = int64_t(kb >> 10) - kBlockLimit;
 }
 
-// The same run in 32 bits: R = B_eff - top (top: the largest B_eff at the
-// run's start), saturated at kRelLow, and the queue keys (Q << 10) | decoder.
-// Taken when the needs sum to less than 2^29 blocks, top < 2^29 and every
-// queue is in [0, 2^21 - 64).  A saturated decoder has B_eff < top - 2^30 < 0:
-// it is never feasible, and never the largest, since the largest stays above
-// top - 2^29; so neither its R nor its B_eff is used.  A feasible R stays
-// above -2^29 after its reservation, the largest above -2^30.
+// The same run in 32 bits: R = kSlots (B_eff - top) + kSlots - 1 - slot (top: the
+// largest B_eff at the run's start; the difference saturated at kRelLow), and the
+// queue keys (Q << 10) | decoder.  Taken when the needs sum to less than 2^25
+// blocks and every queue is in [0, 2^21 - 64).  Under policy MQ every B_eff counts
+// as at most kMostB here: one that starts the run at 2^25 or more holds every
+// need of it, so what it has beyond never decides.  A saturated decoder then has
+// B_eff < 0 under MQ and is never feasible; nor is it ever the largest, which
+// stays above top - 2^25; so neither its R nor its B_eff is used.  A feasible
+// difference stays above -2^26 after its reservation, as does the largest.
+// The slot makes a lane's maximum its lowest decoder with the largest B_eff.
+// An arrival without a feasible decoder takes about 160 ns with one slot a
+// lane, 220 with 4 (256 decoders) and 325 with 16 (1,000); looking for the slot
+// in every register and updating each under a mask took 195, 303 and 650.
 //
 // Runs of arrivals that all find a feasible decoder are matched level by level
 // of the queue lengths instead of one after another.  Every arrival prefers
@@ -345,11 +357,13 @@ __device__ __forceinline__ void reserve_run_wide(const StaticArgs& a, int cnt, i
 // arrivals before it (which the later ones never influence) and goes on after
 // it, over at most as many arrivals at first as that attempt matched.
 // One wavefront issues an instruction about every 4 ns, and that bounds the
-// chain: an arrival takes 114 ns this way, against 220 ns with a wavefront
+// chain: an arrival takes 110 ns this way, against 220 ns with a wavefront
 // minimum each and 375 ns with branches on the chosen lane and slot as well
 // (65,536 arrivals on 256 decoders, 99.8% with a feasible one).
-constexpr int32_t kRelLow = -(1 << 30);
-constexpr int64_t kRunSpan = int64_t(1) << 29;
+static_assert(kResSlots <= 16, "a slot in the four bits that kRelLow leaves free");
+constexpr int32_t kRelLow = -(1 << 26);
+constexpr int64_t kMostB = (int64_t(1) << 26) - 1;
+constexpr int64_t kRunSpan = int64_t(1) << 25;
 constexpr int64_t kRunQueue = int64_t(1) << 21;
 
 __device__ inline uint32_t wave_min_u32(uint32_t v) {
@@ -359,25 +373,49 @@ __device__ inline int32_t wave_max_i32(int32_t v) {
     return wave_last(wave_incl_scan(v, INT32_MIN, [](int32_t x, int32_t y) { return x > y ? x : y; }));
 }
 
+// fn(slot as a constant) for a slot in [kLo, kHi) that is the same in every
+// lane: a tree of scalar branches.
+template <int kLo, int kHi, typename Fn>
+__device__ __forceinline__ void at_slot(int slot, Fn fn) {
+    if constexpr (kHi - kLo == 1) {
+        fn(std::integral_constant<int, kLo>{});
+        // keeps the branches apart: merged, they index the registers by a variable, through memory
+        asm volatile("" ::"i"(kLo));
+    } else {
+        constexpr int kMid = (kLo + kHi) / 2;
+        if (slot < kMid) at_slot<kLo, kMid>(slot, fn);
+        else at_slot<kMid, kHi>(slot, fn);
+    }
+}
+
 template <int kSlots>
 __device__ __forceinline__ void reserve_run(const StaticArgs& a, int cnt, int32_t my_need, int32_t my_rr,
                                             int64_t (&B)[kSlots], int64_t (&Q)[kSlots], int64_t& top,
                                             int32_t& out) {
+    constexpr int kBits = kSlots > 8 ? 4 : kSlots > 4 ? 3 : kSlots > 2 ? 2 : kSlots - 1;
+    constexpr int32_t kLow = (1 << kBits) - 1;
     const int lane = threadIdx.x;
     const bool mq = a.policy == MAPS_POLICY_MQ;
+    const int64_t most = mq ? kMostB : INT64_MAX;
+    top = uniform64(top);
+    const bool capped = top > most;
+    const int64_t ref = capped ? most : top;
     int32_t R[kSlots], R0[kSlots];
     uint32_t K[kSlots];
 #pragma unroll
     for (int s = 0; s < kSlots; ++s) {
         const int32_t d = lane + s * kWave;
-        const int64_t r = B[s] - top;
+        int64_t r = B[s] - ref;
+        if (capped) r = r < 0 ? r : 0;
         // past the last decoder: below every threshold and every maximum
-        R0[s] = R[s] = d >= a.D ? INT32_MIN : r > kRelLow ? int32_t(r) : kRelLow;
+        R0[s] = R[s] = d >= a.D ? INT32_MIN : (r > kRelLow ? int32_t(r) : kRelLow) * (1 << kBits) + (kLow - s);
         K[s] = (uint32_t(Q[s]) << 10) | uint32_t(d);
     }
-    // a decoder holds the need when R >= need - top
-    const int64_t thr64 = int64_t(my_need) - top;
-    const int32_t my_thr = thr64 < int64_t(INT32_MAX) ? int32_t(thr64) : INT32_MAX;
+    // a decoder holds the need when R >= 2^kBits (need - ref); under MC ref may lie far above, then the largest does
+    const int64_t thr64 = int64_t(my_need) - ref;
+    const int32_t my_thr = thr64 >= (INT32_MAX >> kBits) ? INT32_MAX
+                                                         : (thr64 > kRelLow ? int32_t(thr64) : kRelLow) * (1 << kBits);
+    const int32_t my_cost = my_need * (1 << kBits);
     // the first arrival at or after `cur` with any bit of `set`, else 64
     auto first_from = [&](uint64_t set, int cur) {
         set = set >> cur << cur;
@@ -396,94 +434,105 @@ __device__ __forceinline__ void reserve_run(const StaticArgs& a, int cnt, int32_
             ++cur;
             continue;
         }
-        int32_t m = R[0];
+        int32_t m;
+        for (;;) {
+            int32_t mine = R[0];
 #pragma unroll
-        for (int s = 1; s < kSlots; ++s) m = R[s] > m ? R[s] : m;
-        m = wave_max_i32(m);
+            for (int s = 1; s < kSlots; ++s) mine = R[s] > mine ? R[s] : mine;
+            m = wave_max_i32(mine);
+            const int32_t thr = __builtin_amdgcn_readlane(my_thr, cur);
+            if (mq && m >= thr) break;
+            // the lowest decoder with the largest B_eff
+            const int l = __ffsll((unsigned long long)__builtin_amdgcn_ballot_w64(mine == m)) - 1;
+            const int slot = kLow - (m & kLow);
+            const int32_t cost = lane == l ? __builtin_amdgcn_readlane(my_cost, cur) : 0;
+            const uint32_t joins = lane == l ? 1024u : 0u;
+            at_slot<0, kSlots>(slot, [&](auto s) {
+                R[s] -= cost;
+                K[s] += joins;
+            });
+            out = lane == cur ? (slot * kWave + l) | (m >= thr ? 1 << 30 : 0) : out;
+            ++cur;
+            if (cur >= cnt || ((no_bound >> cur) & 1) != 0) break;
+        }
+        if (cur >= cnt || ((no_bound >> cur) & 1) != 0) continue;
         // up to the first arrival that no decoder holds now or that has no bound
-        int end = mq ? first_from(no_bound | __builtin_amdgcn_ballot_w64(my_thr > m), cur) : cur;
-        if (end > cur) {
-            end = end < cur + span ? end : cur + span;
-            span = span < kWave ? 2 * span : kWave;
-            int32_t R1[kSlots];
-            uint32_t K1[kSlots];
+        int end = first_from(no_bound | __builtin_amdgcn_ballot_w64(my_thr > m), cur);
+        end = end < cur + span ? end : cur + span;
+        span = span < kWave ? 2 * span : kWave;
+        int32_t R1[kSlots];
+        uint32_t K1[kSlots];
 #pragma unroll
-            for (int s = 0; s < kSlots; ++s) { R1[s] = R[s]; K1[s] = K[s]; }
-            for (;;) {
-                uint64_t wait = range(cur, end);
-                uint32_t level = 0;   // every shorter queue is done
-                while (wait != 0) {
-                    const bool mine = ((wait >> lane) & 1) != 0;
-                    const int32_t low = -wave_max_i32(mine ? -my_thr : -INT32_MAX);
-                    uint32_t k = ~0u;
+        for (int s = 0; s < kSlots; ++s) { R1[s] = R[s]; K1[s] = K[s]; }
+        for (;;) {
+            uint64_t wait = range(cur, end);
+            uint32_t level = 0;   // every shorter queue is done
+            while (wait != 0) {
+                const bool mine = ((wait >> lane) & 1) != 0;
+                const int32_t low = -wave_max_i32(mine ? -my_thr : -INT32_MAX);
+                uint32_t k = ~0u;
 #pragma unroll
-                    for (int s = 0; s < kSlots; ++s) {
-                        const uint32_t k1 = R[s] >= low && K[s] >= level ? K[s] : ~0u;
-                        k = k1 < k ? k1 : k;
-                    }
-                    k = wave_min_u32(k);
-                    if (k == ~0u) break;   // no decoder holds any waiting arrival
-                    const uint32_t top_k = k | 1023u;   // the last key of this queue length
-                    level = top_k + 1;
-#pragma unroll
-                    for (int s = 0; s < kSlots; ++s) {
-                        uint64_t at = __builtin_amdgcn_ballot_w64(R[s] >= low && K[s] <= top_k && K[s] >= k);
-                        while (at != 0 && wait != 0) {
-                            const int l = __ffsll((unsigned long long)at) - 1;
-                            at &= at - 1;
-                            const int32_t r = __builtin_amdgcn_readlane(R[s], l);
-                            const uint64_t c = __builtin_amdgcn_ballot_w64(my_thr <= r) & wait;
-                            if (c == 0) continue;
-                            const int j = __ffsll((unsigned long long)c) - 1;
-                            wait &= ~(1ull << j);
-                            const int32_t need = __builtin_amdgcn_readlane(my_need, j);
-                            const bool own = lane == l;
-                            R[s] -= own ? need : 0;
-                            K[s] += own ? 1024u : 0u;
-                            out = lane == j ? (l + s * kWave) | (1 << 30) : out;
-                        }
-                    }
+                for (int s = 0; s < kSlots; ++s) {
+                    const uint32_t k1 = R[s] >= low && K[s] >= level ? K[s] : ~0u;
+                    k = k1 < k ? k1 : k;
                 }
-                if (wait == 0) break;
-                end = __ffsll((unsigned long long)wait) - 1;
+                k = wave_min_u32(k);
+                if (k == ~0u) break;   // no decoder holds any waiting arrival
+                const uint32_t top_k = k | 1023u;   // the last key of this queue length
+                level = top_k + 1;
 #pragma unroll
-                for (int s = 0; s < kSlots; ++s) { R[s] = R1[s]; K[s] = K1[s]; }
-                span = end - cur > 4 ? end - cur : 4;
-                if (end == cur) break;
+                for (int s = 0; s < kSlots; ++s) {
+                    uint64_t at = __builtin_amdgcn_ballot_w64(R[s] >= low && K[s] <= top_k && K[s] >= k);
+                    if (at == 0 || wait == 0) continue;
+                    // the loop's first instruction at the start of a 32-byte fetch: where
+                    // it fell by chance an arrival took between 1 and 1.12 times as long
+                    asm volatile(".p2align 5");
+                    do {
+                        const int l = __ffsll((unsigned long long)at) - 1;
+                        at &= at - 1;
+                        const int32_t r = __builtin_amdgcn_readlane(R[s], l);
+                        const uint64_t c = __builtin_amdgcn_ballot_w64(my_thr <= r) & wait;
+                        if (c == 0) continue;
+                        const int j = __ffsll((unsigned long long)c) - 1;
+                        wait &= ~(1ull << j);
+                        const int32_t cost = __builtin_amdgcn_readlane(my_cost, j);
+                        const bool own = lane == l;
+                        R[s] -= own ? cost : 0;
+                        K[s] += own ? 1024u : 0u;
+                        out = lane == j ? (l + s * kWave) | (1 << 30) : out;
+                    } while (at != 0 && wait != 0);
+                }
             }
-            if (end > cur) {
-                cur = end;
-                continue;
-            }
-        }
-        // the lowest decoder with the largest B_eff
-        int32_t best = 0;
+            if (wait == 0) break;
+            // the first arrival of the run finds its decoder whatever follows, so this stays above cur
+            end = __ffsll((unsigned long long)wait) - 1;
 #pragma unroll
-        for (int s = kSlots - 1; s >= 0; --s) {
-            const uint64_t at = __builtin_amdgcn_ballot_w64(R[s] == m);
-            best = at != 0 ? s * kWave + (__ffsll((unsigned long long)at) - 1) : best;
+            for (int s = 0; s < kSlots; ++s) { R[s] = R1[s]; K[s] = K1[s]; }
+            span = end - cur > 4 ? end - cur : 4;
+            if (end <= cur) { end = cur + 1; break; }   // unreachable: an end of the loop in any case
         }
-        const int32_t f = m >= __builtin_amdgcn_readlane(my_thr, cur) ? 1 << 30 : 0;
-        const int32_t need = __builtin_amdgcn_readlane(my_need, cur);
-#pragma unroll
-        for (int s = 0; s < kSlots; ++s) {
-            const bool own = lane + s * kWave == best;
-            R[s] -= own ? need : 0;
-            K[s] += own ? 1024u : 0u;
-        }
-        out = lane == cur ? best | f : out;
-        ++cur;
+        cur = end;
     }
     int32_t m = INT32_MIN;
+    uint64_t key = 0;
 #pragma unroll
     for (int s = 0; s < kSlots; ++s) {
         if (lane + s * kWave < a.D) {
-            B[s] += R[s] - R0[s];
+            B[s] += (R[s] - R0[s]) >> kBits;
             Q[s] = int64_t(K[s] >> 10);
         }
         m = R[s] > m ? R[s] : m;
     }
-    top += wave_max_i32(m);
+    if (!capped) {
+        top += wave_max_i32(m) >> kBits;
+    } else {
+#pragma unroll
+        for (int s = 0; s < kSlots; ++s) {
+            const uint64_t k = best_b_key(B[s], lane + s * kWave, a.D);
+            key = k > key ? k : key;
+        }
+        top = int64_t(wave_max_u64(key) >> 10) - kBlockLimit;
+    }
 }
 
 template <int kSlots>
@@ -521,16 +570,13 @@ __global__ __launch_bounds__(kWave) void static_reserve(StaticArgs a) {
         rr = rr >= a.D ? rr - a.D : rr;
         int32_t out = 0;
         const int cnt = a.A - c0 < kWave ? int(a.A - c0) : kWave;
-        // the run's needs, the largest B_eff and the queues decide the width (the same in every lane)
-        int64_t qmax = 0, qmin = 0;
+        // the run's needs and the queues decide the width (the same in every lane)
+        bool long_queue = false;   // or a negative one
 #pragma unroll
-        for (int s = 0; s < kSlots; ++s) {
-            qmax = Q[s] > qmax ? Q[s] : qmax;
-            qmin = Q[s] < qmin ? Q[s] : qmin;
-        }
-        const bool queues = __builtin_amdgcn_ballot_w64(qmin < 0 || qmax + kWave >= kRunQueue) == 0;
+        for (int s = 0; s < kSlots; ++s) long_queue |= uint64_t(Q[s]) >= uint64_t(kRunQueue - kWave);
+        const bool queues = __builtin_amdgcn_ballot_w64(long_queue) == 0;
         const int64_t need_sum = wave_reduce_add(my_need > 0 ? my_need : int64_t(0));
-        if (queues && need_sum < kRunSpan && top < kRunSpan)
+        if (queues && need_sum < kRunSpan)
             reserve_run<kSlots>(a, cnt, int32_t(my_need), my_rr, B, Q, top, out);
         else
             reserve_run_wide<kSlots>(a, cnt, my_need, my_rr, B, Q, top, range_bad, out);

@@ -197,6 +197,30 @@ def test_records_and_matching(orc, D, A, S):
     _compare(got, want, f"matching D{D} S{S}")
 
 
+@pytest.mark.parametrize("D", [1, 64, 65, 129, 257, 513, 1024])
+def test_largest_with_reservation(orc, D):
+    """Arrivals that take the largest B_eff, one after another: none feasible, some, and policy MC; every
+    decoder alike (the lowest index wins across lanes and slots), a run's needs and the largest B_eff at the
+    limits of the 32-bit form (2^25 blocks) and decoders saturated there (2^26 below the largest)."""
+    rng = np.random.default_rng(D)
+    A = 700
+    a_p, a_U = rng.integers(0, 60, size=A), rng.integers(-1, 400, size=A)
+    big = np.full(A, 2**25 // 64 - 60)                      # 64 of them: just below, at and past 2^25 in one run
+    Q = rng.integers(0, 4, size=D)
+    spread = rng.integers(-3000, 300, size=D)
+    far = np.where(rng.random(D) < 0.5, spread, spread - 2**26 - rng.integers(-40, 40, size=D))
+    for tag, B, U in (("alike", np.full(D, -5), a_U), ("alike with room", np.full(D, 900), a_U),
+                      ("spread", spread, a_U), ("saturated", far, a_U),
+                      ("largest at 2^25", spread + 2**25, a_U), ("needs at 2^25", spread + 2**22, big),
+                      ("around 2^26", far + 2**26, big), ("far above", far + 2**40, big)):
+        for policy in (0, 1):
+            want = orc.place_static(B, Q, 1, a_p, U, policy, 3, True)
+            got = _static(B, Q, 1, a_p, U, policy, 3, True)
+            assert got[5] == 0
+            _compare(got, want, f"D={D} {tag} policy={policy}")
+        say(f"[static] largest D={D} {tag}: feasible {np.mean(want[2] & 1):.3f}")
+
+
 def test_error_bits():
     _, _, _, err = _rsc([0, 2], [5, -1], [0, 0], [3, 3], [100], 16)
     assert err & 1
