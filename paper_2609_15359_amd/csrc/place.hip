@@ -33,7 +33,7 @@ namespace {
 
 constexpr int kNT = 512;          // 8 waves per CU: 256 VGPRs per lane for the arrivals
 constexpr size_t kLdsBytes = 160 * 1024;
-constexpr size_t kRedBytes = 256;   // record path: the tile's bound reduction, past the two buffers
+constexpr size_t kRedBytes = 512;   // record path: the tile's exchanges between wavefronts, past the two buffers
 constexpr int kMaxGroups = 8;
 // Decisions without the pair matrix, groups of this many decoders: the tile
 // first lists the decoders that can be chosen (see list_candidates).  Below
@@ -726,9 +726,10 @@ __device__ __forceinline__ void records_tile(const PlaceArgs& g, const SnapView&
 }
 
 // The decoders of [begin, end) that an arrival of the tile can choose, in
-// index order into `list`; returns their walk.  *tot gets the largest total
-// demand over all of [begin, end), and the errors that a walk over all of them
-// would raise are raised here.  `red` holds 256 bytes.
+// index order into `list` unless that is all of them; returns their walk, the
+// first 64 in *lanes.  *gm gets their maxima, and the largest total demand over
+// all of [begin, end), and the errors that a walk over all of them would raise
+// are raised here.  `red` holds kRedBytes.
 //
 // Whatever its prompt p and bound U, an arrival's peak on decoder d lies in
 //   [base, max(base, min(base + p + U, p + max(PMX_E, U)))],
@@ -738,93 +739,209 @@ __device__ __forceinline__ void records_tile(const PlaceArgs& g, const SnapView&
 // decoders differ in load by more than one request's demand that leaves a
 // handful: 1,048,576 arrivals on 1,024 overloaded decoders took 378 us over
 // every pair and take 15 us.
+//
+// Where no decoder is ruled out the list only costs time.  Up to 64 decoders
+// every wavefront holds them all, one a lane, and the tile's largest values are
+// the only exchange between wavefronts.  Of more, everything known at one point
+// goes through one exchange, and up to kNT headers are read once.  All in 32
+// bits: a value past them means an arrival that could overflow a peak, which is
+// an error.  With an exchange for each value the list added 3 us to a kernel of
+// 13 (64 to 4,096 arrivals on 256 decoders in 8 groups, equal queues and room),
+// now 0.3 to 0.6; where nearly all are ruled out the kernel takes 5.2 us, not 7.0.
 template <int kAPT, int kPolicy>
 __device__ __forceinline__ Walk list_candidates(const PlaceArgs& g, const SnapView& V, int32_t begin, int32_t end,
-                                                const int32_t (&rp)[kAPT], const int32_t (&rU)[kAPT], int64_t* red,
-                                                uint16_t* list, int64_t* tot) {
+                                                const int32_t (&rp)[kAPT], const int32_t (&rU)[kAPT], int32_t* red,
+                                                uint16_t* list, GroupMax* gm, DecLanes* lanes) {
     constexpr int kWaves = kNT / kWave;
     const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
+    // maximum over the wavefronts' values of one exchange
+    auto over_waves = [&](const int32_t* x) {
+        int32_t v = x[0];
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) v = x[w] > v ? x[w] : v;
+        return v;
+    };
+    int32_t* r_arr = red;                      // [3][kWaves] p, U, p + U
+    int32_t* r_key = red + 3 * kWaves;         // [2][kWaves] least of the largest keys, total demand
+    int32_t* r_cnt = red + 5 * kWaves;         // [2][kWaves] candidates of alternate rounds
+    int32_t* r_max = red + 7 * kWaves;         // [4][kWaves] their header maxima
+    static_assert(size_t(11 * kWaves) * 4 <= kRedBytes, "the exchanges");
+
+    // decoder d's values, loaded ahead of the exchange of the arrivals' values
+    struct Dec {
+        DecHeader h;
+        int32_t C, Q;
+    };
+    auto fetch = [&](int32_t d) {
+        Dec x;
+        x.h = V.dec[d];
+        x.C = g.cap[d];
+        x.Q = g.qlen[d];
+        return x;
+    };
+    const bool in_wave = end - begin <= kWave;
+    int32_t d = begin + (in_wave ? lane : int32_t(threadIdx.x));
+    Dec cur{};
+    if (d < end) cur = fetch(d);
+
     int32_t p_hi = 0, U_hi = 0;
-    int64_t pu_hi = 0;
+    uint32_t pu_hi = 0;
 #pragma unroll
     for (int k = 0; k < kAPT; ++k) {
         if (rU[k] < 0) continue;   // placed round robin
         const int32_t p = rp[k] < 0 ? 0 : rp[k];
         p_hi = p > p_hi ? p : p_hi;
         U_hi = rU[k] > U_hi ? rU[k] : U_hi;
-        pu_hi = int64_t(p) + rU[k] > pu_hi ? int64_t(p) + rU[k] : pu_hi;
+        const uint32_t pu = uint32_t(p) + uint32_t(rU[k]);
+        pu_hi = pu > pu_hi ? pu : pu_hi;
     }
-    p_hi = block_reduce_max<kNT>(p_hi, reinterpret_cast<int32_t*>(red));
-    U_hi = block_reduce_max<kNT>(U_hi, reinterpret_cast<int32_t*>(red) + kWaves);
-    pu_hi = block_reduce_max<kNT>(pu_hi, red + kWaves);
+    p_hi = wave_reduce_max(p_hi);
+    U_hi = wave_reduce_max(U_hi);
+    const int32_t pu_w = wave_reduce_max(int32_t(pu_hi ^ 0x80000000u));   // as an ordered signed value
+    if (lane == 0) {
+        r_arr[wid] = p_hi;
+        r_arr[kWaves + wid] = U_hi;
+        r_arr[2 * kWaves + wid] = pu_w;
+    }
     const int64_t n_total = load_uniform(&V.hdr->n_total);
+    __syncthreads();
+    p_hi = over_waves(r_arr);
+    U_hi = over_waves(r_arr + kWaves);
+    pu_hi = uint32_t(over_waves(r_arr + 2 * kWaves)) ^ 0x80000000u;
 
-    // least and largest key of decoder d over the tile; false: its slice is not valid
-    auto keys = [&](int32_t d, int64_t* lo, int64_t* hi, int64_t* t, uint32_t* err) {
-        const DecHeader h = V.dec[d];
-        const int64_t C = g.cap[d];
-        const int32_t Q = g.qlen[d];
-        *t = h.tot;
-        *err = C < 0 || Q < 0 ? uint32_t(MAPS_ERR_NEG_LEN) : 0u;
-        *lo = INT64_MIN;
-        *hi = INT64_MAX;
-        if (!slice_ok(h, n_total, g.L)) {
+    // least and largest key of a decoder over the tile; false: its slice is not valid
+    auto keys = [&](const Dec& x, int32_t* lo, int32_t* hi, uint32_t* err) {
+        const int64_t C = x.C;
+        *err = x.C < 0 || x.Q < 0 ? uint32_t(MAPS_ERR_NEG_LEN) : 0u;
+        *lo = INT32_MIN;
+        *hi = INT32_MAX;
+        if (!slice_ok(x.h, n_total, g.L)) {
             *err |= MAPS_ERR_SNAPSHOT;
             return false;
         }
         if (C < 0) return true;
-        const int64_t base = h.base_peak;
-        const int64_t up = int64_t(p_hi) + (h.pmx_end > U_hi ? h.pmx_end : U_hi);
+        const int64_t base = x.h.base_peak;
+        const int64_t up = int64_t(p_hi) + (x.h.pmx_end > U_hi ? x.h.pmx_end : U_hi);
         const int64_t least = base - C;
-        int64_t most = base + pu_hi < up ? base + pu_hi : up;
+        int64_t most = base + int64_t(pu_hi) < up ? base + int64_t(pu_hi) : up;
         most = (most > base ? most : base) - C;
+        int64_t l = least, h = most;
         if constexpr (kPolicy == MAPS_POLICY_MQ) {
-            const int64_t Qm = int32_t(uint32_t(Q) + 0x80000000u);   // the key where it is feasible
-            *lo = least > 0 ? least - 1 : (Qm < 0 ? Qm : 0);
-            *hi = most <= 0 ? Qm : (least <= 0 && Qm > most - 1 ? Qm : most - 1);
-        } else {
-            *lo = least;
-            *hi = most;
+            const int64_t Qm = int32_t(uint32_t(x.Q) + 0x80000000u);   // the key where it is feasible
+            l = least > 0 ? least - 1 : (Qm < 0 ? Qm : 0);
+            h = most <= 0 ? Qm : (least <= 0 && Qm > most - 1 ? Qm : most - 1);
         }
+        *lo = l < INT32_MAX ? int32_t(l) : INT32_MAX;
+        *hi = h < INT32_MAX ? int32_t(h) : INT32_MAX;
         return true;
     };
 
-    int64_t best = INT64_MAX, t_max = 0;
+    if (in_wave) {
+        int32_t lo = INT32_MAX, hi = INT32_MAX;
+        uint32_t err = 0;
+        const bool ok = d < end && keys(cur, &lo, &hi, &err);
+        if (err && wid == 0) raise_error(g.dev_err, err);
+        const int32_t best = ~wave_reduce_max(~(ok ? hi : INT32_MAX));
+        gm->tot = wave_reduce_max(d < end ? (cur.h.tot < INT32_MAX ? int32_t(cur.h.tot) : INT32_MAX) : 0);
+        const bool take = ok && lo <= best;
+        const uint64_t m = __builtin_amdgcn_ballot_w64(take);
+        const int32_t n = __popcll(m);
+        gm->records = wave_reduce_max(take ? cur.h.E + 1 : 0);
+        gm->hot_lo = wave_reduce_max(take ? cur.h.hot_lo : 0);
+        gm->hot_hi = ~wave_reduce_max(~(take ? cur.h.hot_hi : INT32_MAX));
+        const int32_t flat = wave_reduce_max(take ? cur.h.flat_lo : 0);
+        gm->flat_lo = flat > gm->hot_lo ? flat : gm->hot_lo;
+        *lanes = DecLanes{int32_t(uint64_t(cur.h.slice_off)), int32_t(uint64_t(cur.h.slice_off) >> 32),
+                          d < end ? cur.h.E : -1, d < end ? cur.h.base_peak : -1, cur.C, cur.Q, cur.h.pmx_end, d};
+        if (n == end - begin) return Walk{begin, end, nullptr};
+        // the candidates to the first lanes, the others behind them
+        const uint64_t below = (1ull << lane) - 1ull;
+        const int32_t to = take ? __popcll(m & below) : n + __popcll(~m & below);
+        auto move = [&](int32_t v) { return __builtin_amdgcn_ds_permute(to * 4, v); };
+        *lanes = DecLanes{move(lanes->off_lo), move(lanes->off_hi), move(lanes->E), move(lanes->base),
+                          move(lanes->C), move(lanes->Q), move(lanes->pmx_end), move(lanes->d)};
+        list += wid * kWave;   // each wavefront its own
+        if (take) list[to] = uint16_t(lane);
+        return Walk{begin, begin + n, list};
+    }
+
+    int32_t best = INT32_MAX, t_max = 0;   // total demands count up to INT32_MAX, which no p + U > 0 leaves room beside
     uint32_t errs = 0;
-    for (int32_t d = begin + int32_t(threadIdx.x); d < end; d += kNT) {
-        int64_t lo, hi, t;
+    const bool one_round = end - begin <= kNT;
+    int32_t lo0 = INT32_MAX;
+    bool ok0 = false;
+    for (; d < end; d += kNT) {
+        if (!one_round && d >= begin + kNT) cur = fetch(d);
+        int32_t hi;
         uint32_t err;
-        const bool ok = keys(d, &lo, &hi, &t, &err);
+        ok0 = keys(cur, &lo0, &hi, &err);
         errs |= err;
+        const int32_t t = cur.h.tot < INT32_MAX ? int32_t(cur.h.tot) : INT32_MAX;
         t_max = t > t_max ? t : t_max;
-        if (ok && hi < best) best = hi;
+        if (ok0 && hi < best) best = hi;
     }
     if (errs) raise_error(g.dev_err, errs);
-    best = -block_reduce_max<kNT>(-best, red);
-    *tot = block_reduce_max<kNT>(t_max, red + kWaves);
-    int32_t* count = reinterpret_cast<int32_t*>(red + 2 * kWaves);   // [2][kWaves]
+    const int32_t best_w = wave_reduce_max(~best), tot_w = wave_reduce_max(t_max);   // ~x: the order reversed
+    if (lane == 0) {
+        r_key[wid] = best_w;
+        r_key[kWaves + wid] = tot_w;
+    }
+    __syncthreads();
+    best = ~over_waves(r_key);
+    gm->tot = over_waves(r_key + kWaves);
     int32_t n = 0;
+    int32_t records = 0, hot_lo = 0, hot_hi = INT32_MAX, flat_lo = 0;
     for (int32_t d0 = begin, round = 0; d0 < end; d0 += kNT, round ^= 1) {
-        const int32_t d = d0 + int32_t(threadIdx.x);
-        int64_t lo = INT64_MAX, hi, t;
-        uint32_t err;
-        const bool take = d < end && keys(d, &lo, &hi, &t, &err) && lo <= best;
+        d = d0 + int32_t(threadIdx.x);
+        bool take = false;
+        if (d < end) {
+            if (!one_round) {
+                int32_t hi;
+                uint32_t err;
+                cur = fetch(d);
+                ok0 = keys(cur, &lo0, &hi, &err);
+            }
+            take = ok0 && lo0 <= best;
+        }
+        if (take) {
+            records = records > cur.h.E + 1 ? records : cur.h.E + 1;
+            hot_lo = hot_lo > cur.h.hot_lo ? hot_lo : cur.h.hot_lo;
+            hot_hi = hot_hi < cur.h.hot_hi ? hot_hi : cur.h.hot_hi;
+            flat_lo = flat_lo > cur.h.flat_lo ? flat_lo : cur.h.flat_lo;
+        }
         const uint64_t m = __builtin_amdgcn_ballot_w64(take);
-        if (lane == 0) count[round * kWaves + wid] = __popcll(m);
+        if (lane == 0) r_cnt[round * kWaves + wid] = __popcll(m);
+        if (d0 + kNT >= end) {   // the last round's exchange carries the maxima as well
+            const int32_t a = wave_reduce_max(records), b = wave_reduce_max(hot_lo), c = wave_reduce_max(~hot_hi),
+                          e = wave_reduce_max(flat_lo);
+            if (lane == 0) {
+                r_max[wid] = a;
+                r_max[kWaves + wid] = b;
+                r_max[2 * kWaves + wid] = c;
+                r_max[3 * kWaves + wid] = e;
+            }
+        }
         __syncthreads();   // the other round's counts were read before this barrier
         int32_t before = 0, all = 0;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) {
-            const int32_t c = count[round * kWaves + w];
+            const int32_t c = r_cnt[round * kWaves + w];
             before += w < wid ? c : 0;
             all += c;
         }
         if (take) list[n + before + __popcll(m & ((1ull << lane) - 1ull))] = uint16_t(d - begin);
         n += all;
     }
+    gm->records = over_waves(r_max);
+    gm->hot_lo = over_waves(r_max + kWaves);
+    gm->hot_hi = ~over_waves(r_max + 2 * kWaves);
+    const int32_t flat = over_waves(r_max + 3 * kWaves);
+    gm->flat_lo = flat > gm->hot_lo ? flat : gm->hot_lo;
     __syncthreads();
     n = __builtin_amdgcn_readfirstlane(n);
-    return Walk{begin, begin + n, list};
+    const Walk w{begin, begin + n, n == end - begin ? nullptr : list};
+    *lanes = load_lanes(g, V, w, begin);
+    return w;
 }
 
 // When every slice of the walk fits an LDS buffer the two buffers alternate;
@@ -849,17 +966,16 @@ __global__ __launch_bounds__(kNT) void place_records(PlaceArgs g) {
         return;
     }
     Walk w{d_begin, d_end, nullptr};
-    int64_t tot = 0;
-    if constexpr (!kPairs) {
-        if (g.list) {
-            char* red = reinterpret_cast<char*>(lds + kAreaUnits);
-            w = list_candidates<kAPT, kPolicy>(g, V, d_begin, d_end, rp, rU, reinterpret_cast<int64_t*>(red),
-                                               reinterpret_cast<uint16_t*>(red + kRedBytes), &tot);
-        }
+    GroupMax gm;
+    DecLanes lanes;
+    if (!kPairs && g.list) {
+        char* red = reinterpret_cast<char*>(lds + kAreaUnits);
+        w = list_candidates<kAPT, kPolicy>(g, V, d_begin, d_end, rp, rU, reinterpret_cast<int32_t*>(red),
+                                           reinterpret_cast<uint16_t*>(red + kRedBytes), &gm, &lanes);
+    } else {
+        lanes = load_lanes(g, V, w, d_begin);
+        gm = group_max(V, w);
     }
-    const DecLanes lanes = load_lanes(g, V, w, d_begin);
-    GroupMax gm = group_max(V, w);
-    if (!kPairs && g.list) gm.tot = tot;
     // the full walk stages rank words, PMX values and cold records: (E + 1) records of 4 + 8 bytes
     if (g.L.W / 2 + (int64_t(gm.records) + 3) / 4 + (int64_t(gm.records) + 1) / 2 <= g.buf_units) {
         if (a0 + kNT * kAPT <= g.A)

@@ -494,6 +494,10 @@ def test_calibrate_fused_launch_selects_missing_quantiles(orc, spins, monkeypatc
     (4800, 6, 300, "over"),      # groups of 600 decoders: more than one listing round
     (4800, 6, 300, "mixed"),
     (200, 20, 900, "equal"),     # equal decoders: every key ties
+    (512, 10, 300, "mixed"),     # groups of 64 decoders, the most that one wavefront holds
+    (513, 10, 300, "mixed"),
+    (4096, 4, 300, "over"),      # groups of 512 decoders: one for each thread
+    (4097, 4, 300, "over"),
 ])
 @pytest.mark.parametrize("policy", [0, 1])
 def test_candidates_without_pairs(orc, D, nmax, A, room, policy):
