@@ -297,6 +297,7 @@ constexpr int kGatherRuns = 16;   // runs a wavefront of the select loads at onc
 constexpr int kStagePer = 36;     // scores per thread the bucket select holds in LDS
 constexpr int kKeep = 24;         // of those, kept in registers across passes where they were gathered at once
 constexpr int kStageReads = 3;    // 16-byte reads of the stage in flight a thread
+constexpr int kFewRuns = 4;       // runs that a waiting workgroup's select loads at once
 constexpr int kRunLoads = 8;      // loads a wavefront keeps in flight along one long run
 constexpr uint32_t kStageScores = uint32_t(kSelNT) * kStagePer;
 constexpr size_t kSelStageBytes = size_t(kStageScores) * 4;
@@ -511,10 +512,12 @@ static_assert(kSelStageBytes + sizeof(SelectLds) + kFastBuckets / 8 <= kLdsPerWo
 // longer runs and larger buckets read a load at a time, 128 buckets of 31,250
 // took 89 us (now 50) and a step with one of 1,000,000 took 630 us (now 393).
 //
-// kHold false: nothing is held, every pass reads the runs a load at a time.
-// For the waiting workgroups' rare use: a second whole copy in their kernel
-// costs the first one registers.
-template <bool kHold>
+// kFull false, for the waiting workgroups' rare use: the runs are read
+// kFewRuns loads at a time and the stage one, with no scores kept in registers
+// (with more in flight the kernel spills: 28 us instead of 16).  All 64 buckets
+// of 1,000,000 selected by every waiting workgroup take 0.80 ms, 1.16 with every
+// pass over the runs a load at a time.
+template <bool kFull>
 __device__ __forceinline__ int32_t select_bucket(const SelectArgs& A, int b, SelectLds& lds) {
     const int nb = A.nb;
     const int64_t chunks = A.chunks;
@@ -558,7 +561,8 @@ __device__ __forceinline__ int32_t select_bucket(const SelectArgs& A, int b, Sel
     }
     int32_t k = int32_t(k64);
     const int top = mx >> 24 ? 24 : (mx >> 16 ? 16 : (mx >> 8 ? 8 : 0));
-    uint32_t held = kHold && nbk <= kStageScores ? nbk : 0;   // scores in LDS (0: still in the runs)
+    constexpr int kReads = kFull ? kStageReads : 1;
+    uint32_t held = nbk <= kStageScores ? nbk : 0;   // scores in LDS (0: still in the runs)
     const bool at_once = held != 0;
     uint4 x[kKeep / 4] = {};
     uint32_t zeros = 0;   // the first pass's digit-0 count of this wavefront
@@ -567,12 +571,27 @@ __device__ __forceinline__ int32_t select_bucket(const SelectArgs& A, int b, Sel
     // runs w, w + kSelWaves, ...; lane q reads run q's table entry and the
     // wavefront shares it.
     auto each_score = [&](auto fn) __attribute__((always_inline)) {
-        if constexpr (!kHold) {
-            for (int64_t r = w; r < chunks; r += kSelWaves) {
-                const uint32_t cn = rcnt[r], s0 = rsrc[r], d0 = roff[r];
-                for (uint32_t i0 = 0; i0 < cn; i0 += kWave) {   // bounds uniform across the wavefront
-                    const uint32_t i = i0 + lane;
-                    fn(i < cn ? uint32_t(sorted[s0 + i]) : 0u, i < cn, d0 + i);
+        if constexpr (!kFull) {
+            for (int64_t r0 = w; r0 < chunks; r0 += kSelWaves * kFewRuns) {
+                uint32_t most = 0;   // of the runs' sizes
+#pragma unroll
+                for (int q = 0; q < kFewRuns; ++q) {
+                    const int64_t r = r0 + q * kSelWaves;
+                    const uint32_t cn = r < chunks ? rcnt[r] : 0u;
+                    most = cn > most ? cn : most;
+                }
+                for (uint32_t i = lane; i - lane < most; i += kWave) {   // whole wavefronts
+                    uint32_t v[kFewRuns];
+#pragma unroll
+                    for (int q = 0; q < kFewRuns; ++q) {
+                        const int64_t r = r0 + q * kSelWaves;
+                        v[q] = r < chunks && i < rcnt[r] ? uint32_t(sorted[rsrc[r] + i]) : 0u;
+                    }
+#pragma unroll
+                    for (int q = 0; q < kFewRuns; ++q) {
+                        const int64_t r = r0 + q * kSelWaves;
+                        if (r < chunks) fn(v[q], i < rcnt[r], roff[r] + i);
+                    }
                 }
             }
             return;
@@ -615,7 +634,7 @@ __device__ __forceinline__ int32_t select_bucket(const SelectArgs& A, int b, Sel
             }
         }
     };
-    if (kHold && at_once) {
+    if (at_once) {
         // Every score also enters the first pass's histogram (its top digit:
         // every score lies below 256 << top) as it arrives, so that pass
         // needs no loop of its own.
@@ -626,6 +645,7 @@ __device__ __forceinline__ int32_t select_bucket(const SelectArgs& A, int b, Sel
         hist_flush_zeros(hist[0], zeros);
         __syncthreads();
         // read beside the first pick rather than after it
+        if constexpr (kFull)
 #pragma unroll
         for (int r = 0; r < kKeep / 4; ++r) {
             if (uint32_t(r) * 4 * kSelNT >= nbk) break;
@@ -643,7 +663,7 @@ __device__ __forceinline__ int32_t select_bucket(const SelectArgs& A, int b, Sel
         if (t < 256) hist[cur ^ 1][t] = 0;   // last read by the pick of the previous pass
         if (!(at_once && pass == 0)) {       // the gather built the first pass
             zeros = 0;
-            if (kHold && held != 0) {
+            if (held != 0) {
                 // four scores of the thread, the first at place i of the stage
                 auto add4 = [&](const uint4& v, uint32_t i) __attribute__((always_inline)) {
                     const uint32_t e[4] = {v.x, v.y, v.z, v.w};
@@ -654,7 +674,7 @@ __device__ __forceinline__ int32_t select_bucket(const SelectArgs& A, int b, Sel
                     }
                 };
                 uint32_t i0 = 0;
-                if (at_once) {
+                if (kFull && at_once) {
 #pragma unroll
                     for (int r = 0; r < kKeep / 4; ++r) {
                         if (uint32_t(r) * 4 * kSelNT >= held) break;
@@ -662,19 +682,19 @@ __device__ __forceinline__ int32_t select_bucket(const SelectArgs& A, int b, Sel
                     }
                     i0 = uint32_t(kSelNT) * kKeep;
                 }
-                for (; i0 < held; i0 += kStageReads * 4 * kSelNT) {
-                    uint4 v[kStageReads];   // inside the stage; read before the histogram's atomics
+                for (; i0 < held; i0 += kReads * 4 * kSelNT) {
+                    uint4 v[kReads];   // inside the stage; read before the histogram's atomics
 #pragma unroll
-                    for (int r = 0; r < kStageReads; ++r)
+                    for (int r = 0; r < kReads; ++r)
                         v[r] = reinterpret_cast<const uint4*>(stage)[i0 / 4 + uint32_t(r) * kSelNT + t];
 #pragma unroll
-                    for (int r = 0; r < kStageReads; ++r) {
+                    for (int r = 0; r < kReads; ++r) {
                         if (i0 + uint32_t(r) * 4 * kSelNT >= held) break;   // uniform
                         add4(v[r], i0 + (uint32_t(r) * kSelNT + t) * 4);
                     }
                 }
             } else {
-                const bool gather = kHold && pass > 0 && matching <= kStageScores;
+                const bool gather = pass > 0 && matching <= kStageScores;
                 each_score([&](uint32_t v, bool has, uint32_t) __attribute__((always_inline)) {
                     const uint32_t y = v >> shift;
                     const bool take = has && (y >> 8) == prefix;

@@ -485,6 +485,18 @@ def test_calibrate_fused_launch_selects_missing_quantiles(orc, spins, monkeypatc
         assert_same(f"{name} q", q, qo)
         assert_same(f"{name} count", cnt, co)
         assert_same(f"{name} U", U, orc.apply_bounds(ap, b.edges, qo, b.u_max))
+    # buckets that just fit the stage, just do not, and take more than one pass over many and long runs
+    rng = np.random.default_rng(3)
+    for n, edges, top in ((36864, [], 30000), (36865, [], 30000), (300001, [], 2**30), (200000, [7], 9)):
+        pred, truth = rng.integers(0, 20, size=n), rng.integers(0, top, size=n)
+        ap = rng.integers(-1, 30, size=3000)
+        edges = np.array(edges, np.int32)
+        q, cnt, U, err = _calib_gpu(pred, truth, edges, 100000, ap, 2**30)
+        assert err == 0
+        qo, co = orc.calibrate(pred, truth, edges, 100000)
+        assert_same(f"{n} q", q, qo)
+        assert_same(f"{n} count", cnt, co)
+        assert_same(f"{n} U", U, orc.apply_bounds(ap, edges, qo, 2**30))
 
 
 @pytest.mark.parametrize("D,nmax,A,room", [
