@@ -148,3 +148,26 @@ def test_queues_outgrow_the_lanes(orc, N, C, tokens):
         assert_same(f"N={N} late routed", got[s]["routed"][:-1], want.routed)
         assert_same(f"N={N} late queue area", got[s]["queue_area"], want.queue_area)
         assert got[s]["finish_ms"][-1] == 2**33 + 7
+
+
+@pytest.mark.parametrize("name,arrival,output", [
+    ("gap of 2^22 - 1", [0, 0], [2**21, 2**21 + 9]),               # the last of the float quotients
+    ("gap of 2^22 + 1", [0, 0], [2**21 + 1, 2**21 + 9]),           # the first of the integer divisions
+    ("three in turn", [0, 0, 0], [2**22 + 5] * 3),
+    ("arrival at 2^22 - 1", [0, 0, 2**22 - 1], [2**22, 2**22 + 2, 7]),
+    ("arrival at 2^22", [0, 0, 2**22], [2**22, 2**22 + 2, 7]),
+    ("arrival at 2^22 + 1", [0, 0, 2**22 + 1], [2**22, 2**22 + 2, 7]),
+    ("longest output in 24 bits", [3, 5, 9], [2**24 - 1, 4, 2**22]),
+    ("output of 2^24", [3, 5, 9], [2**24, 4, 2**22]),               # past the fast form
+])
+def test_long_outputs(orc, name, arrival, output):
+    """Queues that stay as they are over millions of milliseconds, on both sides of where the slices since the
+    last event are divided as floats, and outputs on both sides of the fast form's limit."""
+    n = len(output)
+    prompt, bound = np.arange(n), np.array(output) + 3
+    got, err = _gpu(1, 2**30, 10000, [arrival, arrival], prompt, output, bound, [0, 1])
+    assert err == 0
+    for s in (0, 1):
+        want = orc.simulate(1, 2**30, 10000, np.array(arrival, np.int64), prompt, output, bound, s)
+        _compare(got[s], want, f"{name} policy {s}")
+        say(f"[appa] {name}: done at {want.finish_ms.tolist()}")
