@@ -633,7 +633,7 @@ __global__ __launch_bounds__(kSerialNT) void commit_serial(CommitArgs a) {
 // serial chain goes on after that round.
 // 4,096 arrivals on 256 decoders (queues of 0..63, bounds of 3,600 steps on
 // average, 32,768 at most), nearly all feasible: 49 ms in the serial chain
-// before, 4.1 ms with the rounds and the commits by rows.
+// before, 3.7 ms with the rounds and the commits by rows.
 constexpr int kReviewRounds = 8;             // rounds after which the master looks at what they held
 constexpr uint32_t kCheckIn = 20000;         // 200 us at the 100 MHz of the constant clock
 constexpr uint32_t kOwnerDecoders = 64;      // the most an owner takes
@@ -1038,7 +1038,14 @@ extern "C" maps_status maps_internal_place_commit(const void* snapshot, int32_t 
     a.owners = rounds ? (D < cus - 1 ? D : cus - 1) : 0;
     if (a.owners > kMaxOwners) a.owners = kMaxOwners;
     auto serial = D <= kSerialNT ? commit_serial<true> : commit_serial<false>;
-    auto round = D <= 4 * kWave ? commit_rounds<4> : commit_rounds<kRoundDecoders / kWave>;
+    // The master walks its slots at every arrival: as few as hold the decoders
+    // (1,024 arrivals on 257 decoders 1.85 ms with 8 slots, 2.40 with 16; on 16
+    // decoders 2.26 ms with 1 slot, 2.40 with 4).
+    auto round = D <= 1 * kWave   ? commit_rounds<1>
+                 : D <= 2 * kWave ? commit_rounds<2>
+                 : D <= 4 * kWave ? commit_rounds<4>
+                 : D <= 8 * kWave ? commit_rounds<8>
+                                  : commit_rounds<kRoundDecoders / kWave>;
     // dynamic LDS of the chain: queue lengths and capacities, then as many
     // staged range entries as the workgroup's LDS holds beside the kernel's
     // static LDS (less 256 bytes for the alignment of the dynamic part)
