@@ -288,24 +288,28 @@ __device__ __forceinline__ void write_partials(const PlaceArgs& g, int32_t grp, 
 // are written to the other buffer before the single barrier of the next
 // step.  Every lookup then stays in LDS.
 //
-// Where a slice of the group may exceed a buffer (kMixed), the slices take the
-// two ends of the whole area in turn: a slice that fits beside the one before
-// costs the same single barrier, one that overlaps it waits for a second
-// barrier before it is written.  Only a slice that exceeds the area is read
-// from HBM altogether (with the thresholds, so that only lanes past one read a
-// cold record).  262,144 arrivals on 256 decoders of up to 8,192 residents
-// early in their outputs took 303 us with every slice past a buffer read
-// through L2 four arrivals a thread at a time, and take 124 us.
+// Where a slice of the group may exceed a buffer (kMixed) and a thread holds 8
+// arrivals or more (kArea), the slices take the two ends of the whole area in
+// turn: a slice that fits beside the one before costs the same single barrier,
+// one that overlaps it waits for a second barrier before it is written.  Only a
+// slice that exceeds the area is read from HBM altogether (with the thresholds,
+// so that only lanes past one read a cold record).  With fewer arrivals a
+// thread every slice past a buffer is read that way: staging it takes longer
+// than the lookups of so few.  256 decoders of up to 8,192 residents early in
+// their outputs, read against staged: 4,096 arrivals (1 a thread) 41 and 65 us,
+// 32,768 (2) 61 and 70, 65,536 (4) 80 and 76 (with heavy-tailed outputs of up to
+// 65,536 tokens 64 and 74), 131,072 (8) 133 and 88, 262,144 (16) 296 and 138.
 // ---------------------------------------------------------------------------
 constexpr int kStage = 7;   // 16-byte units per thread staged in registers: a whole LDS buffer
 constexpr int kStageArea = 16;   // the same for the area, 131,072 bytes; the tile's reduction and list follow it
 constexpr int32_t kAreaUnits = kStageArea * kNT;
+constexpr int kAreaArrivals = 8;   // arrivals a thread from which on they are staged
 static_assert(2 * kStage <= kStageArea && size_t(kAreaUnits) * 16 + kRedBytes + size_t(kListMax) * 2 <= kLdsBytes,
               "two buffers in the area, the reduction and the list past it");
 
-// kCompact (kMixed, whose staging takes up to kStageArea rows of registers):
-// what follows from the bound is computed at each pair, five instructions,
-// instead of held.
+// kCompact (16 arrivals with kArea, whose staging takes up to kStageArea rows of
+// registers): what follows from the bound is computed at each pair, five
+// instructions, instead of held (8 arrivals: 88 us held, 93 computed).
 template <int kAPT_, bool kCompact_>
 struct RecArrivals {
     static constexpr int kAPT = kAPT_;
@@ -527,20 +531,21 @@ __device__ __forceinline__ void records_tile(const PlaceArgs& g, const SnapView&
     const int32_t d_begin = w.begin, d_end = w.end;   // places of the walk
     const int64_t n_total = load_uniform(&V.hdr->n_total);
     const int32_t ucl_max = 32 * L.W - 1;          // ranks above every event
-    constexpr int kRows = kMixed ? kStageArea : kStage;
-    const int32_t room = kMixed ? kAreaUnits : g.buf_units;   // the largest staged slice
+    constexpr bool kArea = kMixed && kAPT >= kAreaArrivals;   // slices past a buffer are staged
+    constexpr int kRows = kArea ? kStageArea : kStage;
+    const int32_t room = kArea ? kAreaUnits : g.buf_units;    // the largest staged slice
     const int64_t tile_n = g.A - a0 < kNT * kAPT ? g.A - a0 : kNT * kAPT;
 
     // LDS address of buffer 0 (where the dynamic LDS starts)
     const uint32_t lds_off = uint32_t(size_t((__attribute__((address_space(3))) char*)lds));
-    using Arrivals = RecArrivals<kAPT, kMixed>;
+    using Arrivals = RecArrivals<kAPT, kArea && kAPT >= 16>;
     Arrivals s;
     s.lds_off = lds_off;
     s.ucl_max = ucl_max;
     check_arrivals<kAPT>(g, gm.tot, rp, rU, s.p, s.U);
 #pragma unroll
     for (int k = 0; k < kAPT; ++k) {
-        if constexpr (!kMixed) {
+        if constexpr (!Arrivals::kCompact) {
             s.neg_[k] = s.U[k] < 0 ? -1 : 0;
             const uint32_t uc = s.clamped(s.U[k]);
             s.roff_[k] = (uc >> 5) * 8u + lds_off;
@@ -615,7 +620,7 @@ __device__ __forceinline__ void records_tile(const PlaceArgs& g, const SnapView&
         DecLanes lanes = load_lanes(g, V, w, d_begin);
         int32_t lanes0 = d_begin;
         v4i stage[kRows];
-        int32_t before = 0;   // kMixed: units of the other end that the decoder before this one holds
+        int32_t before = 0;   // kArea: units of the other end that the decoder before this one holds
         DecHeader h = lane_header(lanes, 0);
         bool h_ok = d_begin < d_end && slice_ok(h, n_total, L) && (kMixed || fits(h));
         if (h_ok && fits(h)) stage_next(stage, h);
@@ -631,9 +636,9 @@ __device__ __forceinline__ void records_tile(const PlaceArgs& g, const SnapView&
             if (threadIdx.x == 0 && (C < 0 || Q < 0)) raise_error(g.dev_err, MAPS_ERR_NEG_LEN);
             if (!valid && threadIdx.x == 0) raise_error(g.dev_err, MAPS_ERR_SNAPSHOT);
             const int32_t units = in_lds ? int32_t(staged(cur)) : 0;
-            const int32_t at = kOdd ? (kMixed ? kAreaUnits - units : kStage * kNT) : 0;
+            const int32_t at = kOdd ? (kArea ? kAreaUnits - units : kStage * kNT) : 0;
             int4* slice = lds + at;
-            if constexpr (kMixed) {
+            if constexpr (kArea) {
                 if (before + units > kAreaUnits) __syncthreads();   // uniform: every wave is done with the one before
                 before = units;
             }
@@ -644,7 +649,7 @@ __device__ __forceinline__ void records_tile(const PlaceArgs& g, const SnapView&
                 // kStage * kNT units fit it; in the whole area they are left out.
 #pragma unroll
                 for (int j = 0; j < kRows; ++j)
-                    if (j * kNT < units && (!kMixed || int(threadIdx.x) + j * kNT < units))
+                    if (j * kNT < units && (!kArea || int(threadIdx.x) + j * kNT < units))
                         reinterpret_cast<v4i*>(slice)[int(threadIdx.x) + j * kNT] = stage[j];
             }
             if (d + 1 < d_end) {

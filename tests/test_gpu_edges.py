@@ -543,8 +543,13 @@ def test_candidates_without_pairs(orc, D, nmax, A, room, policy):
     ([5000, 4600, 9000, 30, 0, 7000], 20000, 3000, True),            # slices that overlap at the two ends, and small ones
     ([12000, 9800, 200, 13000, 12500, 40, 10000], 60000, 1500, True),  # slices past the whole area, read through L2
     ([12000, 9800, 200, 13000, 12500, 40, 10000], 60000, 1500, False),
-    ([4700] * 3, 20000, 140000, True),                               # 16 arrivals a thread, a ragged last tile
+    ([4700] * 3, 20000, 140000, True),                               # 2 arrivals a thread, a ragged last tile
     ([4700] * 3, 20000, 140000, False),
+    ([5000, 4600, 9000, 30, 0, 7000, 12000, 4700], 20000, 70001, True),     # 4 a thread: read through L2
+    ([5000, 4600, 9000, 30, 0, 7000, 12000, 4700], 20000, 140001, True),    # 8 a thread: staged
+    ([5000, 4600, 9000, 30, 0, 7000, 12000, 4700], 20000, 140001, False),
+    ([5000, 4600, 9000, 30, 0, 7000, 12000, 4700], 20000, 262145, True),    # 16 a thread
+    ([5000, 4600, 9000, 30, 0, 7000, 12000, 4700], 20000, 262145, False),
     ([10, 10], 300000, 600, True),                                   # rank words past the area
 ])
 @pytest.mark.parametrize("policy", [0, 1])
