@@ -22,10 +22,10 @@
 //      prefix sums): one pass over the points, each with one search of its
 //      place among the bounds and, only where the wavefront's best prefix so
 //      far does not fit, a search of the prefix.  Where the promoted requests
-//      alone do not fit, a queue of at most 64 adds them up in order; of a
-//      longer one the prefix that fits at the worst point is an upper end, and
-//      is the answer when it fits at every point, else the next one comes from
-//      the point that it exceeds most (see admit_promoted).
+//      alone do not fit, a few of them are added up in order; of more, the
+//      prefix that fits at the worst point is an upper end, and is the answer
+//      when it fits at every point, else the next one comes from the point
+//      that it exceeds most (see admit_promoted).
 //      Residents' occupancy comes from the projection's LDS where the
 //      workgroup has just built it (an event a thread), else from the snapshot
 //      (record S + t N at the rank of t).
@@ -41,6 +41,12 @@ namespace order {
 
 constexpr int kOrderNT = 1024;
 constexpr int kMaxQ = MAPS_MAX_LOCAL_QUEUE;
+// Up to so many promoted requests are added up in order at each point where
+// they do not all fit; more of them go through admit_promoted, which takes some
+// 10 us whatever their number, against 0.3 us a request (a queue of 200 beside
+// 64 residents: 30, 35, 40 and 45 us with 4, 24, 48 and 64 of them added up, 40 to
+// 44 us the other way).
+constexpr int kAddUp = 48;
 
 struct LocalArgs {
     SnapLayout L;
@@ -76,7 +82,7 @@ struct LocalLds {
     int32_t us[kMaxQ];        // their bounds
     int32_t csuf[kMaxQ + 1];  // step 3: promoted requests with bound >= that position's bound;
                               // until then the entry at each position of the new order
-    int2 pro64[kWave];        // the promoted requests in order of a queue of at most 64
+    int2 pro64[kWave];        // the promoted requests in order, up to 64
     int64_t red64[kOrderNT / kWave];
     int32_t red32[kOrderNT / kWave];
     int32_t promoted;         // promoted requests
@@ -241,9 +247,8 @@ __device__ inline bool worst_point(LocalLds& s, int64_t over, int64_t t, int64_t
     return true;
 }
 
-// The largest prefix of the promoted requests that fits, where not all do (a
-// queue of more than 64; the point in worst_t and worst_room does not hold
-// them).  What the promoted requests hold at one point only grows with the
+// The largest prefix of the promoted requests that fits, where not all do (the
+// point in worst_t and worst_room does not hold them).  What the promoted requests hold at one point only grows with the
 // prefix, so the largest one that fits there, a masked prefix sum in order, is
 // an upper end; a pass over the points (with the masked suffix sums over the
 // bounds for this prefix) shows whether it fits everywhere or which point it
@@ -330,7 +335,7 @@ __device__ inline int admit(LocalLds& s, int n, int32_t C, const uint2* rank, co
             most_t = t;
             most_room = room;
         }
-        if (n <= kWave && __builtin_amdgcn_ballot_w64(over) != 0) {   // add the promoted requests up
+        if (np <= kAddUp && __builtin_amdgcn_ballot_w64(over) != 0) {   // add the promoted requests up
             int64_t sum = 0;
             bool held = over;
             for (int j = 0; j < (best < np ? best : np); ++j) {
@@ -346,7 +351,7 @@ __device__ inline int admit(LocalLds& s, int n, int32_t C, const uint2* rank, co
         best = -wave_reduce_max(-mine);
     });
     // above every -best: somewhere the promoted requests alone do not fit
-    const int most_k = block_reduce_max<kOrderNT>(n > kWave && most > 0 ? 1 : -best, s.red32);
+    const int most_k = block_reduce_max<kOrderNT>(np > kAddUp && most > 0 ? 1 : -best, s.red32);
     if (most_k <= 0) return -most_k;
     worst_point(s, most, most_t, most_room);
     return admit_promoted(s, n, C, rank, cold, E, W, ev);
@@ -538,6 +543,10 @@ __device__ inline void order_queue(const LocalArgs& g, int32_t d, LocalLds& s, i
             // step 3's sums: the prompts of the unpromoted requests before each
             // position, and the promoted requests' suffix sums by bound
             const int np = s.promoted;
+            if (np <= kWave && int(threadIdx.x) < np) {   // the scan's barriers precede its writes over the bounds
+                const int idx = s.csuf[threadIdx.x];
+                s.pro64[threadIdx.x] = make_int2(s.pp[idx], s.ue[idx]);
+            }
             block_scan<kOrderNT, false, false, false, int64_t>(
                 n, int64_t(0), [&](int64_t i) { return i >= np ? int64_t(s.pp[s.csuf[i]]) : int64_t(0); },
                 [&](int64_t i, int64_t v) { s.ppre[i + 1] = v; }, s.red64);

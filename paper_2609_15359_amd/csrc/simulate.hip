@@ -377,7 +377,7 @@ __device__ inline bool fits_fast(const SimArgs& a, const int64_t* arr) {
 
 // A value that is the same in every lane, as a scalar.  The compiler takes the
 // loop-carried ones for divergent and would run every branch on them by
-// execution masks (25 instead of 21 ms for 128 simulations).
+// execution masks, about a fifth slower.
 __device__ inline int32_t uniform(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // Minimum of a 32-bit value and maximum of a 64-bit value over lanes 0..7.

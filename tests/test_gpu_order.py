@@ -1,7 +1,8 @@
 """Admission in the local order (maps_local_order, maps_project_order) against
 the CPU oracle, bit for bit, where the prefix search can go wrong: queue
 lengths at the edges of the one-wavefront and one-key-per-thread forms, no,
-some and only promoted requests, capacities from the base peak to past the
+some and only promoted requests and numbers of them at the edges of adding them
+up, capacities from the base peak to past the
 whole queue, and decoders whose events the projection keeps in LDS (with and
 without a dense profile) or not."""
 import numpy as np
@@ -25,7 +26,7 @@ def _cuda(x, dtype=np.int32):
 
 @pytest.mark.parametrize("u_max,residents", [(700, 300), (20000, 900), (20000, 9000)],
                          ids=["profile", "events-in-lds", "events-in-hbm"])
-@pytest.mark.parametrize("promoted", [0.0, 0.1, 1.0])
+@pytest.mark.parametrize("promoted", [0.0, 0.1, 1.0, 47, 48, 49, 64, 65])
 def test_admission(orc, u_max, residents, promoted):
     import torch
 
@@ -46,6 +47,8 @@ def test_admission(orc, u_max, residents, promoted):
     q_U = rng.integers(-1, u_max + 1, size=nq)
     q_U[rng.random(nq) < 0.3] = u_max // 3                  # runs of equal bounds
     wait = np.where(rng.random(nq) < promoted, 1000, 999)
+    if promoted > 1:                                        # so many of each queue
+        wait = np.concatenate([np.where(rng.permutation(k) < promoted, 1000, 999) for k in qlens])
     base = orc.project(seg, p, g, U)
     dev = [_cuda(x) for x in (p, g, U)]
     demand = np.array([(q_p[a:b] + np.maximum(q_U[a:b], 0)).sum() for a, b in zip(q_off, q_off[1:])])
